@@ -126,6 +126,156 @@ __device__ __forceinline__ void quad_normals(uint32_t q_lo, uint32_t q_hi, uint3
     e[3] = t * s;
 }
 
+// ---- several Philox blocks at a time, in phases ----
+//
+// What bounds the noise is VALU issue, and on gfx950 that depends on which
+// instructions meet.  Measured with register-only loops, 8 waves per SIMD
+// (wave instructions per cycle and CU):
+//   * v_xor / v_bitop3 / v_add_u32 / v_mov, f32 add / mul / fma with at most
+//     one scalar-register read between the two: 1.5 - 1.8, two waves of a
+//     SIMD issue together; with two scalar reads 0.9 - 1.0;
+//   * v_mad_u64_u32, v_and_or, v_alignbit, conversions: 0.9, never together
+//     with a v_xor or v_bitop3 of another wave;
+//   * v_log / v_sqrt / v_sin / v_cos: 0.5, alone.
+// Two waves issue together only when both stand at instructions of the first
+// kind, and with a product after every exclusive-or the oldest wave keeps the
+// others waiting at their products.  So a lane takes kQ blocks in lockstep,
+// each step split into a phase of products (or transcendentals) at a raised
+// wave priority and a phase of simple instructions at the normal one: the
+// waves gather at the simple phases and issue them in pairs.  The round keys
+// are stepped in vector registers (one add per key, shared by the kQ blocks)
+// and the 23-bit masking is a bitop3 of vector registers, so that these pair
+// as well.  The member loop of the update alone, 32 members: 2.34 T normals/s
+// as two plain chains (14.1 instructions per normal), 2.80 with kQ = 2 in
+// phases, 2.97 with kQ = 4 (15.2 instructions per normal); without the
+// priorities 2.63, with the keys in scalar registers 2.59 - 2.74, kQ = 8 at
+// half the waves 2.8.  The words and normals are bit for bit those above.
+__device__ __forceinline__ void heavy_phase() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(2);
+}
+__device__ __forceinline__ void simple_phase() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+}
+
+// A wave-uniform value in a vector register.
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
+    uint32_t r;
+    asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(x));
+    return r;
+}
+
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+// kQ Philox4x32-10 blocks at counters (q_lo[i], q_hi, tensor_id, 0) under one
+// key; q_hi, tensor_id and the key are wave-uniform, so the parts of rounds
+// 1 - 3 that depend on nothing else stay on the scalar unit, and round 1's
+// product of q_lo is the same for every key (hoisted out of a member loop).
+template <int kQ>
+__device__ __forceinline__ void philox_quads(const uint32_t q_lo[kQ], uint32_t q_hi,
+                                             uint32_t tensor_id, uint32_t key0, uint32_t key1,
+                                             Words w[kQ]) {
+    static_assert(kDomainNoise == 0u, "the fourth counter word is left out below");
+    const uint64_t pt = static_cast<uint64_t>(kPhiloxM1) * tensor_id;
+    const uint32_t s0 = static_cast<uint32_t>(pt >> 32) ^ q_hi ^ key0;     // c0 after round 1
+    const uint64_t ps = static_cast<uint64_t>(kPhiloxM0) * s0;             // round 2
+    const uint32_t u0 = static_cast<uint32_t>(pt) ^ (key0 + kWeyl0);
+    const uint32_t u2 = static_cast<uint32_t>(ps >> 32) ^ (key1 + kWeyl1);
+    const uint32_t u3 = static_cast<uint32_t>(ps) ^ (key1 + 2 * kWeyl1);   // round 3
+    uint64_t p0[kQ], p1[kQ];
+    uint32_t c0[kQ], c1[kQ], c2[kQ], c3[kQ];
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) {
+        const uint64_t pq = static_cast<uint64_t>(kPhiloxM0) * q_lo[i];
+        c2[i] = static_cast<uint32_t>(pq >> 32) ^ key1;
+        c3[i] = static_cast<uint32_t>(pq) ^ u2;                            // c2 after round 2
+    }
+    heavy_phase();
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) p1[i] = static_cast<uint64_t>(kPhiloxM1) * c2[i];
+    simple_phase();
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) {
+        c0[i] = static_cast<uint32_t>(p1[i] >> 32) ^ u0;
+        c1[i] = static_cast<uint32_t>(p1[i]);
+        c2[i] = c3[i];
+    }
+    heavy_phase();
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) {
+        p0[i] = static_cast<uint64_t>(kPhiloxM0) * c0[i];
+        p1[i] = static_cast<uint64_t>(kPhiloxM1) * c2[i];
+    }
+    simple_phase();
+    uint32_t k0 = in_vgpr(key0 + 2 * kWeyl0), k1 = in_vgpr(key1 + 2 * kWeyl1);
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) {
+        c0[i] = xor3(static_cast<uint32_t>(p1[i] >> 32), c1[i], k0);
+        c2[i] = static_cast<uint32_t>(p0[i] >> 32) ^ u3;
+        c1[i] = static_cast<uint32_t>(p1[i]);
+        c3[i] = static_cast<uint32_t>(p0[i]);
+    }
+#pragma unroll
+    for (uint32_t round = 3; round < 10; ++round) {
+        heavy_phase();
+#pragma unroll
+        for (int i = 0; i < kQ; ++i) {
+            p0[i] = static_cast<uint64_t>(kPhiloxM0) * c0[i];
+            p1[i] = static_cast<uint64_t>(kPhiloxM1) * c2[i];
+        }
+        simple_phase();
+        k0 += kWeyl0;
+        k1 += kWeyl1;
+#pragma unroll
+        for (int i = 0; i < kQ; ++i) {
+            c0[i] = xor3(static_cast<uint32_t>(p1[i] >> 32), c1[i], k0);
+            c2[i] = xor3(static_cast<uint32_t>(p0[i] >> 32), c3[i], k1);
+            c1[i] = static_cast<uint32_t>(p1[i]);
+            c3[i] = static_cast<uint32_t>(p0[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) w[i] = Words{c0[i], c1[i], c2[i], c3[i]};
+}
+
+// Box-Muller on the 2 kQ word pairs of kQ blocks: the radius factor r, and
+// cos / sin of the angle, of pair p = 2 i + h from words (2 h, 2 h + 1) of
+// block i (pair_radius and pair_angle above, in phases).  The callers'
+// multiply-adds follow in the simple phase it ends with.
+template <int kQ>
+__device__ __forceinline__ void box_muller_quads(const Words w[kQ], float r[2 * kQ],
+                                                 float c[2 * kQ], float s[2 * kQ]) {
+    uint32_t mask = 0x007FFFFFu, one = 0x3F800000u;
+    asm("" : "+v"(mask));
+    asm("" : "+v"(one));
+    auto plus_one = [&](uint32_t x) {               // (x & mask) | one
+        return __uint_as_float(__builtin_amdgcn_bitop3_b32(x, mask, one, 0xEA));
+    };
+    float angle[2 * kQ];
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) {
+        r[2 * i] = plus_one(w[i].w0);
+        r[2 * i + 1] = plus_one(w[i].w2);
+        angle[2 * i] = plus_one(w[i].w1);
+        angle[2 * i + 1] = plus_one(w[i].w3);
+    }
+#pragma unroll
+    for (int p = 0; p < 2 * kQ; ++p) r[p] -= 0x1.fffffep-1f;
+    heavy_phase();
+#pragma unroll
+    for (int p = 0; p < 2 * kQ; ++p) c[p] = __builtin_amdgcn_cosf(angle[p]);
+#pragma unroll
+    for (int p = 0; p < 2 * kQ; ++p) s[p] = __builtin_amdgcn_sinf(angle[p]);
+#pragma unroll
+    for (int p = 0; p < 2 * kQ; ++p) r[p] = __builtin_amdgcn_logf(r[p]);
+#pragma unroll
+    for (int p = 0; p < 2 * kQ; ++p) r[p] = __builtin_amdgcn_sqrtf(-r[p]);
+    simple_phase();
+}
+
 // bf16 <-> binary32.  A bf16 value is the high half of a binary32.
 __device__ __forceinline__ float bf16_lo(uint32_t packed) {
     return __uint_as_float(packed << 16);

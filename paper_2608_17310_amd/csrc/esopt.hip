@@ -28,14 +28,17 @@
 //     tiles; the loads of its next tile are issued before the current tile's
 //     arithmetic (software pipelining), and each tile's stores leave in one
 //     burst after all its arithmetic.  The update is VALU-bound (N noise
-//     streams per element): eight workgroups per CU keep every wave slot
-//     busy, one 8-element group per lane at a time with the next group's
-//     load in flight.  Both shapes were chosen by sweeping on MI355X.  Swap
-//     is the perturb kernel with two streams and a bf16 rounding between
-//     them.
+//     streams per element): 256-lane workgroups take items of a tile, two
+//     8-element groups per lane and step, so that four Philox blocks run in
+//     lockstep (es_noise.hpp) and six or seven waves per SIMD pair their
+//     issue.  4B-shaped set, N = 32: 50.8 -> 43.7 ms; 0.5B, 4 live seeds:
+//     0.83 -> 0.79 ms; a 1M-parameter generation of 4: 185 -> 126 us (its 16
+//     tiles had run on 16 CUs).  Swap is the perturb kernel with two streams
+//     and a bf16 rounding between them.
 //   * The quantized path (int8 codes, es_quant.hpp; fp8 E4M3 codes,
 //     es_fp8.hpp) has a tensor table searched per tile and tiles of 16-code
-//     groups; all its passes are VALU-bound and use the update's shape.
+//     groups; all its passes are VALU-bound: eight 1024-lane
+//     workgroups per CU, a group per lane at a time.
 //   * Perturb/restore read and write each parameter once (4 bytes of HBM
 //     traffic per parameter).  The update regenerates the noise of all
 //     distinct member seeds for the same 8 elements in registers,
@@ -83,6 +86,8 @@ constexpr int kDefaultThreads = 1024;
 constexpr int kDefaultGroups = 8;
 constexpr int kDefaultPerturbWgPerCu = 1;
 constexpr int kDefaultUpdateWgPerCu = 8;
+constexpr int kStepThreads = 256;           // lanes per workgroup of the step kernels
+constexpr int kStepElems = kStepThreads * 2 * kGroupElems;   // two groups per lane and step
 constexpr int kDefaultQGroups = 4;          // int8 tiles: 1024 x 4 x 16 codes (64 KB)
 constexpr double kSqrt2Ln2Double = 1.1774100225154746910;   // sqrt(2 ln 2)
 
@@ -922,14 +927,6 @@ __device__ __forceinline__ bool is_zero_weight(float w) {
     return (__float_as_uint(w) << 1) == 0u;
 }
 
-// One tile of the fused update: for each of the lane's groups in turn,
-// acc = sum_d w_d eps_d (binary32, members in table order, zero weights
-// skipped), theta <- round(theta + acc), store it.  Rounding is to nearest
-// even, or stochastic (kSR) with the draws of one domain-1 Philox call per
-// group under the rounding key.  The kernel is VALU-bound, so one group's
-// registers are live at a time and the number of resident waves hides memory
-// latency; full tiles also prefetch the next group while the current one is
-// computed, which matters when N is small.
 struct RoundKey {
     uint32_t k0, k1;
 };
@@ -941,28 +938,46 @@ struct RestoreArg {
     float coef_k;
 };
 
-// The restore of one member on a group in registers, theta <- RNE(theta +
-// coef eps), exactly as the perturb kernel computes it (group_axpy on the
-// binary32 values, then RNE).  The member's update term is added by the
-// member loop's own group_axpy from the same words, so the loop keeps one
-// accumulation path (two paths merging into the accumulators cost register
-// moves on every member); the Box-Muller transcendentals of this one member
-// are evaluated twice.
-__device__ __forceinline__ void restore_group(const uint32_t w[8], float coef_k, uint32_t raw[4]) {
-    float x[8];
+// How a launch of kStepThreads-lane workgroups cuts a plan's tiles: a tile of
+// tile_elems elements is 2^full_shift items of full_steps steps of kStepElems
+// elements, a tail tile 2^tail_shift items of tail_steps.
+struct StepShape {
+    uint32_t full_steps, full_shift;
+    uint32_t tail_steps, tail_shift;
+};
+
+// x[8 g + k] += scale * eps of the two groups of a step from their four
+// blocks' radius factors and trigonometric values (pair p feeds elements 2 p
+// and 2 p + 1); scale_k = scale * sqrt(2 ln 2).
+__device__ __forceinline__ void step_axpy(const float rad[8], const float c[8], const float sn[8],
+                                          float scale_k, float x[16]) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        x[2 * k] = es::bf16_lo(raw[k]);
-        x[2 * k + 1] = es::bf16_hi(raw[k]);
+    for (int p = 0; p < 8; ++p) {
+        const float t = scale_k * rad[p];
+        x[2 * p] = __builtin_fmaf(t, c[p], x[2 * p]);
+        x[2 * p + 1] = __builtin_fmaf(t, sn[p], x[2 * p + 1]);
     }
-    group_axpy(w, coef_k, x);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) raw[k] = es::pack_bf16x2(x[2 * k], x[2 * k + 1]);
 }
 
-// kRestore: one member (rst) is reverted first, in registers, and the update
-// is added to the reverted values; with no live weight (add == false) the
-// reverted values are stored as they are, as es_update would then leave them.
+// The first quads of a step's blocks: two per 8-element group, at whole-tensor
+// indices n[g] (multiples of 8, so the second does not carry).
+__device__ __forceinline__ void step_quads(const uint64_t n[2], uint32_t q[4]) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        q[2 * g] = static_cast<uint32_t>(n[g] >> 2);
+        q[2 * g + 1] = q[2 * g] + 1u;
+    }
+}
+
+// One step of the fused update: a lane's two 8-element groups at elements e
+// and e + 8 kStepThreads.  acc = sum_d w_d eps_d (binary32, members in table
+// order, zero weights skipped), theta <- round(theta + acc), store it.
+// Rounding is to nearest even, or stochastic (kSR) with the draws of one
+// domain-1 Philox call per group under the rounding key.
+// kRestore: one member (rst) is reverted first, in registers, exactly as the
+// perturb kernel does it (RNE(theta + coef eps)), and the update is added to
+// the reverted values; with no live weight (add == false) the reverted values
+// are stored as they are, as es_update would then leave them.
 // kMaster == 1 (ES_UPDATE_MASTER): the update is added to the binary32
 // masters at mb + 4 e instead (one rounding to binary32), and the bf16 values
 // are rewritten as the masters rounded to nearest-even -- also with no live
@@ -970,110 +985,128 @@ __device__ __forceinline__ void restore_group(const uint32_t w[8], float coef_k,
 // kMaster == 2 (es_perturb_master): the members' terms are added to the
 // masters in registers, m + sum w eps with one rounding for one member (the
 // accumulation starts from m), and only the bf16 values are written.
-template <int kThreads, int kU, bool kFast, bool kNT, bool kSR, bool kRows, bool kRestore,
-          int kMaster>
-__device__ __forceinline__ void update_tile(const TileRef& r, const Member* __restrict__ members,
+//
+// VALU-bound (about 12.7 issue slots per normal, es_noise.hpp): four Philox
+// blocks in lockstep, and the step's input is loaded before the member loop
+// and first used after it (or by the reverted member), so its latency lies
+// under the loop.
+template <bool kFast, bool kNT, bool kSR, bool kRows, bool kRestore, int kMaster>
+__device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
+                                            const Member* __restrict__ members,
                                             uint32_t n_distinct, RoundKey rk, RestoreArg rst,
                                             bool add, uintptr_t mb) {
     constexpr int kIn = kMaster != 0 ? 8 : 4;            // words of a group's input
     const uint32_t q_hi = tile_high_word<kRows>(r);
     const uint32_t g_hi = q_hi >> 1;                     // index >> 35
-    const uint64_t e0 = r.elem0 + uint64_t(threadIdx.x) * kGroupElems;
-    uint32_t next[kIn];
-    auto load_in = [&](auto fast, uint64_t e, uint32_t in[kIn]) {
-        constexpr bool kF = decltype(fast)::value;
-        if constexpr (kMaster != 0) {
-            float m[8];
-            load_master<kF, kNT>(mb, e, r.limit, m, r.aligned16 != 0u);
+    const bool vec = r.aligned16 != 0u;
+    uint64_t eg[2], n[2];
+    bool in[2];
+    uint32_t raw[2][kIn];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) in[k] = __builtin_bit_cast(uint32_t, m[k]);
-        } else {
-            load_group<kF, kNT>(r.data, e, r.limit, in, r.aligned16 != 0u);
-        }
-    };
-    if constexpr (kFast) load_in(std::true_type{}, e0, next);
-#pragma unroll 1
-    for (int u = 0; u < kU; ++u) {
-        const uint64_t e = e0 + uint64_t(u) * kThreads * kGroupElems;
-        if (!kFast && e >= r.limit) break;
-        uint32_t raw[kIn];
-        if constexpr (kFast) {
+    for (int g = 0; g < 2; ++g) {
+        eg[g] = e + uint64_t(g) * (kStepThreads * kGroupElems);
+        in[g] = kFast || eg[g] < r.limit;
+        n[g] = noise_index<kRows>(r, eg[g]);
+        if (in[g]) {
+            if constexpr (kMaster != 0) {
+                float m[8];
+                load_master<kFast, kNT>(mb, eg[g], r.limit, m, vec);
 #pragma unroll
-            for (int k = 0; k < kIn; ++k) raw[k] = next[k];
-            if (u + 1 < kU) load_in(std::true_type{}, e + uint64_t(kThreads) * kGroupElems, next);
-        } else {
-            load_in(std::false_type{}, e, raw);
-        }
-        const uint64_t n = noise_index<kRows>(r, e);
-        const uint32_t q_lo = static_cast<uint32_t>(n >> 2);
-        float acc[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            acc[k] = kMaster == 2 ? __builtin_bit_cast(float, raw[k]) : 0.0f;
-        for (uint32_t d = 0; d < n_distinct; ++d) {
-            const Member m = members[d];
-            const bool live = !is_zero_weight(m.w_k);
-            if constexpr (kRestore) {
-                if (!live && d != rst.d) continue;
+                for (int k = 0; k < 8; ++k) raw[g][k] = __builtin_bit_cast(uint32_t, m[k]);
             } else {
-                if (!live) continue;
+                load_group<kFast, kNT>(r.data, eg[g], r.limit, raw[g], vec);
             }
-            uint32_t w[8];
-            group_words(q_lo, q_hi, r.tensor_id, m.k0, m.k1, w);
-            if constexpr (kRestore) {
-                if (d == rst.d) restore_group(w, rst.coef_k, raw);
-                if (!live) continue;
-            }
-            group_axpy(w, m.w_k, acc);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) raw[g][k] = 0u;
         }
+    }
+    uint32_t q[4];
+    step_quads(n, q);
+    float acc[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+        acc[k] = kMaster == 2 ? __builtin_bit_cast(float, raw[k / 8][k % 8]) : 0.0f;
+    for (uint32_t d = 0; d < n_distinct; ++d) {
+        const Member m = members[d];
+        const bool live = !is_zero_weight(m.w_k);
+        if constexpr (kRestore) {
+            if (!live && d != rst.d) continue;
+        } else {
+            if (!live) continue;
+        }
+        es::Words w[4];
+        float rad[8], c[8], sn[8];
+        es::philox_quads<4>(q, q_hi, r.tensor_id, m.k0, m.k1, w);
+        es::box_muller_quads<4>(w, rad, c, sn);
+        if constexpr (kRestore) {
+            if (d == rst.d) {
+                float x[16];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    x[2 * k] = es::bf16_lo(raw[k / 4][k % 4]);
+                    x[2 * k + 1] = es::bf16_hi(raw[k / 4][k % 4]);
+                }
+                step_axpy(rad, c, sn, rst.coef_k, x);
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    raw[k / 4][k % 4] = es::pack_bf16x2(x[2 * k], x[2 * k + 1]);
+            }
+            if (!live) continue;
+        }
+        step_axpy(rad, c, sn, m.w_k, acc);
+    }
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        if (!in[g]) break;
+        const float* a = acc + 8 * g;
         uint32_t out[4];
         if constexpr (kMaster == 2) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) out[k] = es::pack_bf16x2(acc[2 * k], acc[2 * k + 1]);
+            for (int k = 0; k < 4; ++k) out[k] = es::pack_bf16x2(a[2 * k], a[2 * k + 1]);
         } else if constexpr (kMaster == 1) {
             float m[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) m[k] = __builtin_bit_cast(float, raw[k]);
+            for (int k = 0; k < 8; ++k) m[k] = __builtin_bit_cast(float, raw[g][k]);
             if (add) {
 #pragma unroll
-                for (int k = 0; k < 8; ++k) m[k] += acc[k];
-                store_master<kFast, kNT>(mb, e, r.limit, m, r.aligned16 != 0u);
+                for (int k = 0; k < 8; ++k) m[k] += a[k];
+                store_master<kFast, kNT>(mb, eg[g], r.limit, m, vec);
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) out[k] = es::pack_bf16x2(m[2 * k], m[2 * k + 1]);
         } else if (kRestore && !add) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) out[k] = raw[k];
+            for (int k = 0; k < 4; ++k) out[k] = raw[g][k];
         } else if constexpr (kSR) {
-            const es::Words d = es::philox4x32_10(static_cast<uint32_t>(n >> 3), g_hi, r.tensor_id,
-                                                  es::kDomainRounding, rk.k0, rk.k1);
+            const es::Words d =
+                es::philox4x32_10(static_cast<uint32_t>(n[g] >> 3), g_hi, r.tensor_id,
+                                  es::kDomainRounding, rk.k0, rk.k1);
             const uint32_t draws[4] = {d.w0, d.w1, d.w2, d.w3};
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                out[k] = es::pack_bf16x2_sr(es::bf16_lo(raw[k]) + acc[2 * k],
-                                            es::bf16_hi(raw[k]) + acc[2 * k + 1], draws[k]);
+                out[k] = es::pack_bf16x2_sr(es::bf16_lo(raw[g][k]) + a[2 * k],
+                                            es::bf16_hi(raw[g][k]) + a[2 * k + 1], draws[k]);
         } else {
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                out[k] = es::pack_bf16x2(es::bf16_lo(raw[k]) + acc[2 * k],
-                                         es::bf16_hi(raw[k]) + acc[2 * k + 1]);
+                out[k] = es::pack_bf16x2(es::bf16_lo(raw[g][k]) + a[2 * k],
+                                         es::bf16_hi(raw[g][k]) + a[2 * k + 1]);
         }
-        store_group<kFast, kNT>(r.data, e, r.limit, out, r.aligned16 != 0u);
+        store_group<kFast, kNT>(r.data, eg[g], r.limit, out, vec);
     }
 }
 
 // Fused update over the whole parameter list (member table and header
-// written by es_prepare_kernel): full tiles, then tail tiles; with kRows the
-// tiles of strided blocks, through their row maps; with kRestore the member
-// rst reverted in the same pass.
-template <int kThreads, int kU, bool kNT, bool kSR, bool kRows, bool kRestore, int kMaster>
-__global__ __launch_bounds__(kThreads) void es_update_kernel(const DevTile* __restrict__ tiles,
-                                                             uint64_t n_full, uint64_t n_tail,
-                                                             const DevRows* __restrict__ rows,
-                                                             const Member* __restrict__ members,
-                                                             const UpdateHeader* __restrict__ hdr,
-                                                             RoundKey rk, RestoreArg rst,
-                                                             const uint64_t* __restrict__ mdelta) {
+// written by es_prepare_kernel): the items of the full tiles, then those of
+// the tail tiles; with kRows the tiles of strided blocks, through their row
+// maps; with kRestore the member rst reverted in the same pass.
+template <bool kNT, bool kSR, bool kRows, bool kRestore, int kMaster>
+__global__ __launch_bounds__(kStepThreads) void es_update_kernel(
+    const DevTile* __restrict__ tiles, uint64_t n_full, uint64_t n_tail,
+    const DevRows* __restrict__ rows, const Member* __restrict__ members,
+    const UpdateHeader* __restrict__ hdr, RoundKey rk, RestoreArg rst,
+    const uint64_t* __restrict__ mdelta, StepShape sh) {
     const bool add = hdr->n_live != 0u;
     if (!kRestore && kMaster == 0 && !add) return;   // nothing to add: theta is not written
     const uint32_t n_distinct = hdr->n_distinct;
@@ -1082,15 +1115,33 @@ __global__ __launch_bounds__(kThreads) void es_update_kernel(const DevTile* __re
         if constexpr (kMaster != 0) return mdelta[i] + 2 * reinterpret_cast<uintptr_t>(r.data);
         else return 0;
     };
-    for (uint64_t tile = blockIdx.x; tile < n_full; tile += gridDim.x) {
+    const uint64_t full_items = n_full << sh.full_shift;
+    const uint64_t items = full_items + (n_tail << sh.tail_shift);
+    for (uint64_t i = blockIdx.x; i < items; i += gridDim.x) {
+        const bool full = i < full_items;
+        const uint64_t j = full ? i : i - full_items;
+        const uint32_t shift = full ? sh.full_shift : sh.tail_shift;
+        const uint32_t steps = full ? sh.full_steps : sh.tail_steps;
+        const uint64_t tile = (full ? 0 : n_full) + (j >> shift);
+        const uint32_t part = static_cast<uint32_t>(j) & ((1u << shift) - 1u);
         const TileRef r = load_ref<kRows>(tiles, rows, tile);
-        update_tile<kThreads, kU, true, kNT, kSR, kRows, kRestore, kMaster>(
-            r, members, n_distinct, rk, rst, add, mbase(r, tile));
-    }
-    for (uint64_t tile = blockIdx.x; tile < n_tail; tile += gridDim.x) {
-        const TileRef r = load_ref<kRows>(tiles, rows, n_full + tile);
-        update_tile<kThreads, kU, false, kNT, kSR, kRows, kRestore, kMaster>(
-            r, members, n_distinct, rk, rst, add, mbase(r, n_full + tile));
+        const uintptr_t mb = mbase(r, tile);
+        const uint64_t e0 = r.elem0 + uint64_t(part) * steps * kStepElems;
+#pragma unroll 1
+        for (uint32_t k = 0; k < steps; ++k) {
+            const uint64_t base = e0 + uint64_t(k) * kStepElems;
+            const uint64_t e = base + threadIdx.x * kGroupElems;
+            if (full) {
+                update_step<true, kNT, kSR, kRows, kRestore, kMaster>(r, e, members, n_distinct,
+                                                                      rk, rst, add, mb);
+            } else {
+                if (base >= r.limit) break;
+                if (e < r.limit)
+                    update_step<false, kNT, kSR, kRows, kRestore, kMaster>(r, e, members,
+                                                                           n_distinct, rk, rst,
+                                                                           add, mb);
+            }
+        }
     }
 }
 
@@ -1244,7 +1295,8 @@ __global__ __launch_bounds__(kAuxBlock) void es_normals_kernel(uint32_t k0, uint
 
 using PerturbKernel = void (*)(const DevTile*, uint64_t, uint64_t, const DevRows*, Streams);
 using UpdateKernel = void (*)(const DevTile*, uint64_t, uint64_t, const DevRows*, const Member*,
-                              const UpdateHeader*, RoundKey, RestoreArg, const uint64_t*);
+                              const UpdateHeader*, RoundKey, RestoreArg, const uint64_t*,
+                              StepShape);
 
 // Tile shapes instantiated: T lanes per workgroup x U groups per lane.
 #define ES_TILE_SHAPES(X) X(256, 4) X(256, 8) X(512, 4) X(512, 8) X(1024, 4) X(1024, 8)
@@ -1293,31 +1345,12 @@ PerturbKernel perturb_kernel(int streams, int threads, int groups, bool rows) {
 }
 
 template <bool kRestore>
-UpdateKernel update_kernel_for(int threads, int groups, bool stochastic, bool rows) {
-#define ES_CASE(T, U)                                                                        \
-    if (threads == T && groups == U) {                                                       \
-        if (rows)                                                                            \
-            return stochastic ? es_update_kernel<T, U, true, true, true, kRestore, 0>    \
-                              : es_update_kernel<T, U, true, false, true, kRestore, 0>;  \
-        return stochastic ? es_update_kernel<T, U, true, true, false, kRestore, 0>       \
-                          : es_update_kernel<T, U, true, false, false, kRestore, 0>;     \
-    }
-    ES_TILE_SHAPES(ES_CASE)
-#undef ES_CASE
-    return nullptr;
-}
-
-// The update into binary32 masters (mode 1) and the application of members
-// from the masters (mode 2), both rewriting the bf16 values.
-template <int kMode>
-UpdateKernel master_kernel_for(int threads, int groups, bool rows) {
-#define ES_CASE(T, U)                                                                   \
-    if (threads == T && groups == U)                                                    \
-        return rows ? es_update_kernel<T, U, true, false, true, false, kMode>           \
-                    : es_update_kernel<T, U, true, false, false, false, kMode>;
-    ES_TILE_SHAPES(ES_CASE)
-#undef ES_CASE
-    return nullptr;
+UpdateKernel update_kernel_for(bool stochastic, bool rows) {
+    if (rows)
+        return stochastic ? es_update_kernel<true, true, true, kRestore, 0>
+                          : es_update_kernel<true, false, true, kRestore, 0>;
+    return stochastic ? es_update_kernel<true, true, false, kRestore, 0>
+                      : es_update_kernel<true, false, false, kRestore, 0>;
 }
 
 using ApplyMasterKernel = void (*)(const DevTile*, uint64_t, uint64_t, const DevRows*, Streams,
@@ -1332,16 +1365,20 @@ ApplyMasterKernel apply_master_kernel(int threads, int groups, bool rows) {
     return nullptr;
 }
 
-UpdateKernel update_master_kernel(int threads, int groups, bool rows, bool apply = false) {
-    return apply ? master_kernel_for<2>(threads, groups, rows)
-                 : master_kernel_for<1>(threads, groups, rows);
+// The update into binary32 masters (mode 1) and the application of members
+// from the masters (mode 2), both rewriting the bf16 values.
+UpdateKernel update_master_kernel(bool rows, bool apply = false) {
+    if (apply)
+        return rows ? es_update_kernel<true, false, true, false, 2>
+                    : es_update_kernel<true, false, false, false, 2>;
+    return rows ? es_update_kernel<true, false, true, false, 1>
+                : es_update_kernel<true, false, false, false, 1>;
 }
 
 // restore: the update with one member reverted in the same pass.
-UpdateKernel update_kernel(int threads, int groups, bool stochastic, bool rows,
-                           bool restore = false) {
-    return restore ? update_kernel_for<true>(threads, groups, stochastic, rows)
-                   : update_kernel_for<false>(threads, groups, stochastic, rows);
+UpdateKernel update_kernel(bool stochastic, bool rows, bool restore) {
+    return restore ? update_kernel_for<true>(stochastic, rows)
+                   : update_kernel_for<false>(stochastic, rows);
 }
 
 // ---- quantized path: int8 and E4M3 codes (helpers in es_quant.hpp, es_fp8.hpp) ----
@@ -1640,9 +1677,13 @@ struct es_plan {
     uint64_t n_rfull = 0;           // full and tail tiles of strided blocks, after the
     uint64_t n_rtail = 0;           //   others, each with a row map
     uint32_t grid_perturb = 0;      // workgroups of the perturb / restore launch
-    uint32_t grid_update = 0;       // workgroups of the update launch
+    uint32_t grid_update = 0;       // workgroups of the checksum launch
+    StepShape steps;                // items of the update launch, and its workgroups
+    uint32_t grid_steps = 0;
     uint32_t grid_perturb_rows = 0; // the same for the strided blocks' launch
     uint32_t grid_update_rows = 0;
+    StepShape steps_rows;
+    uint32_t grid_steps_rows = 0;
     int threads = kDefaultThreads;  // lanes per workgroup of the tile kernels
     int groups = kDefaultGroups;    // 8-element groups per lane per tile
     uint64_t tile_elems = 0;        // threads * groups * 8
@@ -1701,16 +1742,19 @@ struct Segment {
     uint64_t n_full, n_tail;
     const DevRows* rows;            // null for the first part
     uint32_t grid_perturb, grid_update;
+    StepShape steps;
+    uint32_t grid_steps;
 };
 
 int plan_segments(const es_plan_t* p, Segment seg[2]) {
     int n = 0;
     if (p->n_full + p->n_tail > 0)
         seg[n++] = Segment{p->d_tiles, p->n_full, p->n_tail, nullptr, p->grid_perturb,
-                           p->grid_update};
+                           p->grid_update, p->steps, p->grid_steps};
     if (p->n_rfull + p->n_rtail > 0)
         seg[n++] = Segment{p->d_tiles + p->n_full + p->n_tail, p->n_rfull, p->n_rtail, p->d_rows,
-                           p->grid_perturb_rows, p->grid_update_rows};
+                           p->grid_perturb_rows, p->grid_update_rows, p->steps_rows,
+                           p->grid_steps_rows};
     return n;
 }
 
@@ -1887,7 +1931,7 @@ void row_divisor(uint32_t r, uint32_t& magic, uint32_t& shift) {
 void launch_shape(int& threads, int& groups) {
     threads = env_int("ESOPT_THREADS", kDefaultThreads, 256, 1024);
     groups = env_int("ESOPT_GROUPS", kDefaultGroups, 2, 8);
-    if (update_kernel(threads, groups, false, false) == nullptr) {
+    if (perturb_kernel(1, threads, groups, false) == nullptr) {
         threads = kDefaultThreads;
         groups = kDefaultGroups;
     }
@@ -2132,16 +2176,16 @@ int update_impl(const char* name, es_plan_t* plan, uint8_t* d_scratch, const uin
         const Segment& g = seg[k];
         const bool strided = g.rows != nullptr;
         const UpdateKernel kernel =
-            master ? update_master_kernel(plan->threads, plan->groups, strided)
-                   : update_kernel(plan->threads, plan->groups, sr, strided, restore != nullptr);
+            master ? update_master_kernel(strided)
+                   : update_kernel(sr, strided, restore != nullptr);
         // the segment's masters: the delta table runs parallel to the tiles
         const uint64_t* mdelta =
             master ? plan->d_master + (strided ? plan->n_full + plan->n_tail : 0) : nullptr;
-        hipLaunchKernelGGL(kernel, dim3(g.grid_update), dim3(plan->threads), 0, s, g.tiles,
+        hipLaunchKernelGGL(kernel, dim3(g.grid_steps), dim3(kStepThreads), 0, s, g.tiles,
                            g.n_full, g.n_tail, g.rows,
                            reinterpret_cast<const Member*>(d_scratch + kOffMembers),
                            reinterpret_cast<const UpdateHeader*>(d_scratch + kOffHeader), rk,
-                           rst, mdelta);
+                           rst, mdelta, g.steps);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, std::string(name) + ": es_update_kernel launch");
     }
@@ -2260,6 +2304,36 @@ void tile_block(const es_block_t& b, uint64_t tile_elems, PlanTiles& t) {
     }
 }
 
+// Items of a step launch over n_full full tiles and n_tail tail tiles of at
+// most tail_max elements (tile_elems a power of two, at least kStepElems), and
+// its grid.  Large plans take up to four steps per item (the tile's descriptor
+// is read once per item); a plan too small to give every wave slot (eight
+// 256-lane workgroups per CU) eight items takes fewer, down to one step, so
+// that a few tiles still spread over the chip.  A tail tile is cut for the
+// longest one, or left whole where there are so many of them (thousands of
+// tiny tensors) that they fill the chip as they are: the empty items of short
+// tiles would only cost their look-up.
+StepShape step_shape(uint64_t n_full, uint64_t n_tail, uint64_t tail_max, uint64_t tile_elems,
+                     int cus, int wg_per_cu, uint32_t& grid) {
+    const uint64_t slots = uint64_t(cus) * 8;
+    const uint32_t tile_steps = static_cast<uint32_t>(tile_elems / kStepElems);
+    StepShape sh{};
+    sh.full_steps = std::min(4u, tile_steps);
+    while (sh.full_steps > 1 && (n_full + n_tail) * (tile_steps / sh.full_steps) < 8 * slots)
+        sh.full_steps /= 2;
+    while ((sh.full_steps << sh.full_shift) < tile_steps) ++sh.full_shift;
+    const uint64_t most = (tail_max + kStepElems - 1) / kStepElems;     // steps of the longest
+    while ((uint64_t(sh.full_steps) << sh.tail_shift) < most &&
+           (n_tail << sh.tail_shift) < 32 * slots)
+        ++sh.tail_shift;
+    const uint64_t parts = uint64_t(1) << sh.tail_shift;
+    sh.tail_steps = static_cast<uint32_t>(std::max<uint64_t>((most + parts - 1) / parts, 1));
+    const uint64_t items = (n_full << sh.full_shift) + (n_tail << sh.tail_shift);
+    grid = static_cast<uint32_t>(
+        std::min<uint64_t>(std::max<uint64_t>(items, 1), uint64_t(cus) * 4 * wg_per_cu));
+    return sh;
+}
+
 // A plan over tiles laid out by the caller (es_plan_create,
 // es_plan_create_blocks): launch grids, one device allocation for the
 // descriptors and row maps, the scratch.
@@ -2303,6 +2377,15 @@ int finish_plan(const char* name, int device, uint32_t n_tensors, uint64_t numel
     p->grid_update = grid(n_full, n_tail, wg_update);
     p->grid_perturb_rows = grid(n_rfull, n_rtail, wg_perturb);
     p->grid_update_rows = grid(n_rfull, n_rtail, wg_update);
+    auto longest = [](const std::vector<DevTile>& v) {
+        uint64_t m = 0;
+        for (const DevTile& d : v) m = std::max(m, d.limit - d.elem0);
+        return m;
+    };
+    p->steps = step_shape(n_full, n_tail, longest(t.tail), p->tile_elems, cus, wg_update,
+                          p->grid_steps);
+    p->steps_rows = step_shape(n_rfull, n_rtail, longest(t.rtail), p->tile_elems, cus, wg_update,
+                               p->grid_steps_rows);
     const size_t tile_bytes = sizeof(DevTile) * std::max<size_t>(tiles.size(), 1);
     const size_t rows_bytes = sizeof(DevRows) * rows.size();
     e = hipMalloc(reinterpret_cast<void**>(&p->d_tiles), tile_bytes + rows_bytes);
@@ -2726,13 +2809,13 @@ int es_perturb_master(es_plan_t* plan, uint64_t seed, int32_t sign, float sigma,
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
         const bool strided = g.rows != nullptr;
-        hipLaunchKernelGGL(update_master_kernel(plan->threads, plan->groups, strided, true),
-                           dim3(g.grid_update), dim3(plan->threads), 0, s, g.tiles, g.n_full,
-                           g.n_tail, g.rows,
+        hipLaunchKernelGGL(update_master_kernel(strided, true), dim3(g.grid_steps),
+                           dim3(kStepThreads), 0, s, g.tiles, g.n_full, g.n_tail, g.rows,
                            reinterpret_cast<const Member*>(plan->d_scratch + kOffMembers),
                            reinterpret_cast<const UpdateHeader*>(plan->d_scratch + kOffHeader),
                            RoundKey{0u, 0u}, RestoreArg{0u, 0.0f},
-                           plan->d_master + (strided ? plan->n_full + plan->n_tail : 0));
+                           plan->d_master + (strided ? plan->n_full + plan->n_tail : 0),
+                           g.steps);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "es_perturb_master: es_update_kernel launch");
     }
