@@ -84,7 +84,7 @@ extern "C" {
 typedef void* es_stream_t;          /* hipStream_t */
 
 /* One parameter tensor: `numel` contiguous bf16 values at device address
- * `data` (2-byte aligned; 16-byte alignment takes the vector path).
+ * `data` (2-byte aligned; 16-byte alignment streams fastest).
  * `tensor_id` is the tensor's noise identity (counter word 2) and must be
  * unique within a plan and stable across calls; the list index is the usual
  * choice.  numel may be 0 (the tensor is skipped).
@@ -522,16 +522,15 @@ double es_sigma_cosine(double sigma0, double sigma_T, uint32_t t, uint32_t T);
 
 /* Calibration pass: reads every parameter of the plan and writes it back
  * unchanged, bit for bit, with the tiles, 16-byte nontemporal accesses and
- * launch shape of es_perturb but no arithmetic and no software pipelining
- * (each workgroup loads a whole tile, then stores it) -- the fastest
- * in-place stream over the plan's memory, so its duration is the practical
- * ceiling against which es_perturb's bandwidth is measured. */
+ * launch shape of es_perturb but no arithmetic (each workgroup loads its
+ * step, then stores it) -- the fastest in-place stream over the plan's
+ * memory, so its duration is the practical ceiling against which
+ * es_perturb's bandwidth is measured. */
 int es_stream_pass(es_plan_t* plan, es_stream_t stream);
 
 /* HBM calibration over a caller's flat device buffer of `bytes` bytes (a
- * positive multiple of 131072, 16-byte aligned), with the tile shape and
- * launch of es_perturb: 1024 lanes x 8 16-byte words per tile, one workgroup
- * per compute unit, nontemporal accesses (the passes' policy; with
+ * positive multiple of 131072, 16-byte aligned): tiles of 1024 lanes x 8
+ * 16-byte words, one workgroup per compute unit, nontemporal accesses (the passes' policy; with
  * ES_CALIBRATE_TEMPORAL or-ed into `mode`, ordinary loads and stores), each
  * tile loaded whole, then stored.  mode 0 reads every word (their XOR is folded into *sink_dev, a
  * device uint32, with one atomic per wave, so the reads are not dead code);

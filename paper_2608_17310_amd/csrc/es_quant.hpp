@@ -122,13 +122,19 @@ typedef uint32_t q32x4_t __attribute__((ext_vector_type(4)));
 #define ESQ_GLOBAL __attribute__((address_space(1)))
 
 // 16 codes of one group in 4 words (byte i of word k is code 4k + i).  The
-// checked path (tail tiles) uses the 16-byte access too when the tensor is
-// 16-byte aligned and the whole group is inside it.
+// checked path (tail tiles) takes the 16-byte access too for every group that
+// lies wholly inside the tensor, at any byte alignment (global memory accesses
+// need none on this part; the type says so to the compiler).
+typedef uint32_t q32x4_any_t __attribute__((ext_vector_type(4), aligned(1)));
+
 template <bool kFast>
 __device__ __forceinline__ void qload(const int8_t* __restrict__ p, uint32_t e, uint32_t numel,
-                                      uint32_t raw[4], bool vec = false) {
-    if (kFast || (vec && e + 16 <= numel)) {
+                                      uint32_t raw[4]) {
+    if (kFast) {
         const q32x4_t v = __builtin_nontemporal_load((const ESQ_GLOBAL q32x4_t*)(p + e));
+        raw[0] = v.x; raw[1] = v.y; raw[2] = v.z; raw[3] = v.w;
+    } else if (e + 16 <= numel) {
+        const q32x4_t v = __builtin_nontemporal_load((const ESQ_GLOBAL q32x4_any_t*)(p + e));
         raw[0] = v.x; raw[1] = v.y; raw[2] = v.z; raw[3] = v.w;
     } else {
         const ESQ_GLOBAL uint8_t* g = (const ESQ_GLOBAL uint8_t*)p;
@@ -147,10 +153,12 @@ __device__ __forceinline__ void qload(const int8_t* __restrict__ p, uint32_t e, 
 
 template <bool kFast>
 __device__ __forceinline__ void qstore(int8_t* __restrict__ p, uint32_t e, uint32_t numel,
-                                       const uint32_t out[4], bool vec = false) {
-    if (kFast || (vec && e + 16 <= numel)) {
-        const q32x4_t v = {out[0], out[1], out[2], out[3]};
+                                       const uint32_t out[4]) {
+    const q32x4_t v = {out[0], out[1], out[2], out[3]};
+    if (kFast) {
         __builtin_nontemporal_store(v, (ESQ_GLOBAL q32x4_t*)(p + e));
+    } else if (e + 16 <= numel) {
+        __builtin_nontemporal_store(v, (ESQ_GLOBAL q32x4_any_t*)(p + e));
     } else {
         ESQ_GLOBAL uint8_t* g = (ESQ_GLOBAL uint8_t*)p;
 #pragma unroll

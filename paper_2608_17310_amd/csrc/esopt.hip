@@ -14,27 +14,25 @@
 //     65536 elements, 128 KB): full tiles on tile-sized boundaries of the
 //     address space, then tail tiles (each tensor's head and remainder, or
 //     every tile of an unaligned tensor), each described by a 32-byte
-//     descriptor.  One launch covers the whole parameter list: a grid of
-//     (CUs x WGs-per-CU) workgroups strides over the full tiles, then the
-//     tails, reading one descriptor per tile with a scalar load, so a tile's
-//     tensor, address and noise identity are wave-uniform.
-//   * Within a tile, lane l of group slot u owns elements
-//     elem0 + 8 (u * T + l) .. +7: one 16-byte load and one 16-byte store, 64
+//     descriptor.  One launch covers the whole parameter list, the full tiles
+//     and then the tails, reading one descriptor per workgroup with a scalar
+//     load, so a tile's tensor, address and noise identity are wave-uniform.
+//   * Within a step of 256 x G groups, lane l of group slot g owns elements
+//     e0 + 8 (256 g + l) .. +7: one 16-byte load and one 16-byte store, 64
 //     lanes covering 1 KB contiguous per instruction.  Its two Philox calls
-//     are the quads 2 g and 2 g + 1 of that group (tiles start at multiples
+//     are the quads 2 n and 2 n + 1 of that group (tiles start at multiples
 //     of 8 elements); no tile crosses a multiple of 2^34 elements, so the
 //     counter's high word is uniform per tile.
-//   * Perturb is HBM-bound: one 1024-lane workgroup per CU streams 128 KB
-//     tiles; the loads of its next tile are issued before the current tile's
-//     arithmetic (software pipelining), and each tile's stores leave in one
-//     burst after all its arithmetic.  The update is VALU-bound (N noise
-//     streams per element): 256-lane workgroups take items of a tile, two
-//     8-element groups per lane and step, so that four Philox blocks run in
-//     lockstep (es_noise.hpp) and six or seven waves per SIMD pair their
-//     issue.  4B-shaped set, N = 32: 50.8 -> 43.7 ms; 0.5B, 4 live seeds:
-//     0.83 -> 0.79 ms; a 1M-parameter generation of 4: 185 -> 126 us (its 16
-//     tiles had run on 16 CUs).  Swap is the perturb kernel with two streams
-//     and a bf16 rounding between them.
+//   * The passes run in 256-lane workgroups of one step each (StepShape): two
+//     or four 8-element groups per lane, loaded in one burst and stored in
+//     one, dispatched in the order of the plan's memory.  Perturb is
+//     HBM-bound: 0.5B-shaped set, perturb and restore, 677 -> 603 us (5.70 ->
+//     6.41 TB/s), against one 1024-lane workgroup per CU that strode over the
+//     tiles with its next tile's loads in flight.  The update is VALU-bound
+//     (N noise streams per element): two groups per lane, so that four Philox
+//     blocks run in lockstep (es_noise.hpp) and six or seven waves per SIMD
+//     pair their issue.  4B-shaped set, N = 32: 50.8 -> 43.7 ms.  Swap is the
+//     perturb kernel with two streams and a bf16 rounding between them.
 //   * The quantized path (int8 codes, es_quant.hpp; fp8 E4M3 codes,
 //     es_fp8.hpp) has a tensor table searched per tile and tiles of 16-code
 //     groups; all its passes are VALU-bound: eight 1024-lane
@@ -45,8 +43,8 @@
 //     accumulates sum_d w_d eps_d in binary32, and then does the single
 //     read-modify-write, so its HBM traffic does not depend on N.
 //   * Tail tiles take a bounds-checked path with identical arithmetic:
-//     16-byte accesses for whole groups of an aligned tensor, 2-byte accesses
-//     for a partial group or an unaligned tensor.
+//     16-byte accesses for whole groups (at any address), 2-byte accesses for
+//     a partial one.
 //   * Blocks of row-major tensors that are not one contiguous range (column
 //     shards) are tiled by address like tensors; their tiles carry a row map
 //     from the element's place in the block to its whole-tensor index, the
@@ -84,10 +82,8 @@ constexpr int kGroupElems = 8;              // bf16 per lane-group (one 16-byte 
 // perturb is HBM-bound and wants large contiguous per-CU streams.
 constexpr int kDefaultThreads = 1024;
 constexpr int kDefaultGroups = 8;
-constexpr int kDefaultPerturbWgPerCu = 1;
 constexpr int kDefaultUpdateWgPerCu = 8;
 constexpr int kStepThreads = 256;           // lanes per workgroup of the step kernels
-constexpr int kStepElems = kStepThreads * 2 * kGroupElems;   // two groups per lane and step
 constexpr int kDefaultQGroups = 4;          // int8 tiles: 1024 x 4 x 16 codes (64 KB)
 constexpr double kSqrt2Ln2Double = 1.1774100225154746910;   // sqrt(2 ln 2)
 
@@ -109,7 +105,7 @@ struct DevTile {
     uint64_t elem0;                         // the tile's first element in its tensor
     uint64_t limit;                         // one past the last element a tail tile may touch
     uint32_t tensor_id;
-    uint32_t aligned16;                     // base 16-byte aligned: whole groups 16-byte accesses
+    uint32_t aligned16;                     // base 16-byte aligned
 };
 static_assert(sizeof(DevTile) == 32, "tile descriptor layout");
 
@@ -205,16 +201,25 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 // global_store (vector-memory counters only) instead of flat accesses.
 #define ES_GLOBAL __attribute__((address_space(1)))
 
-// Load the 8 bf16 of one group (packed in 4 words).  Fast path: one 16-byte
-// load (nontemporal when kNT: the parameters are streamed once per pass).
-// Checked path (tail tiles): the 16-byte load when the tensor is 16-byte
-// aligned and the whole group lies below the bound `limit`, element-wise
-// 2-byte loads below the bound otherwise.
+// Load the 8 bf16 of one group (packed in 4 words): one 16-byte load
+// (nontemporal when kNT: the parameters are streamed once per pass).  The
+// checked path (tail tiles) takes it for every group that lies wholly below
+// the bound `limit`, and 2-byte loads below the bound for a partial group.  A
+// tensor whose base is only 2-byte aligned takes the same 16-byte accesses at
+// its own addresses (global memory accesses need no alignment on this part;
+// the type says so to the compiler): a wave then touches nine 128-byte lines
+// for its eight.
+typedef uint32_t u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
+
 template <bool kFast, bool kNT>
 __device__ __forceinline__ void load_group(const uint16_t* __restrict__ p, uint64_t e,
-                                           uint64_t limit, uint32_t raw[4], bool vec = false) {
-    if (kFast || (vec && e + 8 <= limit)) {
+                                           uint64_t limit, uint32_t raw[4]) {
+    if (kFast) {
         const ES_GLOBAL u32x4_t* a = (const ES_GLOBAL u32x4_t*)(p + e);
+        const u32x4_t v = kNT ? __builtin_nontemporal_load(a) : *a;
+        raw[0] = v.x; raw[1] = v.y; raw[2] = v.z; raw[3] = v.w;
+    } else if (e + 8 <= limit) {
+        const ES_GLOBAL u32x4_any_t* a = (const ES_GLOBAL u32x4_any_t*)(p + e);
         const u32x4_t v = kNT ? __builtin_nontemporal_load(a) : *a;
         raw[0] = v.x; raw[1] = v.y; raw[2] = v.z; raw[3] = v.w;
     } else {
@@ -230,10 +235,14 @@ __device__ __forceinline__ void load_group(const uint16_t* __restrict__ p, uint6
 
 template <bool kFast, bool kNT>
 __device__ __forceinline__ void store_group(uint16_t* __restrict__ p, uint64_t e, uint64_t limit,
-                                            const uint32_t out[4], bool vec = false) {
-    if (kFast || (vec && e + 8 <= limit)) {
+                                            const uint32_t out[4]) {
+    const u32x4_t v = {out[0], out[1], out[2], out[3]};
+    if (kFast) {
         ES_GLOBAL u32x4_t* a = (ES_GLOBAL u32x4_t*)(p + e);
-        const u32x4_t v = {out[0], out[1], out[2], out[3]};
+        if constexpr (kNT) __builtin_nontemporal_store(v, a);
+        else *a = v;
+    } else if (e + 8 <= limit) {
+        ES_GLOBAL u32x4_any_t* a = (ES_GLOBAL u32x4_any_t*)(p + e);
         if constexpr (kNT) __builtin_nontemporal_store(v, a);
         else *a = v;
     } else {
@@ -248,15 +257,14 @@ __device__ __forceinline__ void store_group(uint16_t* __restrict__ p, uint64_t e
 
 // The binary32 master copies of a group's 8 elements (es_plan_set_master):
 // element e's master sits at mb + 4 e, mb being the tile's master base.  A
-// group that takes the 16-byte bf16 path has a 16-byte aligned master group
-// (the masters are 16-byte aligned and laid out as their bf16 tensors), so it
-// takes two 16-byte accesses; element-wise accesses below the bound otherwise.
+// tensor's masters are 16-byte aligned and its groups start at multiples of 8
+// elements of it, so a whole group takes two 16-byte accesses whatever the
+// bf16 base; element-wise accesses below the bound otherwise.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 template <bool kFast, bool kNT>
-__device__ __forceinline__ void load_master(uintptr_t mb, uint64_t e, uint64_t limit, float m[8],
-                                            bool vec = false) {
-    if (kFast || (vec && e + 8 <= limit)) {
+__device__ __forceinline__ void load_master(uintptr_t mb, uint64_t e, uint64_t limit, float m[8]) {
+    if (kFast || e + 8 <= limit) {
         const ES_GLOBAL f32x4_t* a = (const ES_GLOBAL f32x4_t*)(mb + 4 * e);
         const f32x4_t v0 = kNT ? __builtin_nontemporal_load(a) : a[0];
         const f32x4_t v1 = kNT ? __builtin_nontemporal_load(a + 1) : a[1];
@@ -271,8 +279,8 @@ __device__ __forceinline__ void load_master(uintptr_t mb, uint64_t e, uint64_t l
 
 template <bool kFast, bool kNT>
 __device__ __forceinline__ void store_master(uintptr_t mb, uint64_t e, uint64_t limit,
-                                             const float m[8], bool vec = false) {
-    if (kFast || (vec && e + 8 <= limit)) {
+                                             const float m[8]) {
+    if (kFast || e + 8 <= limit) {
         ES_GLOBAL f32x4_t* a = (ES_GLOBAL f32x4_t*)(mb + 4 * e);
         const f32x4_t v0 = {m[0], m[1], m[2], m[3]};
         const f32x4_t v1 = {m[4], m[5], m[6], m[7]};
@@ -291,29 +299,6 @@ __device__ __forceinline__ void store_master(uintptr_t mb, uint64_t e, uint64_t 
     }
 }
 
-// The Philox words of the 8 elements of the group starting at element 8 g:
-// quads 2 g and 2 g + 1 (q_lo is even, so q_lo + 1 does not carry into q_hi).
-__device__ __forceinline__ void group_words(uint32_t q_lo, uint32_t q_hi, uint32_t tensor_id,
-                                            uint32_t k0, uint32_t k1, uint32_t w[8]) {
-    const es::Words a = es::philox4x32_10(q_lo, q_hi, tensor_id, es::kDomainNoise, k0, k1);
-    const es::Words b = es::philox4x32_10(q_lo + 1u, q_hi, tensor_id, es::kDomainNoise, k0, k1);
-    w[0] = a.w0; w[1] = a.w1; w[2] = a.w2; w[3] = a.w3;
-    w[4] = b.w0; w[5] = b.w1; w[6] = b.w2; w[7] = b.w3;
-}
-
-// x[k] += scale * eps_k for the 8 elements of a group, in binary32: each
-// Box-Muller pair (words 2p, 2p+1) feeds elements 2p (cos) and 2p+1 (sin);
-// scale_k = scale * sqrt(2 ln 2).
-__device__ __forceinline__ void group_axpy(const uint32_t w[8], float scale_k, float x[8]) {
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        float t, c, sn;
-        es::scaled_pair(w[2 * p], w[2 * p + 1], scale_k, t, c, sn);
-        x[2 * p] = __builtin_fmaf(t, c, x[2 * p]);
-        x[2 * p + 1] = __builtin_fmaf(t, sn, x[2 * p + 1]);
-    }
-}
-
 // Noise streams applied by one perturb-style pass.  kM = 1: one stream,
 // theta <- RNE(theta + c_0 eps_0) (perturb / restore).  kM = 2: two streams
 // applied in turn with a bf16 rounding in between,
@@ -326,57 +311,65 @@ struct Streams {
     float coef_k[2];
 };
 
-__device__ __forceinline__ void round_to_bf16(float x[8]) {
+// x[8 g + k] += scale * eps of two groups from their four blocks' radius
+// factors and trigonometric values (pair p feeds elements 2 p and 2 p + 1);
+// scale_k = scale * sqrt(2 ln 2).
+__device__ __forceinline__ void pair_axpy(const float rad[8], const float c[8], const float sn[8],
+                                          float scale_k, float x[16]) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint32_t b = es::pack_bf16x2(x[2 * k], x[2 * k + 1]);
-        x[2 * k] = es::bf16_lo(b);
-        x[2 * k + 1] = es::bf16_hi(b);
+    for (int p = 0; p < 8; ++p) {
+        const float t = scale_k * rad[p];
+        x[2 * p] = __builtin_fmaf(t, c[p], x[2 * p]);
+        x[2 * p + 1] = __builtin_fmaf(t, sn[p], x[2 * p + 1]);
     }
 }
 
-// Apply the streams to one 8-element group in registers and pack to bf16.
-// Each stream adds one FMA per element to the binary32 value.
-template <int kM>
-__device__ __forceinline__ void perturb_group(const uint32_t raw[4], uint64_t e, uint32_t q_hi,
-                                              uint32_t tensor_id, const Streams& st,
-                                              uint32_t out[4]) {
-    float x[8];
+// The quads of two groups whose first elements have whole-tensor indices n[g]
+// (multiples of 8, so a group's second quad does not carry).
+__device__ __forceinline__ void pair_quads(const uint64_t n[2], uint32_t q[4]) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        x[2 * k] = es::bf16_lo(raw[k]);
-        x[2 * k + 1] = es::bf16_hi(raw[k]);
+    for (int g = 0; g < 2; ++g) {
+        q[2 * g] = static_cast<uint32_t>(n[g] >> 2);
+        q[2 * g + 1] = q[2 * g] + 1u;
+    }
+}
+
+__device__ __forceinline__ void unpack_pair(const uint32_t raw[2][4], float x[16]) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        x[2 * k] = es::bf16_lo(raw[k / 4][k % 4]);
+        x[2 * k + 1] = es::bf16_hi(raw[k / 4][k % 4]);
+    }
+}
+__device__ __forceinline__ void pack_pair(const float x[16], uint32_t raw[2][4]) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) raw[k / 4][k % 4] = es::pack_bf16x2(x[2 * k], x[2 * k + 1]);
+}
+
+// Apply the streams to two 8-element groups in registers (raw, in place):
+// each stream adds one FMA per element to the binary32 value, rounded to bf16
+// after each stream.  Four Philox blocks in lockstep (es_noise.hpp).
+template <int kM>
+__device__ __forceinline__ void perturb_pair(uint32_t raw[2][4], const uint64_t n[2],
+                                             uint32_t q_hi, uint32_t tensor_id,
+                                             const Streams& st) {
+    uint32_t q[4];
+    pair_quads(n, q);
+    es::Words w[4];
+    float rad[8], c[8], sn[8], x[16];
+#pragma unroll
+    for (int m = 0; m < (kM == 2 ? 2 : 1); ++m) {
+        es::philox_quads<4>(q, q_hi, tensor_id, st.k0[m], st.k1[m], w);
+        es::box_muller_quads<4>(w, rad, c, sn);
+        unpack_pair(raw, x);
+        pair_axpy(rad, c, sn, st.coef_k[m], x);
+        pack_pair(x, raw);
     }
     if constexpr (kM == 3) {
-        uint32_t w[8];
-        group_words(static_cast<uint32_t>(e >> 2), q_hi, tensor_id, st.k0[0], st.k1[0], w);
-        float r[4], c[4], sn[4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            r[p] = es::pair_radius(w[2 * p]);
-            es::pair_angle(w[2 * p + 1], c[p], sn[p]);
-        }
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            if (m == 1) round_to_bf16(x);
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const float t = st.coef_k[m] * r[p];
-                x[2 * p] = __builtin_fmaf(t, c[p], x[2 * p]);
-                x[2 * p + 1] = __builtin_fmaf(t, sn[p], x[2 * p + 1]);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int m = 0; m < kM; ++m) {
-            if (m > 0) round_to_bf16(x);
-            uint32_t w[8];
-            group_words(static_cast<uint32_t>(e >> 2), q_hi, tensor_id, st.k0[m], st.k1[m], w);
-            group_axpy(w, st.coef_k[m], x);
-        }
+        unpack_pair(raw, x);
+        pair_axpy(rad, c, sn, st.coef_k[1], x);
+        pack_pair(x, raw);
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) out[k] = es::pack_bf16x2(x[2 * k], x[2 * k + 1]);
 }
 
 // A tile: up to kThreads * kU * 8 consecutive elements of one tensor, from
@@ -426,210 +419,90 @@ __device__ __forceinline__ uint32_t tile_high_word(const TileRef& r) {
     else return static_cast<uint32_t>(r.elem0 >> 34);
 }
 
-// Keep a prefetched descriptor in scalar registers: without this the
-// compiler may drop it and load it again where it is used, exposing the
-// load's latency there.  Placed after the work that hides the load, so the
-// wait it implies costs nothing.
-__device__ __forceinline__ void keep_in_sgprs(DevTile& d) {
-    asm volatile("" : "+s"(d.data), "+s"(d.elem0), "+s"(d.tensor_id));
-}
-__device__ __forceinline__ void keep_in_sgprs(DevRows& m) {
-    asm volatile("" : "+s"(m.n0), "+s"(m.skip), "+s"(m.magic), "+s"(m.shift), "+s"(m.hi));
-}
+// How a launch of kStepThreads-lane workgroups covers a plan's tiles, one step
+// (kG 8-element groups per lane, 256 x 8 kG elements) per workgroup: a full
+// tile is 2^full_shift steps, a tail tile 2^tail_shift workgroups of
+// tail_steps steps each (one, except where there are very many tail tiles).
+// Workgroups are dispatched in order, so those in flight work on one
+// contiguous stretch of the plan's memory, and a step's loads leave in one
+// burst and its stores in another.  In place over the 0.5B-shaped set (perturb
+// and restore, kG = 4): 6.41 TB/s with one step per workgroup, 6.22 with two,
+// 5.66 with four; 5.67 with two steps over a grid that strides (the order is
+// lost), 5.70 with one 1024-lane workgroup per CU striding over 128 KB tiles
+// with its next tile's loads in flight.
+struct StepShape {
+    uint32_t full_shift;
+    uint32_t tail_shift, tail_steps;
+};
 
-template <int kThreads, int kU>
-__device__ __forceinline__ void load_tile(const TileRef& r, uint32_t raw[kU][4]) {
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-        const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
-        load_group<true, true>(r.data, e, r.limit, raw[u]);
+// The step (or steps) of this workgroup: step(full, tile reference, tile
+// number, the lane's first element); its group g starts 8 kStepThreads g
+// elements on.  For a tail tile the first group starts below the bound (lanes
+// beyond it are left out) and the others may not.
+template <bool kRows, int kG, class Step>
+__device__ __forceinline__ void for_steps(const DevTile* __restrict__ tiles, uint64_t n_full,
+                                          const DevRows* __restrict__ rows, const StepShape& sh,
+                                          Step step) {
+    constexpr uint32_t kElems = kStepThreads * kG * kGroupElems;
+    const uint64_t full_items = n_full << sh.full_shift;
+    const uint64_t i = blockIdx.x;
+    if (i < full_items) {
+        const uint64_t tile = i >> sh.full_shift;
+        const uint32_t part = static_cast<uint32_t>(i) & ((1u << sh.full_shift) - 1u);
+        const TileRef r = load_ref<kRows>(tiles, rows, tile);
+        step(std::true_type{}, r, tile,
+             r.elem0 + part * kElems + threadIdx.x * uint32_t(kGroupElems));
+        return;
     }
-}
-
-// Perturb a full tile whose groups are already in registers: every group is
-// computed first and the tile's stores then leave in one burst.  On MI355X
-// an in-place stream whose writes come in per-tile bursts sustains ~6.2 TB/s,
-// against ~5.5 TB/s when each group's store is interleaved with the next
-// group's arithmetic.
-template <int kThreads, int kU, int kM, bool kRows>
-__device__ __forceinline__ void perturb_loaded(const TileRef& r, uint32_t raw[kU][4],
-                                               const Streams& st) {
-    const uint32_t q_hi = tile_high_word<kRows>(r);
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-        const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
-        uint32_t out[4];
-        perturb_group<kM>(raw[u], noise_index<kRows>(r, e), q_hi, r.tensor_id, st, out);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) raw[u][k] = out[k];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-        const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
-        store_group<true, true>(r.data, e, r.limit, raw[u]);
-    }
-}
-
-// Perturb a tail tile group by group, with bounds-checked accesses (16-byte
-// for whole groups of an aligned tensor, 2-byte otherwise).
-template <int kThreads, int kU, int kM, bool kRows>
-__device__ __forceinline__ void perturb_tail(const TileRef& r, const Streams& st) {
-    const uint32_t q_hi = tile_high_word<kRows>(r);
+    const uint64_t j = i - full_items;
+    const uint64_t tile = n_full + (j >> sh.tail_shift);
+    const uint32_t part = static_cast<uint32_t>(j) & ((1u << sh.tail_shift) - 1u);
+    const TileRef r = load_ref<kRows>(tiles, rows, tile);
 #pragma unroll 1
-    for (int u = 0; u < kU; ++u) {
-        const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
-        if (e >= r.limit) break;
-        uint32_t raw[4], out[4];
-        load_group<false, true>(r.data, e, r.limit, raw, r.aligned16 != 0u);
-        perturb_group<kM>(raw, noise_index<kRows>(r, e), q_hi, r.tensor_id, st, out);
-        store_group<false, true>(r.data, e, r.limit, out, r.aligned16 != 0u);
+    for (uint32_t k = 0; k < sh.tail_steps; ++k) {
+        const uint64_t e = r.elem0 + uint64_t(part * sh.tail_steps + k) * kElems +
+                           threadIdx.x * uint32_t(kGroupElems);
+        if (e >= r.limit) return;
+        step(std::false_type{}, r, tile, e);
     }
 }
 
-// One software-pipeline step over full tiles: issue the 16-byte loads of the
-// workgroup's next tile (`nxt`) into `next_buf`, read the descriptor of the
-// tile after it, then perturb the current tile from `cur_buf`, so the memory
-// pipe does not idle through the Philox / Box-Muller arithmetic and the
-// descriptor's scalar load completes under it.  Returns true when the
-// workgroup has no next tile.
-//
-// The loads are issued on every step, the last one reloading its own tile
-// into the idle buffer (128 KB per workgroup per pass, never used), and the
-// descriptor index is clamped rather than tested: the compiler's wait before
-// the current tile's arithmetic is path-insensitive, and a path without loads
-// after the current tile's made it wait for the next tile's loads as well.
-template <int kThreads, int kU, int kM, bool kRows>
-__device__ __forceinline__ bool perturb_step(const DevTile* __restrict__ tiles,
-                                             const DevRows* __restrict__ rows, uint64_t& tile,
-                                             uint64_t n_full, TileRef& cur, TileRef& nxt,
-                                             uint32_t cur_buf[kU][4], uint32_t next_buf[kU][4],
-                                             const Streams& st) {
-    const uint64_t next = tile + gridDim.x;
-    const bool more = next < n_full;
-    __builtin_amdgcn_sched_barrier(0);
-    load_tile<kThreads, kU>(more ? nxt : cur, next_buf);
-    __builtin_amdgcn_sched_barrier(0);
-    const uint64_t after_i = min(next + gridDim.x, n_full - 1);
-    DevTile after = tiles[after_i];
-    DevRows after_rows{};
-    if constexpr (kRows) after_rows = rows[after_i];
-    __builtin_amdgcn_sched_barrier(0);
-    perturb_loaded<kThreads, kU, kM, kRows>(cur, cur_buf, st);
-    keep_in_sgprs(after);
-    if constexpr (kRows) keep_in_sgprs(after_rows);
-    if (!more) return true;
-    tile = next;
-    cur = nxt;
-    if constexpr (kRows) nxt = tile_ref(after, after_rows);
-    else nxt = tile_ref(after);
-    return false;
-}
-
-// One pass over the whole parameter list applying kM noise streams: full
-// tiles first (16-byte nontemporal accesses, software-pipelined: two register
-// buffers alternate, the loop unrolled twice), then tail tiles.  The first
-// step is peeled off so that every step inside the loop starts with the same
-// memory operations outstanding (the previous tile's stores, then the next
-// tile's loads): the wait for the current tile then leaves both in flight.
-//
-// kRows: the launch over the tiles of strided blocks, each with its row map
-// in `rows` (same index as its descriptor); otherwise `rows` is unused.
-template <int kThreads, int kU, int kM, bool kRows>
-__global__ __launch_bounds__(kThreads) void es_perturb_kernel(const DevTile* __restrict__ tiles,
-                                                              uint64_t n_full, uint64_t n_tail,
-                                                              const DevRows* __restrict__ rows,
-                                                              Streams st) {
-    uint64_t tile = blockIdx.x;
-    if (tile < n_full) {
-        TileRef cur = load_ref<kRows>(tiles, rows, tile);
-        TileRef nxt = load_ref<kRows>(tiles, rows, min(tile + gridDim.x, n_full - 1));
-        uint32_t a[kU][4], b[kU][4];
-        load_tile<kThreads, kU>(cur, a);
-        if (!perturb_step<kThreads, kU, kM, kRows>(tiles, rows, tile, n_full, cur, nxt, a, b,
-                                                   st)) {
-            for (;;) {
-                if (perturb_step<kThreads, kU, kM, kRows>(tiles, rows, tile, n_full, cur, nxt, b,
-                                                          a, st))
-                    break;
-                if (perturb_step<kThreads, kU, kM, kRows>(tiles, rows, tile, n_full, cur, nxt, a,
-                                                          b, st))
-                    break;
-            }
+// One pass over the whole parameter list applying kM noise streams: each lane
+// loads its kG groups, generates their noise (two groups at a time, which the
+// loads' latency lies under), and stores them in one burst.  HBM-bound with
+// one stream, VALU-bound with two.  kRows: the launch over the tiles of strided
+// blocks, each with its row map in `rows` (same index as its descriptor);
+// otherwise `rows` is unused.
+template <int kM, bool kRows, int kG>
+__global__ __launch_bounds__(kStepThreads) void es_perturb_kernel(const DevTile* __restrict__ tiles,
+                                                                  uint64_t n_full,
+                                                                  const DevRows* __restrict__ rows,
+                                                                  Streams st, StepShape sh) {
+    constexpr uint64_t kSlab = uint64_t(kStepThreads) * kGroupElems;
+    for_steps<kRows, kG>(tiles, n_full, rows, sh,
+                         [&](auto full, const TileRef& r, uint64_t, uint64_t e) {
+        constexpr bool kFast = decltype(full)::value;
+        uint32_t raw[kG][4];
+#pragma unroll
+        for (int g = 0; g < kG; ++g) {
+            if (kFast || e + g * kSlab < r.limit)
+                load_group<kFast, true>(r.data, e + g * kSlab, r.limit, raw[g]);
+            else
+                raw[g][0] = raw[g][1] = raw[g][2] = raw[g][3] = 0u;
         }
-    }
-    for (uint64_t tl = blockIdx.x; tl < n_tail; tl += gridDim.x)
-        perturb_tail<kThreads, kU, kM, kRows>(load_ref<kRows>(tiles, rows, n_full + tl), st);
-}
-
-// A member applied from binary32 masters (es_perturb_master) with sigma > 0:
-// bf16 values RNE(m + c eps) from the masters at mb + 4 e, the masters only
-// read -- the arithmetic of es_perturb on the masters' values.  The perturb
-// kernel's pipeline at half a tile per step: a half tile's masters (kU / 2
-// slabs of 32 bytes per lane) take the registers a whole tile of bf16 takes
-// there, so two half-tile buffers alternate, the next half's loads issued
-// before the current half's arithmetic and each half's bf16 stores leaving
-// in one burst.
-//
-// Within a slab (kThreads * 8 consecutive elements) lane t takes the quads
-// at elements 4 t and 4 (kThreads + t): each 16-byte master load then covers
-// 1 KB of consecutive masters per wave (one lane's 8 consecutive masters
-// would take two loads of 16 bytes at a 32-byte stride, and streamed lines
-// were fetched twice), and each 8-byte bf16 store 512 consecutive bytes.
-// A quad is one Philox block: its two Box-Muller pairs are its elements.
-template <int kThreads>
-__device__ __forceinline__ uint64_t slab_quad(const TileRef& r, int slab, int q) {
-    return r.elem0 + uint64_t(slab * kThreads) * kGroupElems +
-           4 * (uint64_t(q) * kThreads + threadIdx.x);
-}
-
-template <int kThreads, int kH>
-__device__ __forceinline__ void master_half_load(const TileRef& r, uintptr_t mb, int h,
-                                                 float m[kH][8]) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < kH; ++u)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const uint64_t e = slab_quad<kThreads>(r, h * kH + u, q);
-            const f32x4_t v = __builtin_nontemporal_load((const ES_GLOBAL f32x4_t*)(mb + 4 * e));
-            m[u][4 * q] = v.x; m[u][4 * q + 1] = v.y; m[u][4 * q + 2] = v.z; m[u][4 * q + 3] = v.w;
+        for (int g = 0; g < kG; g += 2) {
+            const uint64_t n[2] = {noise_index<kRows>(r, e + g * kSlab),
+                                   noise_index<kRows>(r, e + (g + 1) * kSlab)};
+            perturb_pair<kM>(raw + g, n, tile_high_word<kRows>(r), r.tensor_id, st);
+            __builtin_amdgcn_sched_barrier(0);
         }
-}
-
-template <int kThreads, int kH, bool kRows>
-__device__ __forceinline__ void master_half_apply(const TileRef& r, int h, float m[kH][8],
-                                                  const Streams& st) {
-    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-    const uint32_t q_hi = tile_high_word<kRows>(r);
-    uint32_t out[kH][4];
 #pragma unroll
-    for (int u = 0; u < kH; ++u)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const uint64_t e = slab_quad<kThreads>(r, h * kH + u, q);
-            const es::Words w = es::philox4x32_10(
-                static_cast<uint32_t>(noise_index<kRows>(r, e) >> 2), q_hi, r.tensor_id,
-                es::kDomainNoise, st.k0[0], st.k1[0]);
-            float* x = &m[u][4 * q];
-            float t, c, sn;
-            es::scaled_pair(w.w0, w.w1, st.coef_k[0], t, c, sn);
-            x[0] = __builtin_fmaf(t, c, x[0]);
-            x[1] = __builtin_fmaf(t, sn, x[1]);
-            es::scaled_pair(w.w2, w.w3, st.coef_k[0], t, c, sn);
-            x[2] = __builtin_fmaf(t, c, x[2]);
-            x[3] = __builtin_fmaf(t, sn, x[3]);
-            out[u][2 * q] = es::pack_bf16x2(x[0], x[1]);
-            out[u][2 * q + 1] = es::pack_bf16x2(x[2], x[3]);
-        }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < kH; ++u)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const uint64_t e = slab_quad<kThreads>(r, h * kH + u, q);
-            const u32x2_t v = {out[u][2 * q], out[u][2 * q + 1]};
-            __builtin_nontemporal_store(v, (ES_GLOBAL u32x2_t*)(r.data + e));
-        }
+        for (int g = 0; g < kG; ++g)
+            if (kFast || e + g * kSlab < r.limit)
+                store_group<kFast, true>(r.data, e + g * kSlab, r.limit, raw[g]);
+    });
 }
 
 // A tile's master base: its bf16 base times two plus the tensor's delta.
@@ -638,127 +511,114 @@ __device__ __forceinline__ uintptr_t master_base(const uint64_t* __restrict__ md
     return mdelta[i] + 2 * reinterpret_cast<uintptr_t>(r.data);
 }
 
-// Full tiles: buffer a holds a tile's first half, b its second.  Each turn
-// of the loop finishes the current tile's second half while the next tile's
-// first half loads, then loads that tile's second half under its first
-// half's arithmetic; the last tile's second half is done after the loop.
-// Every path into the loop's head then has the same memory operations
-// outstanding (the second half's loads, then the first half's stores), so
-// its first wait leaves the stores in flight; the next tile's descriptor is
-// read a turn ahead, as in the perturb kernel.  Tail tiles follow, group by
-// group with bounds-checked accesses.
-template <int kThreads, int kU, bool kRows>
-__global__ __launch_bounds__(kThreads) void es_apply_master_kernel(
-    const DevTile* __restrict__ tiles, uint64_t n_full, uint64_t n_tail,
-    const DevRows* __restrict__ rows, Streams st, const uint64_t* __restrict__ mdelta) {
-    static_assert(kU % 2 == 0, "a tile is taken in two halves");
-    constexpr int kH = kU / 2;
-    uint64_t tile = blockIdx.x;
-    if (tile < n_full) {
-        TileRef cur = load_ref<kRows>(tiles, rows, tile);
-        uintptr_t cur_mb = master_base(mdelta, cur, tile);
-        const uint64_t nxt_i = min(tile + gridDim.x, n_full - 1);
-        TileRef nxt = load_ref<kRows>(tiles, rows, nxt_i);
-        uintptr_t nxt_mb = master_base(mdelta, nxt, nxt_i);
-        float a[kH][8], b[kH][8];
-        master_half_load<kThreads, kH>(cur, cur_mb, 0, a);
-        master_half_load<kThreads, kH>(cur, cur_mb, 1, b);
-        __builtin_amdgcn_sched_barrier(0);
-        master_half_apply<kThreads, kH, kRows>(cur, 0, a, st);
-        while (tile + gridDim.x < n_full) {
-            tile += gridDim.x;
-            __builtin_amdgcn_sched_barrier(0);
-            master_half_load<kThreads, kH>(nxt, nxt_mb, 0, a);
-            __builtin_amdgcn_sched_barrier(0);
-            const uint64_t after_i = min(tile + gridDim.x, n_full - 1);
-            DevTile after = tiles[after_i];
-            DevRows after_rows{};
-            if constexpr (kRows) after_rows = rows[after_i];
-            uint64_t after_d = mdelta[after_i];
-            __builtin_amdgcn_sched_barrier(0);
-            master_half_apply<kThreads, kH, kRows>(cur, 1, b, st);
-            keep_in_sgprs(after);
-            if constexpr (kRows) keep_in_sgprs(after_rows);
-            asm volatile("" : "+s"(after_d));
-            cur = nxt;
-            cur_mb = nxt_mb;
-            if constexpr (kRows) nxt = tile_ref(after, after_rows);
-            else nxt = tile_ref(after);
-            nxt_mb = after_d + 2 * reinterpret_cast<uintptr_t>(nxt.data);
-            __builtin_amdgcn_sched_barrier(0);
-            master_half_load<kThreads, kH>(cur, cur_mb, 1, b);
-            __builtin_amdgcn_sched_barrier(0);
-            master_half_apply<kThreads, kH, kRows>(cur, 0, a, st);
-        }
-        master_half_apply<kThreads, kH, kRows>(cur, 1, b, st);
-    }
-    for (uint64_t tl = blockIdx.x; tl < n_tail; tl += gridDim.x) {
-        const TileRef r = load_ref<kRows>(tiles, rows, n_full + tl);
-        const uintptr_t mb = master_base(mdelta, r, n_full + tl);
+// A member applied from binary32 masters (es_perturb_master) with sigma > 0:
+// bf16 values RNE(m + c eps) from the masters at mb + 4 e, the masters only
+// read -- the arithmetic of es_perturb on the masters' values.  HBM-bound, 6
+// bytes per parameter.  In a full tile a lane takes the quads at elements 4 t
+// and 4 (256 + t) of each slab of 2048: a 16-byte master load then covers 1 KB
+// of consecutive masters per wave (one lane's 8 consecutive masters would take
+// two loads of 16 bytes at a 32-byte stride, and streamed lines were fetched
+// twice), and an 8-byte bf16 store 512 consecutive bytes.  A quad is one Philox
+// block: its two Box-Muller pairs are its elements.  Tail tiles take the groups
+// of the other passes with bounds-checked accesses.
+template <bool kRows, int kG>
+__global__ __launch_bounds__(kStepThreads) void es_apply_master_kernel(
+    const DevTile* __restrict__ tiles, uint64_t n_full, const DevRows* __restrict__ rows,
+    Streams st, const uint64_t* __restrict__ mdelta, StepShape sh) {
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    constexpr uint64_t kSlab = uint64_t(kStepThreads) * kGroupElems;
+    for_steps<kRows, kG>(tiles, n_full, rows, sh,
+                         [&](auto full, const TileRef& r, uint64_t tile, uint64_t e) {
+        constexpr bool kFast = decltype(full)::value;
+        const uintptr_t mb = master_base(mdelta, r, tile);
         const uint32_t q_hi = tile_high_word<kRows>(r);
-#pragma unroll 1
-        for (int u = 0; u < kU; ++u) {
-            const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
-            if (e >= r.limit) break;
-            float m[8];
-            load_master<false, true>(mb, e, r.limit, m, r.aligned16 != 0u);
-            uint32_t w[8], out[4];
-            group_words(static_cast<uint32_t>(noise_index<kRows>(r, e) >> 2), q_hi, r.tensor_id,
-                        st.k0[0], st.k1[0], w);
-            group_axpy(w, st.coef_k[0], m);
+        float m[kG][8];
+        if constexpr (kFast) {
+            const uint64_t e4 = e - threadIdx.x * 4u;        // the lane's first quad
 #pragma unroll
-            for (int k = 0; k < 4; ++k) out[k] = es::pack_bf16x2(m[2 * k], m[2 * k + 1]);
-            store_group<false, true>(r.data, e, r.limit, out, r.aligned16 != 0u);
+            for (int i = 0; i < 2 * kG; ++i) {
+                const f32x4_t v = __builtin_nontemporal_load(
+                    (const ES_GLOBAL f32x4_t*)(mb + 4 * (e4 + i * (kSlab / 2))));
+                float* x = m[i / 2] + 4 * (i % 2);
+                x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int g = 0; g < kG; ++g) {
+                if (e + g * kSlab < r.limit)
+                    load_master<false, true>(mb, e + g * kSlab, r.limit, m[g]);
+                else
+                    for (int k = 0; k < 8; ++k) m[g][k] = 0.0f;
+            }
         }
-    }
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t out[kG][4];
+#pragma unroll
+        for (int g = 0; g < kG; g += 2) {
+            uint32_t q[4];
+            if constexpr (kFast) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    q[i] = static_cast<uint32_t>(
+                        noise_index<kRows>(r, e - threadIdx.x * 4u + (2 * g + i) * (kSlab / 2)) >>
+                        2);
+            } else {
+                const uint64_t n[2] = {noise_index<kRows>(r, e + g * kSlab),
+                                       noise_index<kRows>(r, e + (g + 1) * kSlab)};
+                pair_quads(n, q);
+            }
+            es::Words w[4];
+            float rad[8], c[8], sn[8];
+            es::philox_quads<4>(q, q_hi, r.tensor_id, st.k0[0], st.k1[0], w);
+            es::box_muller_quads<4>(w, rad, c, sn);
+            pair_axpy(rad, c, sn, st.coef_k[0], &m[g][0]);
+            pack_pair(&m[g][0], out + g);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (kFast) {
+            const uint64_t e4 = e - threadIdx.x * 4u;
+#pragma unroll
+            for (int i = 0; i < 2 * kG; ++i) {
+                const u32x2_t v = {out[i / 2][2 * (i % 2)], out[i / 2][2 * (i % 2) + 1]};
+                __builtin_nontemporal_store(v,
+                                            (ES_GLOBAL u32x2_t*)(r.data + e4 + i * (kSlab / 2)));
+            }
+        } else {
+#pragma unroll
+            for (int g = 0; g < kG; ++g)
+                if (e + g * kSlab < r.limit)
+                    store_group<false, true>(r.data, e + g * kSlab, r.limit, out[g]);
+        }
+    });
 }
 
 // The in-place streaming ceiling of a plan (es_stream_pass): every element
 // is read and written back as itself (XOR with `flip`, which the host passes
-// as 0, so the compiler keeps the stores), over the same tiles and 16-byte
-// nontemporal accesses as the passes above but without arithmetic and
-// without software pipelining -- each workgroup loads a whole tile, then
-// stores it.  On MI355X this is the fastest in-place stream measured (about
-// 3 % above the same stream pipelined), so it bounds what any pass over the
-// plan can reach.
-template <int kThreads, int kU>
-__global__ __launch_bounds__(kThreads) void es_stream_kernel(const DevTile* __restrict__ tiles,
-                                                             uint64_t n_full, uint64_t n_tail,
-                                                             uint32_t flip) {
-    TileRef r{};
-    if (blockIdx.x < n_full) r = tile_ref(tiles[blockIdx.x]);
-    for (uint64_t tile = blockIdx.x; tile < n_full; tile += gridDim.x) {
-        uint32_t raw[kU][4];
-        load_tile<kThreads, kU>(r, raw);
-        // the next tile's descriptor, read under this tile's loads
-        DevTile next = tiles[min(tile + gridDim.x, n_full - 1)];
+// as 0, so the compiler keeps the stores), over the same steps and 16-byte
+// nontemporal accesses as the passes above but without arithmetic, so it
+// bounds what any pass over the plan can reach.
+template <int kG>
+__global__ __launch_bounds__(kStepThreads) void es_stream_kernel(const DevTile* __restrict__ tiles,
+                                                                 uint64_t n_full, uint32_t flip,
+                                                                 StepShape sh) {
+    constexpr uint64_t kSlab = uint64_t(kStepThreads) * kGroupElems;
+    for_steps<false, kG>(tiles, n_full, nullptr, sh,
+                         [&](auto full, const TileRef& r, uint64_t, uint64_t e) {
+        constexpr bool kFast = decltype(full)::value;
+        uint32_t raw[kG][4];
+#pragma unroll
+        for (int g = 0; g < kG; ++g)
+            if (kFast || e + g * kSlab < r.limit)
+                load_group<kFast, true>(r.data, e + g * kSlab, r.limit, raw[g]);
         __builtin_amdgcn_sched_barrier(0);      // all loads issued before the first wait
 #pragma unroll
-        for (int u = 0; u < kU; ++u)
+        for (int g = 0; g < kG; ++g)
+            if (kFast || e + g * kSlab < r.limit) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) raw[u][k] ^= flip;
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
-            store_group<true, true>(r.data, e, r.limit, raw[u]);
-        }
-        keep_in_sgprs(next);
-        r = tile_ref(next);
-    }
-    for (uint64_t tl = blockIdx.x; tl < n_tail; tl += gridDim.x) {
-        const TileRef r = tile_ref(tiles[n_full + tl]);
-#pragma unroll 1
-        for (int u = 0; u < kU; ++u) {
-            const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
-            if (e >= r.limit) break;
-            uint32_t raw[4];
-            load_group<false, true>(r.data, e, r.limit, raw, r.aligned16 != 0u);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) raw[k] ^= flip;
-            store_group<false, true>(r.data, e, r.limit, raw, r.aligned16 != 0u);
-        }
-    }
+                for (int k = 0; k < 4; ++k) raw[g][k] ^= flip;
+                store_group<kFast, true>(r.data, e + g * kSlab, r.limit, raw[g]);
+            }
+    });
 }
 
 // Parameter checksum (es_plan_checksum):
@@ -850,7 +710,7 @@ __global__ __launch_bounds__(kThreads) void es_checksum_kernel(const DevTile* __
             const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
             if (e >= r.limit) break;
             uint32_t raw[4];
-            load_group<false, true>(r.data, e, r.limit, raw, r.aligned16 != 0u);
+            load_group<false, true>(r.data, e, r.limit, raw);
             const uint64_t n = noise_index<kRows>(r, e);
             // the bound moves with the index: n + (limit - e) for a row map
             acc += checksum_terms<kGroupElems, 16, true>(raw, n, kRows ? n + (r.limit - e) : r.limit,
@@ -866,9 +726,8 @@ __global__ __launch_bounds__(64) void es_zero_u64_kernel(unsigned long long* __r
     if (threadIdx.x == 0) *p = 0ull;
 }
 
-// HBM calibration over a caller's flat buffer (es_hbm_calibrate), with the
-// perturb's workgroup and tile shape: kThreads lanes x kU 16-byte words per
-// tile, each tile loaded whole and then stored, with nontemporal accesses
+// HBM calibration over a caller's flat buffer (es_hbm_calibrate): tiles of
+// kThreads lanes x kU 16-byte words, each loaded whole and then stored, with nontemporal accesses
 // (kNT, the passes' policy) or ordinary ones.  kMode 0 reads every word
 // (their XOR leaves in one atomic per wave, so the loads are live), 1 writes
 // every word (the pattern tile, u, lane, 0), 2 reads every word and writes it
@@ -938,37 +797,6 @@ struct RestoreArg {
     float coef_k;
 };
 
-// How a launch of kStepThreads-lane workgroups cuts a plan's tiles: a tile of
-// tile_elems elements is 2^full_shift items of full_steps steps of kStepElems
-// elements, a tail tile 2^tail_shift items of tail_steps.
-struct StepShape {
-    uint32_t full_steps, full_shift;
-    uint32_t tail_steps, tail_shift;
-};
-
-// x[8 g + k] += scale * eps of the two groups of a step from their four
-// blocks' radius factors and trigonometric values (pair p feeds elements 2 p
-// and 2 p + 1); scale_k = scale * sqrt(2 ln 2).
-__device__ __forceinline__ void step_axpy(const float rad[8], const float c[8], const float sn[8],
-                                          float scale_k, float x[16]) {
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-        const float t = scale_k * rad[p];
-        x[2 * p] = __builtin_fmaf(t, c[p], x[2 * p]);
-        x[2 * p + 1] = __builtin_fmaf(t, sn[p], x[2 * p + 1]);
-    }
-}
-
-// The first quads of a step's blocks: two per 8-element group, at whole-tensor
-// indices n[g] (multiples of 8, so the second does not carry).
-__device__ __forceinline__ void step_quads(const uint64_t n[2], uint32_t q[4]) {
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-        q[2 * g] = static_cast<uint32_t>(n[g] >> 2);
-        q[2 * g + 1] = q[2 * g] + 1u;
-    }
-}
-
 // One step of the fused update: a lane's two 8-element groups at elements e
 // and e + 8 kStepThreads.  acc = sum_d w_d eps_d (binary32, members in table
 // order, zero weights skipped), theta <- round(theta + acc), store it.
@@ -998,7 +826,6 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
     constexpr int kIn = kMaster != 0 ? 8 : 4;            // words of a group's input
     const uint32_t q_hi = tile_high_word<kRows>(r);
     const uint32_t g_hi = q_hi >> 1;                     // index >> 35
-    const bool vec = r.aligned16 != 0u;
     uint64_t eg[2], n[2];
     bool in[2];
     uint32_t raw[2][kIn];
@@ -1010,11 +837,11 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
         if (in[g]) {
             if constexpr (kMaster != 0) {
                 float m[8];
-                load_master<kFast, kNT>(mb, eg[g], r.limit, m, vec);
+                load_master<kFast, kNT>(mb, eg[g], r.limit, m);
 #pragma unroll
                 for (int k = 0; k < 8; ++k) raw[g][k] = __builtin_bit_cast(uint32_t, m[k]);
             } else {
-                load_group<kFast, kNT>(r.data, eg[g], r.limit, raw[g], vec);
+                load_group<kFast, kNT>(r.data, eg[g], r.limit, raw[g]);
             }
         } else {
 #pragma unroll
@@ -1022,7 +849,7 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
         }
     }
     uint32_t q[4];
-    step_quads(n, q);
+    pair_quads(n, q);
     float acc[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k)
@@ -1042,19 +869,13 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
         if constexpr (kRestore) {
             if (d == rst.d) {
                 float x[16];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    x[2 * k] = es::bf16_lo(raw[k / 4][k % 4]);
-                    x[2 * k + 1] = es::bf16_hi(raw[k / 4][k % 4]);
-                }
-                step_axpy(rad, c, sn, rst.coef_k, x);
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    raw[k / 4][k % 4] = es::pack_bf16x2(x[2 * k], x[2 * k + 1]);
+                unpack_pair(raw, x);
+                pair_axpy(rad, c, sn, rst.coef_k, x);
+                pack_pair(x, raw);
             }
             if (!live) continue;
         }
-        step_axpy(rad, c, sn, m.w_k, acc);
+        pair_axpy(rad, c, sn, m.w_k, acc);
     }
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
@@ -1071,7 +892,7 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
             if (add) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) m[k] += a[k];
-                store_master<kFast, kNT>(mb, eg[g], r.limit, m, vec);
+                store_master<kFast, kNT>(mb, eg[g], r.limit, m);
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) out[k] = es::pack_bf16x2(m[2 * k], m[2 * k + 1]);
@@ -1093,56 +914,31 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
                 out[k] = es::pack_bf16x2(es::bf16_lo(raw[g][k]) + a[2 * k],
                                          es::bf16_hi(raw[g][k]) + a[2 * k + 1]);
         }
-        store_group<kFast, kNT>(r.data, eg[g], r.limit, out, vec);
+        store_group<kFast, kNT>(r.data, eg[g], r.limit, out);
     }
 }
 
 // Fused update over the whole parameter list (member table and header
-// written by es_prepare_kernel): the items of the full tiles, then those of
+// written by es_prepare_kernel): the steps of the full tiles, then those of
 // the tail tiles; with kRows the tiles of strided blocks, through their row
 // maps; with kRestore the member rst reverted in the same pass.
 template <bool kNT, bool kSR, bool kRows, bool kRestore, int kMaster>
 __global__ __launch_bounds__(kStepThreads) void es_update_kernel(
-    const DevTile* __restrict__ tiles, uint64_t n_full, uint64_t n_tail,
-    const DevRows* __restrict__ rows, const Member* __restrict__ members,
-    const UpdateHeader* __restrict__ hdr, RoundKey rk, RestoreArg rst,
+    const DevTile* __restrict__ tiles, uint64_t n_full, const DevRows* __restrict__ rows,
+    const Member* __restrict__ members, const UpdateHeader* __restrict__ hdr, RoundKey rk, RestoreArg rst,
     const uint64_t* __restrict__ mdelta, StepShape sh) {
     const bool add = hdr->n_live != 0u;
     if (!kRestore && kMaster == 0 && !add) return;   // nothing to add: theta is not written
     const uint32_t n_distinct = hdr->n_distinct;
-    // a tile's master base: its bf16 base times two plus the tensor's delta
     auto mbase = [&](const TileRef& r, uint64_t i) -> uintptr_t {
-        if constexpr (kMaster != 0) return mdelta[i] + 2 * reinterpret_cast<uintptr_t>(r.data);
+        if constexpr (kMaster != 0) return master_base(mdelta, r, i);
         else return 0;
     };
-    const uint64_t full_items = n_full << sh.full_shift;
-    const uint64_t items = full_items + (n_tail << sh.tail_shift);
-    for (uint64_t i = blockIdx.x; i < items; i += gridDim.x) {
-        const bool full = i < full_items;
-        const uint64_t j = full ? i : i - full_items;
-        const uint32_t shift = full ? sh.full_shift : sh.tail_shift;
-        const uint32_t steps = full ? sh.full_steps : sh.tail_steps;
-        const uint64_t tile = (full ? 0 : n_full) + (j >> shift);
-        const uint32_t part = static_cast<uint32_t>(j) & ((1u << shift) - 1u);
-        const TileRef r = load_ref<kRows>(tiles, rows, tile);
-        const uintptr_t mb = mbase(r, tile);
-        const uint64_t e0 = r.elem0 + uint64_t(part) * steps * kStepElems;
-#pragma unroll 1
-        for (uint32_t k = 0; k < steps; ++k) {
-            const uint64_t base = e0 + uint64_t(k) * kStepElems;
-            const uint64_t e = base + threadIdx.x * kGroupElems;
-            if (full) {
-                update_step<true, kNT, kSR, kRows, kRestore, kMaster>(r, e, members, n_distinct,
-                                                                      rk, rst, add, mb);
-            } else {
-                if (base >= r.limit) break;
-                if (e < r.limit)
-                    update_step<false, kNT, kSR, kRows, kRestore, kMaster>(r, e, members,
-                                                                           n_distinct, rk, rst,
-                                                                           add, mb);
-            }
-        }
-    }
+    for_steps<kRows, 2>(tiles, n_full, rows, sh,
+                        [&](auto full, const TileRef& r, uint64_t tile, uint64_t e) {
+        update_step<decltype(full)::value, kNT, kSR, kRows, kRestore, kMaster>(
+            r, e, members, n_distinct, rk, rst, add, mbase(r, tile));
+    });
 }
 
 // The scratch of es_update_noalloc: one update's staged member tables, merged
@@ -1293,30 +1089,31 @@ __global__ __launch_bounds__(kAuxBlock) void es_normals_kernel(uint32_t k0, uint
     }
 }
 
-using PerturbKernel = void (*)(const DevTile*, uint64_t, uint64_t, const DevRows*, Streams);
-using UpdateKernel = void (*)(const DevTile*, uint64_t, uint64_t, const DevRows*, const Member*,
+using PerturbKernel = void (*)(const DevTile*, uint64_t, const DevRows*, Streams, StepShape);
+using UpdateKernel = void (*)(const DevTile*, uint64_t, const DevRows*, const Member*,
                               const UpdateHeader*, RoundKey, RestoreArg, const uint64_t*,
                               StepShape);
+using ApplyMasterKernel = void (*)(const DevTile*, uint64_t, const DevRows*, Streams,
+                                   const uint64_t*, StepShape);
+
+// streams: 1 (perturb / restore), 2 (swap, two keys), 3 (swap, one key);
+// rows: the launch over strided blocks' tiles; kG: groups per lane and step.
+template <int kG>
+PerturbKernel perturb_kernel(int streams, bool rows) {
+    switch (streams) {
+        case 1: return rows ? es_perturb_kernel<1, true, kG> : es_perturb_kernel<1, false, kG>;
+        case 2: return rows ? es_perturb_kernel<2, true, kG> : es_perturb_kernel<2, false, kG>;
+        default: return rows ? es_perturb_kernel<3, true, kG> : es_perturb_kernel<3, false, kG>;
+    }
+}
+
+template <int kG>
+ApplyMasterKernel apply_master_kernel(bool rows) {
+    return rows ? es_apply_master_kernel<true, kG> : es_apply_master_kernel<false, kG>;
+}
 
 // Tile shapes instantiated: T lanes per workgroup x U groups per lane.
 #define ES_TILE_SHAPES(X) X(256, 4) X(256, 8) X(512, 4) X(512, 8) X(1024, 4) X(1024, 8)
-
-template <int kM, bool kRows>
-PerturbKernel perturb_kernel_for(int threads, int groups) {
-#define ES_CASE(T, U) if (threads == T && groups == U) return es_perturb_kernel<T, U, kM, kRows>;
-    ES_TILE_SHAPES(ES_CASE)
-#undef ES_CASE
-    return nullptr;
-}
-
-using StreamKernel = void (*)(const DevTile*, uint64_t, uint64_t, uint32_t);
-
-StreamKernel stream_kernel(int threads, int groups) {
-#define ES_CASE(T, U) if (threads == T && groups == U) return es_stream_kernel<T, U>;
-    ES_TILE_SHAPES(ES_CASE)
-#undef ES_CASE
-    return nullptr;
-}
 
 using ChecksumKernel = void (*)(const DevTile*, uint64_t, uint64_t, const DevRows*,
                                 unsigned long long*);
@@ -1330,20 +1127,6 @@ ChecksumKernel checksum_kernel(int threads, int groups, bool rows) {
     return nullptr;
 }
 
-// streams: 1 (perturb / restore), 2 (swap, two keys), 3 (swap, one key);
-// rows: the launch over strided blocks' tiles.
-PerturbKernel perturb_kernel(int streams, int threads, int groups, bool rows) {
-    switch (streams * 2 + (rows ? 1 : 0)) {
-        case 2: return perturb_kernel_for<1, false>(threads, groups);
-        case 3: return perturb_kernel_for<1, true>(threads, groups);
-        case 4: return perturb_kernel_for<2, false>(threads, groups);
-        case 5: return perturb_kernel_for<2, true>(threads, groups);
-        case 6: return perturb_kernel_for<3, false>(threads, groups);
-        case 7: return perturb_kernel_for<3, true>(threads, groups);
-        default: return nullptr;
-    }
-}
-
 template <bool kRestore>
 UpdateKernel update_kernel_for(bool stochastic, bool rows) {
     if (rows)
@@ -1351,18 +1134,6 @@ UpdateKernel update_kernel_for(bool stochastic, bool rows) {
                           : es_update_kernel<true, false, true, kRestore, 0>;
     return stochastic ? es_update_kernel<true, true, false, kRestore, 0>
                       : es_update_kernel<true, false, false, kRestore, 0>;
-}
-
-using ApplyMasterKernel = void (*)(const DevTile*, uint64_t, uint64_t, const DevRows*, Streams,
-                                   const uint64_t*);
-
-ApplyMasterKernel apply_master_kernel(int threads, int groups, bool rows) {
-#define ES_CASE(T, U)                                                                   \
-    if (threads == T && groups == U)                                                    \
-        return rows ? es_apply_master_kernel<T, U, true> : es_apply_master_kernel<T, U, false>;
-    ES_TILE_SHAPES(ES_CASE)
-#undef ES_CASE
-    return nullptr;
 }
 
 // The update into binary32 masters (mode 1) and the application of members
@@ -1498,7 +1269,7 @@ __device__ __forceinline__ void qtile(const esq::QTileRef& r, const Member* __re
         if (!kFast && e >= r.numel) break;
         const uint32_t n = esq::qnoise_index(r, e);
         uint32_t raw[4];
-        esq::qload<kFast>(r.data, e, r.numel, raw, r.aligned16 != 0u);
+        esq::qload<kFast>(r.data, e, r.numel, raw);
         float inv0, inv1;
         esq::group_inv_scales(r, e, inv0, inv1);
         uint32_t out[4];
@@ -1558,7 +1329,7 @@ __device__ __forceinline__ void qtile(const esq::QTileRef& r, const Member* __re
                 }
             }
         }
-        esq::qstore<kFast>(r.data, e, r.numel, out, r.aligned16 != 0u);
+        esq::qstore<kFast>(r.data, e, r.numel, out);
     }
 }
 
@@ -1644,7 +1415,7 @@ __global__ __launch_bounds__(kThreads) void es_qchecksum_kernel(
             const uint32_t e = r.elem0 + (uint32_t(u) * kThreads + threadIdx.x) * esq::kQGroup;
             if (e >= r.numel) break;
             uint32_t raw[4];
-            esq::qload<false>(r.data, e, r.numel, raw, r.aligned16 != 0u);
+            esq::qload<false>(r.data, e, r.numel, raw);
             const uint32_t n = esq::qnoise_index(r, e);
             acc += checksum_terms<esq::kQGroup, 8, true>(raw, n, uint64_t(n) + (r.numel - e),
                                                          salt);
@@ -1676,14 +1447,11 @@ struct es_plan {
     uint64_t n_tail = 0;            // tail tiles (bounds-checked path)
     uint64_t n_rfull = 0;           // full and tail tiles of strided blocks, after the
     uint64_t n_rtail = 0;           //   others, each with a row map
-    uint32_t grid_perturb = 0;      // workgroups of the perturb / restore launch
-    uint32_t grid_update = 0;       // workgroups of the checksum launch
-    StepShape steps;                // items of the update launch, and its workgroups
-    uint32_t grid_steps = 0;
-    uint32_t grid_perturb_rows = 0; // the same for the strided blocks' launch
-    uint32_t grid_update_rows = 0;
-    StepShape steps_rows;
-    uint32_t grid_steps_rows = 0;
+    uint64_t tail_max = 0;          // elements of the longest tail tile
+    uint64_t rtail_max = 0;         //   and of the longest of strided blocks
+    int cus = 0;                    // compute units of the device
+    uint32_t grid_sum = 0;          // workgroups of the checksum launch
+    uint32_t grid_sum_rows = 0;     //   and of its launch over strided blocks
     int threads = kDefaultThreads;  // lanes per workgroup of the tile kernels
     int groups = kDefaultGroups;    // 8-element groups per lane per tile
     uint64_t tile_elems = 0;        // threads * groups * 8
@@ -1741,21 +1509,56 @@ struct Segment {
     const DevTile* tiles;
     uint64_t n_full, n_tail;
     const DevRows* rows;            // null for the first part
-    uint32_t grid_perturb, grid_update;
-    StepShape steps;
-    uint32_t grid_steps;
+    uint64_t tail_max;
+    uint32_t grid_sum;
 };
 
 int plan_segments(const es_plan_t* p, Segment seg[2]) {
     int n = 0;
     if (p->n_full + p->n_tail > 0)
-        seg[n++] = Segment{p->d_tiles, p->n_full, p->n_tail, nullptr, p->grid_perturb,
-                           p->grid_update, p->steps, p->grid_steps};
+        seg[n++] = Segment{p->d_tiles, p->n_full, p->n_tail, nullptr, p->tail_max, p->grid_sum};
     if (p->n_rfull + p->n_rtail > 0)
         seg[n++] = Segment{p->d_tiles + p->n_full + p->n_tail, p->n_rfull, p->n_rtail, p->d_rows,
-                           p->grid_perturb_rows, p->grid_update_rows, p->steps_rows,
-                           p->grid_steps_rows};
+                           p->rtail_max, p->grid_sum_rows};
     return n;
+}
+
+// The step launch over n_full full tiles of tile_elems elements (a power of
+// two, at least 8192) and n_tail tail tiles of at most tail_max, with steps of
+// step_elems elements.  A tail tile is cut for the longest one; where there are
+// so many of them (tens of thousands of tiny tensors) that they fill the chip
+// several times over, they are cut less and a workgroup goes on to the next
+// step instead, since the empty workgroups of the short ones only cost.
+struct StepLaunch {
+    StepShape shape;
+    uint32_t grid;
+};
+
+StepLaunch step_launch(uint64_t n_full, uint64_t n_tail, uint64_t tail_max, uint64_t tile_elems,
+                       uint64_t step_elems) {
+    constexpr uint64_t kManyTails = 65536;
+    StepShape sh{};
+    while ((step_elems << sh.full_shift) < tile_elems) ++sh.full_shift;
+    while ((step_elems << sh.tail_shift) < tail_max && (n_tail << sh.tail_shift) < kManyTails)
+        ++sh.tail_shift;
+    const uint64_t part = step_elems << sh.tail_shift;
+    sh.tail_steps = static_cast<uint32_t>(std::max<uint64_t>((tail_max + part - 1) / part, 1));
+    return StepLaunch{sh, static_cast<uint32_t>((n_full << sh.full_shift) +
+                                                (n_tail << sh.tail_shift))};
+}
+
+StepLaunch plan_steps(const es_plan_t* p, const Segment& g, int groups) {
+    return step_launch(g.n_full, g.n_tail, g.tail_max, p->tile_elems,
+                       uint64_t(kStepThreads) * groups * kGroupElems);
+}
+
+// Groups per lane and step of the memory-bound passes: four, or two where
+// four would leave wave slots empty (fewer than eight workgroups per CU).
+// Perturb and restore over 1 M parameters: 2 x 4.9 us with two; over the
+// 0.5B-shaped set 603 us with four, 618 with two, 686 with eight.
+bool four_groups(const es_plan_t* p, const Segment& g) {
+    const uint64_t elems = g.n_full * p->tile_elems + g.n_tail * g.tail_max;
+    return elems >= uint64_t(p->cus) * 8 * (kStepThreads * 4 * kGroupElems);
 }
 
 // One pass of the perturb kernel: streams = 1 (seed[0], coef[0]), 2 (two
@@ -1774,9 +1577,13 @@ int launch_streams(es_plan_t* p, int streams, const uint64_t* seed, const double
     const int n_seg = plan_segments(p, seg);
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
-        const PerturbKernel kernel = perturb_kernel(streams, p->threads, p->groups, g.rows != nullptr);
-        hipLaunchKernelGGL(kernel, dim3(g.grid_perturb), dim3(p->threads), 0, s, g.tiles, g.n_full,
-                           g.n_tail, g.rows, st);
+        const bool four = four_groups(p, g);
+        const StepLaunch l = plan_steps(p, g, four ? 4 : 2);
+        const bool strided = g.rows != nullptr;
+        hipLaunchKernelGGL(four ? perturb_kernel<4>(streams, strided)
+                                : perturb_kernel<2>(streams, strided),
+                           dim3(l.grid), dim3(kStepThreads), 0, s, g.tiles, g.n_full, g.rows, st,
+                           l.shape);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "es_perturb_kernel launch");
     }
@@ -1931,7 +1738,7 @@ void row_divisor(uint32_t r, uint32_t& magic, uint32_t& shift) {
 void launch_shape(int& threads, int& groups) {
     threads = env_int("ESOPT_THREADS", kDefaultThreads, 256, 1024);
     groups = env_int("ESOPT_GROUPS", kDefaultGroups, 2, 8);
-    if (perturb_kernel(1, threads, groups, false) == nullptr) {
+    if (checksum_kernel(threads, groups, false) == nullptr) {
         threads = kDefaultThreads;
         groups = kDefaultGroups;
     }
@@ -2181,11 +1988,11 @@ int update_impl(const char* name, es_plan_t* plan, uint8_t* d_scratch, const uin
         // the segment's masters: the delta table runs parallel to the tiles
         const uint64_t* mdelta =
             master ? plan->d_master + (strided ? plan->n_full + plan->n_tail : 0) : nullptr;
-        hipLaunchKernelGGL(kernel, dim3(g.grid_steps), dim3(kStepThreads), 0, s, g.tiles,
-                           g.n_full, g.n_tail, g.rows,
-                           reinterpret_cast<const Member*>(d_scratch + kOffMembers),
+        const StepLaunch l = plan_steps(plan, g, 2);
+        hipLaunchKernelGGL(kernel, dim3(l.grid), dim3(kStepThreads), 0, s, g.tiles, g.n_full,
+                           g.rows, reinterpret_cast<const Member*>(d_scratch + kOffMembers),
                            reinterpret_cast<const UpdateHeader*>(d_scratch + kOffHeader), rk,
-                           rst, mdelta, g.steps);
+                           rst, mdelta, l.shape);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, std::string(name) + ": es_update_kernel launch");
     }
@@ -2304,36 +2111,6 @@ void tile_block(const es_block_t& b, uint64_t tile_elems, PlanTiles& t) {
     }
 }
 
-// Items of a step launch over n_full full tiles and n_tail tail tiles of at
-// most tail_max elements (tile_elems a power of two, at least kStepElems), and
-// its grid.  Large plans take up to four steps per item (the tile's descriptor
-// is read once per item); a plan too small to give every wave slot (eight
-// 256-lane workgroups per CU) eight items takes fewer, down to one step, so
-// that a few tiles still spread over the chip.  A tail tile is cut for the
-// longest one, or left whole where there are so many of them (thousands of
-// tiny tensors) that they fill the chip as they are: the empty items of short
-// tiles would only cost their look-up.
-StepShape step_shape(uint64_t n_full, uint64_t n_tail, uint64_t tail_max, uint64_t tile_elems,
-                     int cus, int wg_per_cu, uint32_t& grid) {
-    const uint64_t slots = uint64_t(cus) * 8;
-    const uint32_t tile_steps = static_cast<uint32_t>(tile_elems / kStepElems);
-    StepShape sh{};
-    sh.full_steps = std::min(4u, tile_steps);
-    while (sh.full_steps > 1 && (n_full + n_tail) * (tile_steps / sh.full_steps) < 8 * slots)
-        sh.full_steps /= 2;
-    while ((sh.full_steps << sh.full_shift) < tile_steps) ++sh.full_shift;
-    const uint64_t most = (tail_max + kStepElems - 1) / kStepElems;     // steps of the longest
-    while ((uint64_t(sh.full_steps) << sh.tail_shift) < most &&
-           (n_tail << sh.tail_shift) < 32 * slots)
-        ++sh.tail_shift;
-    const uint64_t parts = uint64_t(1) << sh.tail_shift;
-    sh.tail_steps = static_cast<uint32_t>(std::max<uint64_t>((most + parts - 1) / parts, 1));
-    const uint64_t items = (n_full << sh.full_shift) + (n_tail << sh.tail_shift);
-    grid = static_cast<uint32_t>(
-        std::min<uint64_t>(std::max<uint64_t>(items, 1), uint64_t(cus) * 4 * wg_per_cu));
-    return sh;
-}
-
 // A plan over tiles laid out by the caller (es_plan_create,
 // es_plan_create_blocks): launch grids, one device allocation for the
 // descriptors and row maps, the scratch.
@@ -2358,7 +2135,6 @@ int finish_plan(const char* name, int device, uint32_t n_tensors, uint64_t numel
     int cus = 0;
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
     if (e != hipSuccess) { delete p; return hip_fail(e, "hipDeviceGetAttribute"); }
-    const int wg_perturb = env_int("ESOPT_PERTURB_WG_PER_CU", kDefaultPerturbWgPerCu, 1, 32);
     const int wg_update = env_int("ESOPT_UPDATE_WG_PER_CU", kDefaultUpdateWgPerCu, 1, 32);
     p->threads = threads;
     p->groups = groups;
@@ -2369,23 +2145,20 @@ int finish_plan(const char* name, int device, uint32_t n_tensors, uint64_t numel
     p->n_tail = n_tail;
     p->n_rfull = n_rfull;
     p->n_rtail = n_rtail;
-    auto grid = [&](uint64_t a, uint64_t b, int per_cu) {
+    auto grid = [&](uint64_t a, uint64_t b, int per_cu) {   // checksum: a grid that strides
         const uint64_t cap = std::max<uint64_t>(std::max(a, b), 1);
         return static_cast<uint32_t>(std::min<uint64_t>(cap, uint64_t(cus) * per_cu));
     };
-    p->grid_perturb = grid(n_full, n_tail, wg_perturb);
-    p->grid_update = grid(n_full, n_tail, wg_update);
-    p->grid_perturb_rows = grid(n_rfull, n_rtail, wg_perturb);
-    p->grid_update_rows = grid(n_rfull, n_rtail, wg_update);
+    p->grid_sum = grid(n_full, n_tail, wg_update);
+    p->grid_sum_rows = grid(n_rfull, n_rtail, wg_update);
+    p->cus = cus;
     auto longest = [](const std::vector<DevTile>& v) {
         uint64_t m = 0;
         for (const DevTile& d : v) m = std::max(m, d.limit - d.elem0);
         return m;
     };
-    p->steps = step_shape(n_full, n_tail, longest(t.tail), p->tile_elems, cus, wg_update,
-                          p->grid_steps);
-    p->steps_rows = step_shape(n_rfull, n_rtail, longest(t.rtail), p->tile_elems, cus, wg_update,
-                               p->grid_steps_rows);
+    p->tail_max = longest(t.tail);
+    p->rtail_max = longest(t.rtail);
     const size_t tile_bytes = sizeof(DevTile) * std::max<size_t>(tiles.size(), 1);
     const size_t rows_bytes = sizeof(DevRows) * rows.size();
     e = hipMalloc(reinterpret_cast<void**>(&p->d_tiles), tile_bytes + rows_bytes);
@@ -2787,10 +2560,13 @@ int es_perturb_master(es_plan_t* plan, uint64_t seed, int32_t sign, float sigma,
         for (int k = 0; k < n_seg; ++k) {
             const Segment& g = seg[k];
             const bool strided = g.rows != nullptr;
-            hipLaunchKernelGGL(apply_master_kernel(plan->threads, plan->groups, strided),
-                               dim3(g.grid_perturb), dim3(plan->threads), 0, s, g.tiles, g.n_full,
-                               g.n_tail, g.rows, st,
-                               plan->d_master + (strided ? plan->n_full + plan->n_tail : 0));
+            const bool four = four_groups(plan, g);
+            const StepLaunch l = plan_steps(plan, g, four ? 4 : 2);
+            hipLaunchKernelGGL(four ? apply_master_kernel<4>(strided)
+                                    : apply_master_kernel<2>(strided),
+                               dim3(l.grid), dim3(kStepThreads), 0, s, g.tiles, g.n_full, g.rows,
+                               st, plan->d_master + (strided ? plan->n_full + plan->n_tail : 0),
+                               l.shape);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess)
                 return hip_fail(e, "es_perturb_master: es_apply_master_kernel launch");
@@ -2809,13 +2585,13 @@ int es_perturb_master(es_plan_t* plan, uint64_t seed, int32_t sign, float sigma,
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
         const bool strided = g.rows != nullptr;
-        hipLaunchKernelGGL(update_master_kernel(strided, true), dim3(g.grid_steps),
-                           dim3(kStepThreads), 0, s, g.tiles, g.n_full, g.n_tail, g.rows,
+        const StepLaunch l = plan_steps(plan, g, 2);
+        hipLaunchKernelGGL(update_master_kernel(strided, true), dim3(l.grid), dim3(kStepThreads),
+                           0, s, g.tiles, g.n_full, g.rows,
                            reinterpret_cast<const Member*>(plan->d_scratch + kOffMembers),
                            reinterpret_cast<const UpdateHeader*>(plan->d_scratch + kOffHeader),
                            RoundKey{0u, 0u}, RestoreArg{0u, 0.0f},
-                           plan->d_master + (strided ? plan->n_full + plan->n_tail : 0),
-                           g.steps);
+                           plan->d_master + (strided ? plan->n_full + plan->n_tail : 0), l.shape);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "es_perturb_master: es_update_kernel launch");
     }
@@ -3090,9 +2866,11 @@ int es_stream_pass(es_plan_t* plan, es_stream_t stream) {
     const int n_seg = plan_segments(plan, seg);
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
-        hipLaunchKernelGGL(stream_kernel(plan->threads, plan->groups), dim3(g.grid_perturb),
-                           dim3(plan->threads), 0, static_cast<hipStream_t>(stream), g.tiles,
-                           g.n_full, g.n_tail, 0u);
+        const bool four = four_groups(plan, g);
+        const StepLaunch l = plan_steps(plan, g, four ? 4 : 2);
+        hipLaunchKernelGGL(four ? es_stream_kernel<4> : es_stream_kernel<2>, dim3(l.grid),
+                           dim3(kStepThreads), 0, static_cast<hipStream_t>(stream), g.tiles,
+                           g.n_full, 0u, l.shape);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "es_stream_kernel launch");
     }
@@ -3159,7 +2937,7 @@ int es_plan_checksum(es_plan_t* plan, uint64_t* out_dev, es_stream_t stream) {
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
         hipLaunchKernelGGL(checksum_kernel(plan->threads, plan->groups, g.rows != nullptr),
-                           dim3(g.grid_update), dim3(plan->threads), 0, s, g.tiles, g.n_full,
+                           dim3(g.grid_sum), dim3(plan->threads), 0, s, g.tiles, g.n_full,
                            g.n_tail, g.rows, out);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "es_checksum_kernel launch");

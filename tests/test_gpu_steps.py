@@ -1,16 +1,16 @@
 """Tensors whose sizes sit at the edges of the step kernels' cuts (a lane's
-8-element groups, a workgroup's step of 4096 elements, items of 1 to 4 steps,
-the 65 536-element tile), at bases that are 16-byte aligned and not: the
-update in its forms against the oracle, the bytes around each tensor
-untouched, and a plan of so many tiny tensors that its tail tiles are not cut
-into items."""
+8-element groups, a workgroup's step of 4096 or 8192 elements, the 65
+536-element tile), at bases that are 16-byte aligned and not: the update in
+its forms, perturb, swap and a member applied from masters against the oracle,
+the bytes around each tensor untouched, and a plan of so many tiny tensors
+that its tail tiles are not cut into steps."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
 from paper_2608_17310_amd import esopt, workloads as wl
-from parity import to_device, to_host, report, assert_parity, update_delta
+from parity import (to_device, to_host, report, assert_parity, update_delta, perturb_delta)
 
 pytestmark = pytest.mark.gpu
 
@@ -68,6 +68,50 @@ def test_update_at_the_edges(pad, flags):
                                       round_seed=3)[0],
            lambda i, el: update_delta(i, SEEDS, SIGNS, REWARDS, ALPHA, SIGMA, flags, el),
            f"update pad {pad} flags {flags}")
+
+
+@pytest.mark.parametrize("pad", [0, 1])
+@pytest.mark.parametrize("filler", [0, 17_000_000])
+def test_perturbation_passes_at_the_edges(pad, filler):
+    """perturb, two-key swap and perturb_master; with a 17 M-element tensor in
+    the plan the steps take four groups per lane instead of two."""
+    bits, flat, parts = _buffer(pad)
+    views = [t for _, t in parts]
+    fill_bits = wl.random_bf16_bits(filler + 3, 55) if filler else None
+    if filler:
+        fill = to_device(fill_bits)
+        views.append(fill)
+        at = np.concatenate([np.arange(9000), 8 * np.random.default_rng(3).integers(0, filler // 8, 500),
+                             np.arange(filler - 9000, filler + 3)]).astype(np.uint64)
+    with esopt.Plan(views) as plan:
+        def check(call, expected, delta, what):
+            before, fbefore = to_host(flat), to_host(fill) if filler else None
+            call()
+            torch.cuda.synchronize()
+            _check(before, flat, parts, lambda b, i: expected(b, i, None), delta, what)
+            if filler:
+                i = len(parts)
+                rep = report(to_host(fill)[at], expected(fbefore[at], i, at), fbefore[at],
+                             delta(i, at))
+                assert_parity(rep, what + " filler")
+
+        check(lambda: plan.perturb(5, -1, SIGMA),
+              lambda b, i, el: oracle.perturb(b, 5, i, -1, SIGMA, elems=el),
+              lambda i, el: perturb_delta(5, i, -1, SIGMA, el), "perturb")
+        check(lambda: plan.swap(5, -1, 6, 1, SIGMA),
+              lambda b, i, el: oracle.swap(b, i, 5, -1, SIGMA, 6, 1, SIGMA, elems=el),
+              lambda i, el: perturb_delta(6, i, 1, SIGMA, el), "swap")
+        ms = [t.float() for t in views]
+        mh = [m.cpu().numpy() for m in ms]
+        plan.set_master(ms)
+        check(lambda: plan.perturb_master(7, 1, SIGMA),
+              lambda b, i, el: oracle.perturb_master(mh[i] if el is None else mh[i][at], 7, i, 1,
+                                                     SIGMA, elems=el),
+              lambda i, el: perturb_delta(7, i, 1, SIGMA, el), "perturb_master")
+    tail = to_host(flat)
+    for o, t in parts:
+        tail[o:o + t.numel()] = bits[o:o + t.numel()]
+    assert np.array_equal(tail, bits)
 
 
 @pytest.mark.parametrize("pad", [0, 1])
