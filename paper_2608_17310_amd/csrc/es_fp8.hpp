@@ -37,6 +37,8 @@
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
+#include "es_noise.hpp"
+
 namespace esf {
 
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -51,33 +53,53 @@ __device__ __forceinline__ void decode4(uint32_t w, float v[4]) {
 }
 
 // A = U = 2^32 u, u = (2 r + 1) 2^-10, r the word's top 9 bits (the spare
-// draw of a perturbation or restore).
-__device__ __forceinline__ uint32_t draw9_fixed(uint32_t w) {
-    return (w & 0xFF800000u) | 0x00400000u;
+// draw of a perturbation or restore), as one bitop3 of vector registers, which
+// two waves can issue together.
+struct DrawBits {
+    uint32_t mask = 0xFF800000u, half = 0x00400000u;
+    __device__ __forceinline__ DrawBits() {
+        asm("" : "+v"(mask));
+        asm("" : "+v"(half));
+    }
+};
+__device__ __forceinline__ uint32_t draw9_fixed(uint32_t w, const DrawBits& k) {
+    return __builtin_amdgcn_bitop3_b32(w, k.mask, k.half, 0xEA);   // (w & mask) | half
 }
 
-// Four values rounded onto the grid by the rules above, a[i] the operand for
-// x[i] >= 0 (its complement serves x[i] < 0), as the codes of one word.  A
+// 16 values rounded onto the grid by the rules above, a[i] the operand for
+// x[i] >= 0 (its complement serves x[i] < 0), as the codes of four words.  A
 // zero result is +0 (the conversion gives -0 for a negative x that rounds to
-// zero; its sign is cleared).
-__device__ __forceinline__ uint32_t round4(const float x[4], const uint32_t a[4]) {
-    float xc[4];
-    uint32_t rn[4];
+// zero; its sign is cleared).  The operands are formed in a simple phase and
+// the clamps and conversions follow in a heavy one (es_noise.hpp); the sign is
+// taken before the clamp, which keeps it.
+__device__ __forceinline__ void round16(const float x[16], uint32_t a[16], uint32_t out[4]) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        xc[i] = __builtin_amdgcn_fmed3f(x[i], -kE4M3Max, kE4M3Max);
-        const uint32_t s = static_cast<uint32_t>(static_cast<int32_t>(__float_as_uint(xc[i])) >> 31);
-        rn[i] = a[i] ^ s;
+    for (int i = 0; i < 16; ++i)
+        a[i] ^= static_cast<uint32_t>(static_cast<int32_t>(__float_as_uint(x[i])) >> 31);
+    es::heavy_phase();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        int w = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int c = 4 * k + i;
+            const float xc = __builtin_amdgcn_fmed3f(x[c], -kE4M3Max, kE4M3Max);
+            const int rn = static_cast<int>(a[c]);
+            w = i == 0   ? __builtin_amdgcn_cvt_sr_fp8_f32(xc, rn, w, 0)
+                : i == 1 ? __builtin_amdgcn_cvt_sr_fp8_f32(xc, rn, w, 1)
+                : i == 2 ? __builtin_amdgcn_cvt_sr_fp8_f32(xc, rn, w, 2)
+                         : __builtin_amdgcn_cvt_sr_fp8_f32(xc, rn, w, 3);
+        }
+        out[k] = static_cast<uint32_t>(w);
     }
-    int w = __builtin_amdgcn_cvt_sr_fp8_f32(xc[0], static_cast<int>(rn[0]), 0, 0);
-    w = __builtin_amdgcn_cvt_sr_fp8_f32(xc[1], static_cast<int>(rn[1]), w, 1);
-    w = __builtin_amdgcn_cvt_sr_fp8_f32(xc[2], static_cast<int>(rn[2]), w, 2);
-    w = __builtin_amdgcn_cvt_sr_fp8_f32(xc[3], static_cast<int>(rn[3]), w, 3);
-    const uint32_t u = static_cast<uint32_t>(w);
-    // bit 7 of each byte of nz: its magnitude (low 7 bits) is nonzero; the
-    // low bits cannot carry out of their byte
-    const uint32_t nz = (u & 0x7F7F7F7Fu) + 0x7F7F7F7Fu;
-    return u & (nz | 0x7F7F7F7Fu);
+    es::simple_phase();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        // bit 7 of each byte of nz: its magnitude (low 7 bits) is nonzero; the
+        // low bits cannot carry out of their byte
+        const uint32_t nz = (out[k] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu;
+        out[k] &= nz | 0x7F7F7F7Fu;
+    }
 }
 
 // Codes that must keep their bytes: not-a-number codes (0x7F, 0xFF) and the

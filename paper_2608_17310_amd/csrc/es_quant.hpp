@@ -22,16 +22,19 @@
 // Elements whose scale is not a normal positive finite binary32 value are
 // left unchanged.
 //
-// Layout: a lane owns 16 consecutive codes (one 16-byte access); a tile is
-// T lanes x U groups x 16 codes.  Both passes are VALU-bound (16 normals per
-// 16 bytes), so they run one group per lane at a time at full occupancy.
+// Layout: a lane owns 16 consecutive codes (one 16-byte access, four Philox
+// blocks in lockstep); a tile is T lanes x U groups x 16 codes, taken in steps
+// of 256 groups.  All passes are VALU-bound (16 normals per 16 bytes).  Of the
+// int8 perturbation's 23.5 instructions per code 15.2 are the noise; the
+// step's float work is done for the 16 codes in a simple phase and its
+// conversions, saturating sums, clamps and packing in a heavy one (swap over
+// the 0.5B-shaped set 563 us without the split, 524 with it).
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
 #include "es_noise.hpp"
-#include "es_table.hpp"
 
 namespace esq {
 
@@ -64,7 +67,7 @@ struct DevQTensor {
     uint32_t magic;
     uint32_t shift;
     uint32_t n_tensors;                         // entries before the sentinel (same in all)
-    uint32_t aligned16;                         // base 16-byte aligned: vector tail groups
+    uint32_t aligned16;                         // base 16-byte aligned
     uint32_t skip;                              // 0, or whole-tensor codes between block rows
     uint32_t cmagic;                            // j / cols (read only when skip > 0)
     uint32_t cshift;
@@ -82,7 +85,6 @@ struct QTileRef {
     uint32_t tensor_id;
     uint32_t magic;
     uint32_t shift;
-    uint32_t aligned16;
     uint32_t skip;
     uint32_t cmagic;
     uint32_t cshift;
@@ -95,27 +97,43 @@ __device__ __forceinline__ uint32_t qnoise_index(const QTileRef& r, uint32_t e) 
     return n;
 }
 
-template <uint32_t kTileElems>
-__device__ __forceinline__ QTileRef qlocate_full(const DevQTensor* __restrict__ tab, uint32_t& t,
-                                                 uint64_t tile) {
-    t = es::seek_tensor(t, tile, tab[0].n_tensors,
-                        [tab](uint32_t i) { return tab[i].first_full; });
-    return QTileRef{tab[t].data, tab[t].scales, tab[t].numel, tab[t].noise0,
-                    static_cast<uint32_t>((tile - tab[t].first_full) * kTileElems), tab[t].row,
-                    tab[t].tensor_id, tab[t].magic, tab[t].shift, tab[t].aligned16,
-                    tab[t].skip, tab[t].cmagic, tab[t].cshift};
+// The entry that owns global tile `tile`: the last one, of the n before the
+// sentinel, whose first(i) is not beyond it (first() does not decrease, and
+// first(0) = 0).  One load per 64-fold step: the lanes of a wave probe the
+// range in parallel, so a workgroup that starts anywhere in the list finds its
+// tensor in two round trips for up to 4096 tensors.  All lanes must be active.
+template <class First>
+__device__ __forceinline__ uint32_t find_tensor(uint64_t tile, uint32_t n, First first) {
+    uint32_t lo = 0, span = n;                  // the owner is one of lo .. lo + span - 1
+    while (span > 1u) {
+        const uint32_t step = (span + 63u) / 64u;
+        const uint32_t at = (threadIdx.x & 63u) * step;
+        const bool below = at < span && first(lo + (at < span ? at : 0u)) <= tile;
+        const uint32_t last = __popcll(__ballot(below)) - 1u;
+        lo += last * step;
+        span = min(step, span - last * step);
+    }
+    return lo;
 }
 
-template <uint32_t kTileElems>
-__device__ __forceinline__ QTileRef qlocate_tail(const DevQTensor* __restrict__ tab, uint32_t& t,
-                                                 uint64_t tile) {
-    t = es::seek_tensor(t, tile, tab[0].n_tensors,
-                        [tab](uint32_t i) { return tab[i].first_tail; });
+__device__ __forceinline__ QTileRef qtile_ref(const DevQTensor& d, uint32_t elem0) {
+    return QTileRef{d.data, d.scales, d.numel, d.noise0, elem0, d.row, d.tensor_id, d.magic,
+                    d.shift, d.skip, d.cmagic, d.cshift};
+}
+
+// Full tile `tile` of the plan, and tail tile `tile`.
+__device__ __forceinline__ QTileRef qlocate_full(const DevQTensor* __restrict__ tab, uint32_t n,
+                                                 uint64_t tile, uint32_t tile_elems) {
+    const uint32_t t = find_tensor(tile, n, [tab](uint32_t i) { return tab[i].first_full; });
+    return qtile_ref(tab[t], static_cast<uint32_t>(tile - tab[t].first_full) * tile_elems);
+}
+
+__device__ __forceinline__ QTileRef qlocate_tail(const DevQTensor* __restrict__ tab, uint32_t n,
+                                                 uint64_t tile, uint32_t tile_elems) {
+    const uint32_t t = find_tensor(tile, n, [tab](uint32_t i) { return tab[i].first_tail; });
     const uint64_t n_full = tab[t + 1].first_full - tab[t].first_full;
-    return QTileRef{tab[t].data, tab[t].scales, tab[t].numel, tab[t].noise0,
-                    static_cast<uint32_t>((n_full + tile - tab[t].first_tail) * kTileElems),
-                    tab[t].row, tab[t].tensor_id, tab[t].magic, tab[t].shift, tab[t].aligned16,
-                    tab[t].skip, tab[t].cmagic, tab[t].cshift};
+    return qtile_ref(tab[t],
+                     static_cast<uint32_t>(n_full + tile - tab[t].first_tail) * tile_elems);
 }
 
 typedef uint32_t q32x4_t __attribute__((ext_vector_type(4)));
@@ -171,44 +189,44 @@ __device__ __forceinline__ void qstore(int8_t* __restrict__ p, uint32_t e, uint3
     }
 }
 
-// The reciprocal of the scale of the 8 codes starting at element j (j is a
-// multiple of 8 and the row length a multiple of 8, so the 8 codes share
-// one scale), or 0 when the scale is not a normal positive finite value.
-// The hardware reciprocal (1 ulp) is well inside the offsets' tolerance.
-__device__ __forceinline__ float inv_scale(const QTileRef& r, uint32_t j) {
+// The scale of the 8 codes starting at element j (j is a multiple of 8 and the
+// row length a multiple of 8, so the 8 codes share one scale); 0 beyond the
+// last code.
+__device__ __forceinline__ float load_scale(const QTileRef& r, uint32_t j) {
     if (j >= r.numel) return 0.0f;
     const ESQ_GLOBAL float* s = (const ESQ_GLOBAL float*)r.scales;
-    const uint32_t idx = r.row == 0u ? 0u : __umulhi(j, r.magic) >> r.shift;
-    const float v = s[idx];
+    return s[r.row == 0u ? 0u : __umulhi(j, r.magic) >> r.shift];
+}
+
+// The two scales of a 16-code group (codes 0-7 and 8-15); one lookup when the
+// row length is a multiple of 16 (both halves in one row).
+__device__ __forceinline__ void group_scales(const QTileRef& r, uint32_t e, float s[2]) {
+    s[0] = load_scale(r, e);
+    s[1] = (r.row & 15u) == 0u ? s[0] : load_scale(r, e + 8);
+}
+
+// The reciprocal of a scale, or 0 when it is not a normal positive finite
+// value.  The hardware reciprocal (1 ulp) is well inside the offsets'
+// tolerance.
+__device__ __forceinline__ float inv_scale(float v) {
     const bool ok = v >= 0x1p-126f && v <= 0x1.fffffep127f;
     return ok ? __builtin_amdgcn_rcpf(v) : 0.0f;
 }
 
-// The two reciprocal scales of a 16-code group (codes 0-7 and 8-15); one
-// lookup when the row length is a multiple of 16 (both halves in one row).
-__device__ __forceinline__ void group_inv_scales(const QTileRef& r, uint32_t e, float& inv0,
-                                                 float& inv1) {
-    inv0 = inv_scale(r, e);
-    inv1 = (r.row & 15u) == 0u ? inv0 : inv_scale(r, e + 8);
-}
+// One noise stream of the 16 codes of a group whose first code has
+// whole-tensor index n (a multiple of 16): the words of its four blocks, the
+// radius factors and the trigonometric values (es_noise.hpp).
+struct GroupNoise {
+    es::Words w[4];
+    float rad[8], c[8], sn[8];
+};
 
-// One noise stream's scaled normals for the 16 codes of a group whose first
-// code has whole-tensor index n: acc[i] += w_k * (normal of element n + i),
-// w_k = weight * sqrt(2 ln 2).
-__device__ __forceinline__ void qgroup_axpy(uint32_t n, uint32_t tensor_id, uint32_t k0,
-                                            uint32_t k1, float w_k, float acc[16]) {
-    const uint32_t q = n >> 2;                  // multiple of 4: q + 3 does not carry
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const es::Words w = es::philox4x32_10(q + c, 0u, tensor_id, es::kDomainNoise, k0, k1);
-        float t, cs, sn;
-        es::scaled_pair(w.w0, w.w1, w_k, t, cs, sn);
-        acc[4 * c] = __builtin_fmaf(t, cs, acc[4 * c]);
-        acc[4 * c + 1] = __builtin_fmaf(t, sn, acc[4 * c + 1]);
-        es::scaled_pair(w.w2, w.w3, w_k, t, cs, sn);
-        acc[4 * c + 2] = __builtin_fmaf(t, cs, acc[4 * c + 2]);
-        acc[4 * c + 3] = __builtin_fmaf(t, sn, acc[4 * c + 3]);
-    }
+__device__ __forceinline__ void group_noise(uint32_t n, uint32_t tensor_id, uint32_t k0,
+                                            uint32_t k1, GroupNoise& g) {
+    const uint32_t q0 = n >> 2;                 // multiple of 4: q0 + 3 does not carry
+    const uint32_t q[4] = {q0, q0 + 1u, q0 + 2u, q0 + 3u};
+    es::philox_quads<4>(q, 0u, tensor_id, k0, k1, g.w);
+    es::box_muller_quads<4>(g.w, g.rad, g.c, g.sn);
 }
 
 // The low bytes of four 32-bit codes packed into one word (code i in byte
@@ -222,42 +240,45 @@ __device__ __forceinline__ uint32_t pack_codes(int32_t c0, int32_t c1, int32_t c
 }
 
 // floor(x) as an integer in one instruction (the compiler emits a floor and
-// a conversion); x is within +-2^31 here.
+// a conversion), saturating at the ends of int32.
 __device__ __forceinline__ int32_t floor_to_int(float x) {
     int32_t r;
     asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
     return r;
 }
 
-// 1 + (2 r + 1) 2^-10 as a binary32 from the top 9 bits r of a noise word.
-// `one_plus_half_step` is 0x3F802000 (1 + 2^-10) held in a vector register
-// by the caller: with the mask in a scalar register the masking and the OR
-// are then one v_and_or_b32 (a VOP3 instruction reads at most one scalar
-// register or literal on this architecture).
-__device__ __forceinline__ float spare_one_plus(uint32_t w, uint32_t one_plus_half_step) {
-    return __uint_as_float(((w >> 9) & 0x007FC000u) | one_plus_half_step);
-}
-
-// 0x3F802000 in a vector register (see spare_one_plus).
-__device__ __forceinline__ uint32_t one_plus_half_step_vgpr() {
-    uint32_t c = 0x3F802000u;
-    asm volatile("" : "+v"(c));
-    return c;
+// 1 + (2 r + 1) 2^-10 as a binary32 from the top 9 bits r of a noise word:
+// ((w >> 9) & 0x007FC000) | 0x3F802000 with both constants in vector registers
+// (SpareBits), one shift and one bitop3, which two waves can issue together.
+struct SpareBits {
+    uint32_t mask = 0x007FC000u, one_plus = 0x3F802000u;
+    __device__ __forceinline__ SpareBits() {
+        asm("" : "+v"(mask));
+        asm("" : "+v"(one_plus));
+    }
+};
+__device__ __forceinline__ float spare_one_plus(uint32_t w, const SpareBits& k) {
+    return __uint_as_float(__builtin_amdgcn_bitop3_b32(w >> 9, k.mask, k.one_plus, 0xEA));
 }
 
 // Perturb / restore code: clamp(q +- floor(d + (2 r + 1) 2^-10), lo, 127)
-// from v = d + f, f = 1 + (2 r + 1) 2^-10 (formed by the caller as one FMA):
-// floor(v) - 1.  v is capped at +-2^30 quanta, far beyond what any code can
-// absorb, so the integer arithmetic cannot overflow.  lo is -127; a caller
+// from v = d + f, f = 1 + (2 r + 1) 2^-10 (formed by the caller as one FMA;
+// finite): the step is floor(v) - 1.  The conversion saturates at the ends of
+// int32 and so does the sum, so a step far beyond what any code can absorb
+// clamps to the right end without a bound on v first.  lo is -127; a caller
 // whose scale is invalid passes d = 0 (so the step is 0) and lo = -128, which
 // returns every code unchanged without a branch.
 template <bool kNegate>
 __device__ __forceinline__ int32_t qstep9(int32_t q, float v, int32_t lo) {
-    const int32_t k = floor_to_int(__builtin_amdgcn_fmed3f(v, -0x1p30f, 0x1p30f)) - 1;
-    const int32_t x = kNegate ? q - k : q + k;
+    const int32_t k = floor_to_int(v);
+    int32_t x, r;
+    if constexpr (kNegate) {
+        asm("v_sub_i32 %0, %1, %2 clamp" : "=v"(x) : "v"(q + 1), "v"(k));
+    } else {
+        asm("v_add_i32 %0, %1, %2 clamp" : "=v"(x) : "v"(q - 1), "v"(k));
+    }
     // min(max(x, lo), 127) in one v_med3_i32 (lo <= 127 always; the compiler
     // only forms the median for constant bounds)
-    int32_t r;
     asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(lo), "s"(127));
     return r;
 }

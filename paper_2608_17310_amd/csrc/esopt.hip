@@ -34,9 +34,10 @@
 //     pair their issue.  4B-shaped set, N = 32: 50.8 -> 43.7 ms.  Swap is the
 //     perturb kernel with two streams and a bf16 rounding between them.
 //   * The quantized path (int8 codes, es_quant.hpp; fp8 E4M3 codes,
-//     es_fp8.hpp) has a tensor table searched per tile and tiles of 16-code
-//     groups; all its passes are VALU-bound: eight 1024-lane
-//     workgroups per CU, a group per lane at a time.
+//     es_fp8.hpp) has a tensor table, searched once per workgroup, and
+//     256-lane workgroups of up to eight steps of one 16-code group per lane;
+//     all its passes are VALU-bound.  0.5B-shaped set, int8 swap 602 -> 506
+//     us; an eighth of it, fp8 update of 8 members 254 -> 196 us.
 //   * Perturb/restore read and write each parameter once (4 bytes of HBM
 //     traffic per parameter).  The update regenerates the noise of all
 //     distinct member seeds for the same 8 elements in registers,
@@ -71,7 +72,6 @@
 #include "es_fp8.hpp"
 #include "es_noise.hpp"
 #include "es_quant.hpp"
-#include "es_table.hpp"
 
 namespace {
 
@@ -1164,225 +1164,249 @@ struct QPass {
     Member m_from;
 };
 
-// Perturb / restore of one 16-code group (n: the whole-tensor index of its
-// first code): per quad of codes one noise call, whose words give the four
-// normals and the four rounding draws.  The scale's reciprocal is folded into
-// the pair's radius factor, and d + f is one FMA.
+// Perturb / restore of one 16-code group from its noise: per quad of codes one
+// block, whose words give the four normals and the four rounding draws.  The
+// scale's reciprocal is folded into the pair's radius factor, and d + f is one
+// FMA.
 template <bool kNegate>
-__device__ __forceinline__ void qperturb_group(const uint32_t raw[4], uint32_t n,
-                                               uint32_t tensor_id, const Member& m, float inv0,
-                                               float inv1, uint32_t out[4]) {
-    const uint32_t q = n >> 2;                  // multiple of 4: q + 3 does not carry
+__device__ __forceinline__ void qperturb_group(const uint32_t raw[4], const esq::GroupNoise& gn,
+                                               float w_k, const float inv[2], uint32_t out[4]) {
     // an invalid scale has inv = 0: its step is 0 and its codes clamp to
-    // [-128, 127], i.e. they are left as they are
-    const float wk_inv[2] = {m.w_k * inv0, m.w_k * inv1};
-    const int32_t lo[2] = {inv0 != 0.0f ? -127 : -128, inv1 != 0.0f ? -127 : -128};
-    const uint32_t one_plus = esq::one_plus_half_step_vgpr();
+    // [-128, 127], i.e. they are left as they are; the bound keeps a step in
+    // quanta finite (it saturates every code long before), so that no product
+    // with a zero cosine is a NaN
+    const float wk_inv[2] = {__builtin_amdgcn_fmed3f(w_k * inv[0], -0x1p100f, 0x1p100f),
+                             __builtin_amdgcn_fmed3f(w_k * inv[1], -0x1p100f, 0x1p100f)};
+    const int32_t lo[2] = {inv[0] != 0.0f ? -127 : -128, inv[1] != 0.0f ? -127 : -128};
+    const esq::SpareBits bits;
+    float v[16];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        const es::Words w = es::philox4x32_10(q + c, 0u, tensor_id, es::kDomainNoise, m.k0, m.k1);
-        const uint32_t ws[4] = {w.w0, w.w1, w.w2, w.w3};
+        const uint32_t ws[4] = {gn.w[c].w0, gn.w[c].w1, gn.w[c].w2, gn.w[c].w3};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int p = 2 * c + i / 2;
+            const float t = wk_inv[c >> 1] * gn.rad[p];
+            v[4 * c + i] = __builtin_fmaf(t, (i & 1) ? gn.sn[p] : gn.c[p],
+                                          esq::spare_one_plus(ws[i], bits));
+        }
+    }
+    es::heavy_phase();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
         int32_t code[4];
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            float t, cs, sn;
-            es::scaled_pair(ws[2 * p], ws[2 * p + 1], wk_inv[c >> 1], t, cs, sn);
-            const float trig[2] = {cs, sn};
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int i = 2 * p + h;
-                const int32_t qc = static_cast<int8_t>(raw[c] >> (8 * i));
-                const float v = __builtin_fmaf(t, trig[h], esq::spare_one_plus(ws[i], one_plus));
-                code[i] = esq::qstep9<kNegate>(qc, v, lo[c >> 1]);
-            }
-        }
+        for (int i = 0; i < 4; ++i)
+            code[i] = esq::qstep9<kNegate>(static_cast<int8_t>(raw[c] >> (8 * i)), v[4 * c + i],
+                                           lo[c >> 1]);
         out[c] = esq::pack_codes(code[0], code[1], code[2], code[3]);
     }
+    es::simple_phase();
 }
 
 // Code formats of a quantized plan.
 constexpr int kFmtInt8 = 0;
 constexpr int kFmtE4M3 = 1;
 
-// fp8 perturb / restore of one 16-code group (n as above): per quad of codes one noise
-// call, whose words give the four normals and the four spare draws.  The
+// fp8 perturb / restore of one 16-code group from its noise (as above).  The
 // scale's reciprocal is folded into the pair's radius factor; x = v -+ d is
 // one fused multiply-add, and the restore rounds with the complementary
 // rule (operand ~U for U), so it undoes the perturbation inside a binade.
 template <bool kNegate>
-__device__ __forceinline__ void f8perturb_group(const uint32_t raw[4], uint32_t n,
-                                                uint32_t tensor_id, const Member& m, float inv0,
-                                                float inv1, uint32_t out[4]) {
-    const uint32_t q = n >> 2;                  // multiple of 4: q + 3 does not carry
-    const float wk_inv[2] = {m.w_k * inv0, m.w_k * inv1};
+__device__ __forceinline__ void f8perturb_group(const uint32_t raw[4], const esq::GroupNoise& gn,
+                                                float w_k, const float inv[2], uint32_t out[4]) {
+    const float wk_inv[2] = {w_k * inv[0], w_k * inv[1]};
+    const esf::DrawBits bits;
+    float x[16];
+    uint32_t a[16];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        const es::Words w = es::philox4x32_10(q + c, 0u, tensor_id, es::kDomainNoise, m.k0, m.k1);
-        const uint32_t ws[4] = {w.w0, w.w1, w.w2, w.w3};
-        float v[4], x[4];
-        uint32_t a[4];
-        esf::decode4(raw[c], v);
+        const uint32_t ws[4] = {gn.w[c].w0, gn.w[c].w1, gn.w[c].w2, gn.w[c].w3};
+        esf::decode4(raw[c], x + 4 * c);
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            float t, cs, sn;
-            es::scaled_pair(ws[2 * p], ws[2 * p + 1], wk_inv[c >> 1], t, cs, sn);
-            const float trig[2] = {cs, sn};
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int i = 2 * p + h;
-                const uint32_t u = esf::draw9_fixed(ws[i]);
-                x[i] = __builtin_fmaf(kNegate ? -t : t, trig[h], v[i]);
-                a[i] = kNegate ? ~u : u;
-            }
+        for (int i = 0; i < 4; ++i) {
+            const int p = 2 * c + i / 2;
+            const float t = wk_inv[c >> 1] * gn.rad[p];
+            const uint32_t u = esf::draw9_fixed(ws[i], bits);
+            x[4 * c + i] = __builtin_fmaf(kNegate ? -t : t, (i & 1) ? gn.sn[p] : gn.c[p],
+                                          x[4 * c + i]);
+            a[4 * c + i] = kNegate ? ~u : u;
         }
-        out[c] = esf::round4(x, a);
     }
+    esf::round16(x, a, out);
 }
 
 // Perturb (kNegate false) or restore of one 16-code group in the plan's
 // format, codes with an invalid scale or a not-a-number code left as they are.
 template <bool kNegate, int kFmt>
-__device__ __forceinline__ void qmember_group(const uint32_t raw[4], uint32_t n,
-                                              uint32_t tensor_id, const Member& m, float inv0,
-                                              float inv1, uint32_t out[4]) {
+__device__ __forceinline__ void qmember_group(const uint32_t raw[4], const esq::GroupNoise& gn,
+                                              float w_k, const float inv[2], uint32_t out[4]) {
     if constexpr (kFmt == kFmtE4M3) {
-        f8perturb_group<kNegate>(raw, n, tensor_id, m, inv0, inv1, out);
-        esf::keep_special(raw, inv0, inv1, out);
+        f8perturb_group<kNegate>(raw, gn, w_k, inv, out);
+        esf::keep_special(raw, inv[0], inv[1], out);
     } else {
-        qperturb_group<kNegate>(raw, n, tensor_id, m, inv0, inv1, out);
+        qperturb_group<kNegate>(raw, gn, w_k, inv, out);
     }
 }
 
-// One tile of a quantized pass (int8 or E4M3 codes, kFmt): for each of the
-// lane's 16-code groups in turn, the step in scale units (binary32) and the
-// stochastically rounded, clamped code.  e indexes the codes and scales at hand; n, the whole-tensor index
-// of code e, selects the noise and the rounding draws.
-// kSwap: the member ps.m_from reverted and ps.m applied in registers, the
-// codes of the two separate passes.
-template <int kThreads, int kU, bool kFast, bool kTable, bool kNegate, int kFmt, bool kSwap>
-__device__ __forceinline__ void qtile(const esq::QTileRef& r, const Member* __restrict__ members,
-                                      uint32_t n_members, const QPass& ps) {
-    const uint32_t e0 = r.elem0 + threadIdx.x * esq::kQGroup;
-#pragma unroll 1
-    for (int u = 0; u < kU; ++u) {
-        const uint32_t e = e0 + uint32_t(u) * kThreads * esq::kQGroup;
-        if (!kFast && e >= r.numel) break;
-        const uint32_t n = esq::qnoise_index(r, e);
-        uint32_t raw[4];
-        esq::qload<kFast>(r.data, e, r.numel, raw);
-        float inv0, inv1;
-        esq::group_inv_scales(r, e, inv0, inv1);
-        uint32_t out[4];
-        if constexpr (kSwap) {
-            uint32_t mid[4];
-            qmember_group<true, kFmt>(raw, n, r.tensor_id, ps.m_from, inv0, inv1, mid);
-            qmember_group<false, kFmt>(mid, n, r.tensor_id, ps.m, inv0, inv1, out);
-        } else if constexpr (!kTable) {
-            qmember_group<kNegate, kFmt>(raw, n, r.tensor_id, ps.m, inv0, inv1, out);
-        } else {
-            float acc[16];
+// The quantized passes.
+enum class QKind { kPerturb, kRestore, kUpdate, kSwap };
+
+// One step of a quantized pass (int8 or E4M3 codes, kFmt): the lane's 16-code
+// group at code e of its tensor, the step in scale units (binary32) and the
+// stochastically rounded, clamped code.  e indexes the codes and scales at
+// hand; n, the whole-tensor index of code e, selects the noise and the
+// rounding draws.  A swap reverts the member ps.m_from and applies ps.m in
+// registers, the codes of the two separate passes; members that share a key
+// (antithetic partners) share their noise.
+//
+// VALU-bound: four Philox blocks in lockstep per group and stream
+// (es_noise.hpp); the codes and scales are loaded first and used after the
+// noise, which their latency lies under.
+template <bool kFast, QKind kKind, int kFmt>
+__device__ __forceinline__ void qstep_group(const esq::QTileRef& r, uint32_t e,
+                                            const Member* __restrict__ members,
+                                            uint32_t n_members, const QPass& ps) {
+    const uint32_t n = esq::qnoise_index(r, e);
+    uint32_t raw[4], out[4];
+    float sc[2], inv[2];
+    esq::qload<kFast>(r.data, e, r.numel, raw);
+    esq::group_scales(r, e, sc);
+    if constexpr (kKind != QKind::kUpdate) {
+        esq::GroupNoise gn;
+        const Member& first = kKind == QKind::kSwap ? ps.m_from : ps.m;
+        esq::group_noise(n, r.tensor_id, first.k0, first.k1, gn);
+        inv[0] = esq::inv_scale(sc[0]);
+        inv[1] = esq::inv_scale(sc[1]);
+        constexpr bool kNegate = kKind != QKind::kPerturb;
+        qmember_group<kNegate, kFmt>(raw, gn, first.w_k, inv, out);
+        if constexpr (kKind == QKind::kSwap) {
+            if (ps.m.k0 != ps.m_from.k0 || ps.m.k1 != ps.m_from.k1)
+                esq::group_noise(n, r.tensor_id, ps.m.k0, ps.m.k1, gn);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-            for (uint32_t d = 0; d < n_members; ++d) {
-                const Member m = members[d];
-                if (is_zero_weight(m.w_k)) continue;
-                esq::qgroup_axpy(n, r.tensor_id, m.k0, m.k1, m.w_k, acc);
+            for (int k = 0; k < 4; ++k) raw[k] = out[k];
+            qmember_group<false, kFmt>(raw, gn, ps.m.w_k, inv, out);
+        }
+    } else {
+        float acc[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+        for (uint32_t d = 0; d < n_members; ++d) {
+            const Member m = members[d];
+            if (is_zero_weight(m.w_k)) continue;
+            esq::GroupNoise gn;
+            esq::group_noise(n, r.tensor_id, m.k0, m.k1, gn);
+            pair_axpy(gn.rad, gn.c, gn.sn, m.w_k, acc);
+        }
+        inv[0] = esq::inv_scale(sc[0]);
+        inv[1] = esq::inv_scale(sc[1]);
+        const es::Words da =
+            es::philox4x32_10(n >> 3, 0u, r.tensor_id, es::kDomainRounding, ps.dk0, ps.dk1);
+        const es::Words db =
+            es::philox4x32_10((n >> 3) + 1u, 0u, r.tensor_id, es::kDomainRounding, ps.dk0, ps.dk1);
+        const uint32_t dw[8] = {da.w0, da.w1, da.w2, da.w3, db.w0, db.w1, db.w2, db.w3};
+        if constexpr (kFmt == kFmtE4M3) {
+            // x = v + acc / s (one fused multiply-add), rounded onto the
+            // grid with the threshold 1 - r 2^-16 (operand r 2^16)
+            float x[16];
+            uint32_t a[16];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                esf::decode4(raw[k], x + 4 * k);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int c = 4 * k + i;
+                    const uint32_t d = dw[c >> 1];
+                    a[c] = (c & 1) ? (d & 0xFFFF0000u) : (d << 16);
+                    x[c] = __builtin_fmaf(acc[c], inv[c / 8], x[c]);
+                }
             }
-            const es::Words da =
-                es::philox4x32_10(n >> 3, 0u, r.tensor_id, es::kDomainRounding, ps.dk0, ps.dk1);
-            const es::Words db = es::philox4x32_10((n >> 3) + 1u, 0u, r.tensor_id,
-                                                   es::kDomainRounding, ps.dk0, ps.dk1);
-            const uint32_t dw[8] = {da.w0, da.w1, da.w2, da.w3, db.w0, db.w1, db.w2, db.w3};
-            if constexpr (kFmt == kFmtE4M3) {
-                // x = v + acc / s (one fused multiply-add), rounded onto the
-                // grid with the threshold 1 - r 2^-16 (operand r 2^16)
+            esf::round16(x, a, out);
+            esf::keep_special(raw, inv[0], inv[1], out);
+        } else {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    float v[4], x[4];
-                    uint32_t a[4];
-                    esf::decode4(raw[k], v);
+            for (int k = 0; k < 4; ++k) {
+                uint32_t w = 0;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int c = 4 * k + i;
-                        const uint32_t d = dw[c >> 1];
-                        a[i] = (c & 1) ? (d & 0xFFFF0000u) : (d << 16);
-                        x[i] = __builtin_fmaf(acc[c], c < 8 ? inv0 : inv1, v[i]);
-                    }
-                    out[k] = esf::round4(x, a);
+                for (int i = 0; i < 4; ++i) {
+                    const int c = 4 * k + i;
+                    const int32_t q = static_cast<int8_t>(raw[k] >> (8 * i));
+                    const uint32_t draw = (dw[c >> 1] >> (16 * (c & 1))) & 0xFFFFu;
+                    const int32_t v =
+                        inv[c / 8] != 0.0f ? esq::qstep<false>(q, acc[c] * inv[c / 8], draw) : q;
+                    w |= (static_cast<uint32_t>(v) & 0xFFu) << (8 * i);
                 }
-                esf::keep_special(raw, inv0, inv1, out);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    uint32_t w = 0;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int c = 4 * k + i;
-                        const float inv = c < 8 ? inv0 : inv1;
-                        const int32_t q = static_cast<int8_t>(raw[k] >> (8 * i));
-                        const uint32_t draw = (dw[c >> 1] >> (16 * (c & 1))) & 0xFFFFu;
-                        const int32_t v =
-                            inv != 0.0f ? esq::qstep<false>(q, acc[c] * inv, draw) : q;
-                        w |= (static_cast<uint32_t>(v) & 0xFFu) << (8 * i);
-                    }
-                    out[k] = w;
-                }
+                out[k] = w;
             }
         }
-        esq::qstore<kFast>(r.data, e, r.numel, out);
     }
+    esq::qstore<kFast>(r.data, e, r.numel, out);
 }
 
 // A pass over the whole quantized parameter list: perturb / restore (one
 // inline member, draws from its own noise words), swap (two inline members)
 // or the update (member table and header written by es_prepare_kernel, draws
-// of domain 1 under the rounding seed).
-template <int kThreads, int kU, bool kTable, bool kNegate, int kFmt, bool kSwap>
-__global__ __launch_bounds__(kThreads) void es_qpass_kernel(const esq::DevQTensor* __restrict__ tab,
-                                                            uint64_t n_full, uint64_t n_tail,
-                                                            const Member* __restrict__ members,
-                                                            const UpdateHeader* __restrict__ hdr,
-                                                            QPass ps) {
-    constexpr uint32_t kTileElems = uint32_t(kThreads) * kU * esq::kQGroup;
+// of domain 1 under the rounding seed).  A workgroup takes full_steps (tail_
+// steps) steps of 256 lanes x 16 codes of one tile of tile_elems codes,
+// 2^full_shift (2^tail_shift) workgroups per tile.
+struct QShape {
+    uint32_t tile_elems, n_tensors;
+    uint32_t full_shift, full_steps;
+    uint32_t tail_shift, tail_steps;
+};
+constexpr uint32_t kQStepCodes = kStepThreads * esq::kQGroup;
+
+template <QKind kKind, int kFmt>
+__global__ __launch_bounds__(kStepThreads) void es_qpass_kernel(
+    const esq::DevQTensor* __restrict__ tab, uint64_t n_full, const Member* __restrict__ members,
+    const UpdateHeader* __restrict__ hdr, QPass ps, QShape sh) {
     uint32_t n_members = 1;
-    if constexpr (kTable) {
+    if constexpr (kKind == QKind::kUpdate) {
         if (hdr->n_live == 0u) return;      // nothing to add: codes are not written
         n_members = hdr->n_distinct;
     }
-    uint32_t t = 0;
-    for (uint64_t tile = blockIdx.x; tile < n_full; tile += gridDim.x)
-        qtile<kThreads, kU, true, kTable, kNegate, kFmt, kSwap>(
-            esq::qlocate_full<kTileElems>(tab, t, tile), members, n_members, ps);
-    t = 0;
-    for (uint64_t tile = blockIdx.x; tile < n_tail; tile += gridDim.x)
-        qtile<kThreads, kU, false, kTable, kNegate, kFmt, kSwap>(
-            esq::qlocate_tail<kTileElems>(tab, t, tile), members, n_members, ps);
+    const uint64_t full_items = n_full << sh.full_shift;
+    const uint64_t i = blockIdx.x;
+    if (i < full_items) {
+        const uint32_t part = static_cast<uint32_t>(i) & ((1u << sh.full_shift) - 1u);
+        const esq::QTileRef r = esq::qlocate_full(tab, sh.n_tensors, i >> sh.full_shift,
+                                                  sh.tile_elems);
+        const uint32_t e0 = r.elem0 + part * sh.full_steps * kQStepCodes +
+                            threadIdx.x * esq::kQGroup;
+#pragma unroll 1
+        for (uint32_t k = 0; k < sh.full_steps; ++k)
+            qstep_group<true, kKind, kFmt>(r, e0 + k * kQStepCodes, members, n_members, ps);
+        return;
+    }
+    const uint64_t j = i - full_items;
+    const uint32_t part = static_cast<uint32_t>(j) & ((1u << sh.tail_shift) - 1u);
+    const esq::QTileRef r = esq::qlocate_tail(tab, sh.n_tensors, j >> sh.tail_shift,
+                                              sh.tile_elems);
+    const uint32_t e0 = r.elem0 + part * sh.tail_steps * kQStepCodes + threadIdx.x * esq::kQGroup;
+    const uint32_t end = min(r.numel - r.elem0, sh.tile_elems) + r.elem0;   // the tile's
+#pragma unroll 1
+    for (uint32_t k = 0; k < sh.tail_steps; ++k) {
+        const uint32_t e = e0 + k * kQStepCodes;
+        if (e >= end) return;
+        qstep_group<false, kKind, kFmt>(r, e, members, n_members, ps);
+    }
 }
 
-using QPassKernel = void (*)(const esq::DevQTensor*, uint64_t, uint64_t, const Member*,
-                             const UpdateHeader*, QPass);
-
-enum class QKind { kPerturb, kRestore, kUpdate, kSwap };
+using QPassKernel = void (*)(const esq::DevQTensor*, uint64_t, const Member*, const UpdateHeader*,
+                             QPass, QShape);
 
 template <int kFmt>
-QPassKernel qpass_kernel_for(int threads, int groups, QKind kind) {
-#define ES_CASE(T, U)                                                                      \
-    if (threads == T && groups == U) {                                                     \
-        switch (kind) {                                                                    \
-            case QKind::kPerturb: return es_qpass_kernel<T, U, false, false, kFmt, false>; \
-            case QKind::kRestore: return es_qpass_kernel<T, U, false, true, kFmt, false>;  \
-            case QKind::kUpdate: return es_qpass_kernel<T, U, true, false, kFmt, false>;   \
-            case QKind::kSwap: return es_qpass_kernel<T, U, false, false, kFmt, true>;     \
-        }                                                                                  \
+QPassKernel qpass_kernel_for(QKind kind) {
+    switch (kind) {
+        case QKind::kPerturb: return es_qpass_kernel<QKind::kPerturb, kFmt>;
+        case QKind::kRestore: return es_qpass_kernel<QKind::kRestore, kFmt>;
+        case QKind::kUpdate: return es_qpass_kernel<QKind::kUpdate, kFmt>;
+        default: return es_qpass_kernel<QKind::kSwap, kFmt>;
     }
-    ES_TILE_SHAPES(ES_CASE)
-#undef ES_CASE
-    return nullptr;
 }
 
-QPassKernel qpass_kernel(int threads, int groups, QKind kind, int format) {
-    return format == kFmtE4M3 ? qpass_kernel_for<kFmtE4M3>(threads, groups, kind)
-                              : qpass_kernel_for<kFmtInt8>(threads, groups, kind);
+QPassKernel qpass_kernel(QKind kind, int format) {
+    return format == kFmtE4M3 ? qpass_kernel_for<kFmtE4M3>(kind) : qpass_kernel_for<kFmtInt8>(kind);
 }
 
 // Quantized plan: the same sum with b the code's 8 bits and j the element's
@@ -1390,13 +1414,12 @@ QPassKernel qpass_kernel(int threads, int groups, QKind kind, int format) {
 // consecutive).
 template <int kThreads, int kU>
 __global__ __launch_bounds__(kThreads) void es_qchecksum_kernel(
-    const esq::DevQTensor* __restrict__ tab, uint64_t n_full, uint64_t n_tail,
+    const esq::DevQTensor* __restrict__ tab, uint64_t n_full, uint64_t n_tail, uint32_t n_tensors,
     unsigned long long* __restrict__ out) {
     constexpr uint32_t kTileElems = uint32_t(kThreads) * kU * esq::kQGroup;
     uint64_t acc = 0;
-    uint32_t t = 0;
     for (uint64_t tile = blockIdx.x; tile < n_full; tile += gridDim.x) {
-        const esq::QTileRef r = esq::qlocate_full<kTileElems>(tab, t, tile);
+        const esq::QTileRef r = esq::qlocate_full(tab, n_tensors, tile, kTileElems);
         const uint64_t salt = uint64_t(r.tensor_id) * kSumT;
 #pragma unroll 1
         for (int u = 0; u < kU; ++u) {
@@ -1406,9 +1429,8 @@ __global__ __launch_bounds__(kThreads) void es_qchecksum_kernel(
             acc += checksum_terms<esq::kQGroup, 8, false>(raw, esq::qnoise_index(r, e), 0, salt);
         }
     }
-    t = 0;
     for (uint64_t tile = blockIdx.x; tile < n_tail; tile += gridDim.x) {
-        const esq::QTileRef r = esq::qlocate_tail<kTileElems>(tab, t, tile);
+        const esq::QTileRef r = esq::qlocate_tail(tab, n_tensors, tile, kTileElems);
         const uint64_t salt = uint64_t(r.tensor_id) * kSumT;
 #pragma unroll 1
         for (int u = 0; u < kU; ++u) {
@@ -1424,7 +1446,8 @@ __global__ __launch_bounds__(kThreads) void es_qchecksum_kernel(
     add_workgroup_sum<kThreads>(acc, out);
 }
 
-using QChecksumKernel = void (*)(const esq::DevQTensor*, uint64_t, uint64_t, unsigned long long*);
+using QChecksumKernel = void (*)(const esq::DevQTensor*, uint64_t, uint64_t, uint32_t,
+                                 unsigned long long*);
 
 QChecksumKernel qchecksum_kernel(int threads, int groups) {
 #define ES_CASE(T, U) if (threads == T && groups == U) return es_qchecksum_kernel<T, U>;
@@ -1473,7 +1496,9 @@ struct es_qplan {
     uint64_t numel = 0;
     uint64_t n_full = 0;
     uint64_t n_tail = 0;
-    uint32_t grid = 0;              // workgroups of every quantized pass
+    uint64_t tail_max = 0;          // codes of the longest tail tile
+    int cus = 0;                    // compute units of the device
+    uint32_t grid = 0;              // workgroups of the checksum launch
     int threads = kDefaultThreads;
     int groups = kDefaultQGroups;   // 16-code groups per lane per tile
     int format = kFmtInt8;          // ES_QFORMAT_INT8 or ES_QFORMAT_E4M3 (one per plan)
@@ -1617,10 +1642,29 @@ int check_qdevice(const es_qplan_t* p) {
 
 int launch_qpass(es_qplan_t* p, QKind kind, const QPass& ps, hipStream_t s) {
     if (p->n_full + p->n_tail == 0) return ES_OK;
-    const QPassKernel kernel = qpass_kernel(p->threads, p->groups, kind, p->format);
-    hipLaunchKernelGGL(kernel, dim3(p->grid), dim3(p->threads), 0, s, p->d_tab, p->n_full,
-                       p->n_tail, reinterpret_cast<const Member*>(p->d_scratch + kOffMembers),
-                       reinterpret_cast<const UpdateHeader*>(p->d_scratch + kOffHeader), ps);
+    QShape sh{};
+    sh.tile_elems = static_cast<uint32_t>(p->threads) * p->groups * esq::kQGroup;
+    sh.n_tensors = p->n_tensors;
+    // up to eight steps per workgroup (it looks its tensor up once), as many
+    // as leave three workgroups per slot of the chip: int8 swap over the
+    // 0.5B-shaped set 557 us with one, 524, 510 and 506 with two, four and
+    // eight; fp8 update of 8 over an eighth of it 198, 195 and 204 us with
+    // one, two and four
+    const uint64_t slots = uint64_t(p->cus) * 8;
+    sh.full_steps = 1;
+    while (sh.full_steps < 8 && 2 * sh.full_steps * kQStepCodes <= sh.tile_elems &&
+           p->numel / (2 * sh.full_steps * kQStepCodes) >= 3 * slots)
+        sh.full_steps *= 2;
+    while ((sh.full_steps * kQStepCodes << sh.full_shift) < sh.tile_elems) ++sh.full_shift;
+    const StepLaunch l = step_launch(0, p->n_tail, p->tail_max, sh.tile_elems, kQStepCodes * sh.full_steps);
+    sh.tail_shift = l.shape.tail_shift;
+    sh.tail_steps = l.shape.tail_steps * sh.full_steps;
+    const uint32_t grid = static_cast<uint32_t>((p->n_full << sh.full_shift) +
+                                                (p->n_tail << sh.tail_shift));
+    hipLaunchKernelGGL(qpass_kernel(kind, p->format), dim3(grid), dim3(kStepThreads), 0, s,
+                       p->d_tab, p->n_full,
+                       reinterpret_cast<const Member*>(p->d_scratch + kOffMembers),
+                       reinterpret_cast<const UpdateHeader*>(p->d_scratch + kOffHeader), ps, sh);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "es_qpass_kernel launch");
     return ES_OK;
@@ -2249,7 +2293,7 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
         return fail(ES_ERR_INVALID_ARG, nm + ": format not ES_QFORMAT_INT8 or ES_QFORMAT_E4M3");
     int threads = env_int("ESOPT_THREADS", kDefaultThreads, 256, 1024);
     int groups = env_int("ESOPT_QGROUPS", kDefaultQGroups, 2, 8);
-    if (qpass_kernel(threads, groups, QKind::kUpdate, static_cast<int>(format)) == nullptr) {
+    if (qchecksum_kernel(threads, groups) == nullptr) {
         threads = kDefaultThreads;
         groups = kDefaultQGroups;
     }
@@ -2258,7 +2302,7 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
     std::vector<esq::DevQTensor> tab(n_tensors + 1);
     std::unordered_map<uint32_t, uint32_t> ids;
     std::vector<std::pair<uintptr_t, uintptr_t>> ranges;
-    uint64_t n_full = 0, n_tail = 0, numel = 0;
+    uint64_t n_full = 0, n_tail = 0, numel = 0, tail_max = 0;
     for (uint32_t i = 0; i < n_tensors; ++i) {
         const QSpec& t = specs[i];
         const std::string where = nm + ": " + kind + " " + std::to_string(i);
@@ -2282,6 +2326,7 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
                                  (a % 16 == 0) ? 1u : 0u, static_cast<uint32_t>(t.skip), cmagic,
                                  cshift, 0u};
         if (t.numel > 0) ranges.emplace_back(a, a + t.numel);
+        tail_max = std::max(tail_max, std::min(tile_elems, t.numel - full * tile_elems));
         n_full += full;
         n_tail += tail;
         numel += t.numel;
@@ -2313,6 +2358,7 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
     e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
     if (e != hipSuccess) { delete p; return hip_fail(e, "hipDeviceGetAttribute"); }
     const int wg = env_int("ESOPT_UPDATE_WG_PER_CU", kDefaultUpdateWgPerCu, 1, 32);
+    p->cus = cus;
     p->threads = threads;
     p->groups = groups;
     p->format = static_cast<int>(format);
@@ -2320,6 +2366,7 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
     p->numel = numel;
     p->n_full = n_full;
     p->n_tail = n_tail;
+    p->tail_max = tail_max;
     const uint64_t cap = std::max<uint64_t>(std::max(n_full, n_tail), 1);
     p->grid = static_cast<uint32_t>(std::min<uint64_t>(cap, uint64_t(cus) * wg));
     e = hipMalloc(reinterpret_cast<void**>(&p->d_tab), sizeof(esq::DevQTensor) * tab.size());
@@ -2960,7 +3007,8 @@ int es_qplan_checksum(es_qplan_t* plan, uint64_t* out_dev, es_stream_t stream) {
     if (e != hipSuccess) return hip_fail(e, "es_zero_u64_kernel launch");
     if (plan->n_full + plan->n_tail == 0) return ES_OK;
     hipLaunchKernelGGL(qchecksum_kernel(plan->threads, plan->groups), dim3(plan->grid),
-                       dim3(plan->threads), 0, s, plan->d_tab, plan->n_full, plan->n_tail, out);
+                       dim3(plan->threads), 0, s, plan->d_tab, plan->n_full, plan->n_tail,
+                       plan->n_tensors, out);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "es_qchecksum_kernel launch");
     return ES_OK;

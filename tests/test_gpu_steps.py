@@ -159,3 +159,99 @@ def test_many_tiny_tensors_and_a_long_one():
         for acc, part in zip(pooled, (got[o:o + n], exp, bits[o:o + n], d)):
             acc.append(part)
     assert_parity(report(*(np.concatenate(p) for p in pooled)), "many tiny tensors")
+
+
+# ------------------------------------------------------------ quantized plans --
+# The GPU's binary32 step is within about 1e-6 of its size of the oracle's, so
+# a code differs only where the step lands that close to a rounding threshold:
+# a few codes in 1e6 at these steps (a few quanta), by one code.
+
+QSIZES = [1, 15, 16, 17, 4095, 4096, 4097, 32768 + 3, 65536, 65536 + 4096 + 1]
+
+
+def _qbuffer(fmt, pad, sizes):
+    rng = np.random.default_rng(400 + pad)
+    offs, cur = [], 0
+    for n in sizes:
+        offs.append(cur + pad)
+        cur += -(-(pad + n + 16) // 256) * 256
+    codes = (rng.integers(-127, 128, cur).astype(np.int8) if fmt == "int8"
+             else (rng.integers(0, 2, cur) * 128 + rng.integers(0, 127, cur)).astype(np.uint8))
+    flat = torch.from_numpy(codes).cuda()
+    rows = [8 * (1 + i % 5) if i % 2 else 0 for i in range(len(sizes))]
+    scales = [rng.uniform(4e-4, 9e-4, 1 if r == 0 else -(-n // r)).astype(np.float32)
+              for r, n in zip(rows, sizes)]
+    return codes, flat, offs, rows, scales
+
+
+def _qexpected(fmt, kind, b, i, row, scales):
+    if kind == "update":
+        f = oracle.qupdate if fmt == "int8" else oracle.f8update
+        return f(b, scales, row, i, SEEDS, SIGNS, REWARDS, 5e-3, SIGMA, round_seed=9)[0]
+    perturb, restore = ((oracle.qperturb, oracle.qrestore) if fmt == "int8"
+                        else (oracle.f8perturb, oracle.f8restore))
+    if kind == "swap":
+        b = restore(b, scales, row, 4, i, 1, SIGMA)
+    return perturb(b, scales, row, 5, i, 1, SIGMA)
+
+
+def _qrun(plan, kind):
+    if kind == "update":
+        plan.update(SEEDS, SIGNS, torch.from_numpy(REWARDS).cuda(), 5e-3, round_seed=9)
+    elif kind == "swap":
+        plan.swap(4, 1, 5, 1, SIGMA)
+    else:
+        plan.perturb(5, 1, SIGMA)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("fmt", ["int8", "e4m3"])
+@pytest.mark.parametrize("kind", ["perturb", "swap", "update"])
+@pytest.mark.parametrize("pad", [0, 5])
+def test_quantized_passes_at_the_edges(fmt, kind, pad):
+    codes, flat, offs, rows, scales = _qbuffer(fmt, pad, QSIZES)
+    views = [flat[o:o + n] for o, n in zip(offs, QSIZES)]
+    with esopt.QPlan(views, [torch.from_numpy(s).cuda() for s in scales], rows,
+                     format=fmt) as plan:
+        _qrun(plan, kind)
+    got, want = flat.cpu().numpy(), codes.copy()
+    for i, (o, n) in enumerate(zip(offs, QSIZES)):
+        want[o:o + n] = _qexpected(fmt, kind, codes[o:o + n], i, rows[i], scales[i])
+    assert np.mean(got != want) <= 5e-5, np.mean(got != want)
+    near = got != want
+    assert np.all(np.abs(got[near].astype(int) - want[near].astype(int)) <= 1)
+    assert np.mean(got != codes) > 0.3
+
+
+@pytest.mark.parametrize("n_tensors", [1, 64, 65, 5000])
+def test_quantized_lookup_over_many_tensors(n_tensors):
+    """The tensor of a workgroup's tile is found 64 table entries at a time."""
+    sizes = [33 + 16 * (i % 3) for i in range(n_tensors - 1)] + [70_001]
+    codes, flat, offs, rows, scales = _qbuffer("int8", 0, sizes)
+    views = [flat[o:o + n] for o, n in zip(offs, sizes)]
+    with esopt.QPlan(views, [torch.from_numpy(s).cuda() for s in scales], rows) as plan:
+        _qrun(plan, "perturb")
+    got = flat.cpu().numpy()
+    for i in sorted({0, 1, 62, 63, 64, 4095, 4096, n_tensors - 2, n_tensors - 1}):
+        if 0 <= i < n_tensors:
+            o, n = offs[i], sizes[i]
+            want = _qexpected("int8", "perturb", codes[o:o + n], i, rows[i], scales[i])
+            assert np.mean(got[o:o + n] != want) <= 5e-5, i
+
+
+@pytest.mark.parametrize("sigma", [1e6, 1e30])
+def test_int8_steps_beyond_every_code(sigma):
+    """Steps of up to 1e38 quanta and beyond clamp to the end they point to,
+    and a restore of them to the other."""
+    codes, flat, offs, rows, scales = _qbuffer("int8", 0, [5000])
+    s = np.full_like(scales[0], 1e-30 if sigma > 1e20 else 1e-4)
+    with esopt.QPlan([flat[:5000]], [torch.from_numpy(s).cuda()], [0]) as plan:
+        plan.perturb(3, 1, sigma)
+        torch.cuda.synchronize()
+        up = flat[:5000].cpu().numpy()
+        # every such step saturates, so the signs of smaller ones say where
+        want = oracle.qperturb(codes[:5000], np.full_like(s, 1e-4), 0, 3, 0, 1, 1e6)
+        assert np.array_equal(up, want) and set(np.unique(np.abs(up))) == {127}
+        plan.restore(3, 1, sigma)
+        torch.cuda.synchronize()
+        assert np.array_equal(flat[:5000].cpu().numpy(), -want)
