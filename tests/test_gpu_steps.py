@@ -255,3 +255,30 @@ def test_int8_steps_beyond_every_code(sigma):
         plan.restore(3, 1, sigma)
         torch.cuda.synchronize()
         assert np.array_equal(flat[:5000].cpu().numpy(), -want)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 128, 129, 1024])
+def test_populations_at_the_table_limits(n):
+    """Up to 128 members the tables travel in the kernel arguments, above that
+    through the scratch; seeds repeat out of order, with both signs."""
+    rng = np.random.default_rng(n)
+    pool = rng.integers(0, 1 << 63, max(1, n // 2))
+    seeds = [int(x) for x in rng.choice(pool, n)]
+    signs = [int(x) for x in rng.choice([-1, 1], n)]
+    r = rng.standard_normal(n).astype(np.float32)
+    bits = wl.random_bf16_bits(777, 5)
+    t = to_device(bits)
+    z = torch.full((n,), float("nan"), device="cuda")
+    st = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    flags = esopt.ES_REWARDS_ARE_WEIGHTS if n == 1 else 0
+    with esopt.Plan([t]) as plan:
+        plan.update(seeds, signs, torch.from_numpy(r).cuda(), ALPHA, flags=flags, z_out=z,
+                    status_out=st)
+        torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    np.testing.assert_allclose(z.cpu().numpy(), r if flags else oracle.zscore(r)[0], rtol=1e-6,
+                               atol=1e-7)
+    exp, _ = oracle.update(bits, 0, seeds, signs, r, ALPHA, SIGMA, flags=flags)
+    rep = report(to_host(t), exp, bits,
+                 update_delta(0, seeds, signs, r, ALPHA, SIGMA, flags, np.arange(777, dtype=np.uint64)))
+    assert_parity(rep, f"population of {n}")
