@@ -826,11 +826,29 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
     constexpr int kIn = kMaster != 0 ? 8 : 4;            // words of a group's input
     const uint32_t q_hi = tile_high_word<kRows>(r);
     const uint32_t g_hi = q_hi >> 1;                     // index >> 35
+    // the masters of a full tile are taken in quads, lane t those at 4 t of
+    // each 1024 elements, so that a 16-byte access covers 1 KB of consecutive
+    // masters per wave (as in es_apply_master_kernel): with the member applied
+    // first, 0.5B-shaped set, 1426 us by groups and 1385 by quads
+    constexpr bool kQuads = kFast && kMaster != 0;
+    constexpr uint32_t kQuadSlab = kStepThreads * 4;
+    const uint64_t e4 = e - threadIdx.x * 4u;
     uint64_t eg[2], n[2];
     bool in[2];
     uint32_t raw[2][kIn];
+    if constexpr (kQuads) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f32x4_t v = __builtin_nontemporal_load(
+                (const ES_GLOBAL f32x4_t*)(mb + 4 * (e4 + i * kQuadSlab)));
+            uint32_t* x = raw[i / 2] + 4 * (i % 2);
+            x[0] = __float_as_uint(v.x); x[1] = __float_as_uint(v.y);
+            x[2] = __float_as_uint(v.z); x[3] = __float_as_uint(v.w);
+        }
+    }
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
+        if constexpr (kQuads) break;
         eg[g] = e + uint64_t(g) * (kStepThreads * kGroupElems);
         in[g] = kFast || eg[g] < r.limit;
         n[g] = noise_index<kRows>(r, eg[g]);
@@ -849,7 +867,13 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
         }
     }
     uint32_t q[4];
-    pair_quads(n, q);
+    if constexpr (kQuads) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            q[i] = static_cast<uint32_t>(noise_index<kRows>(r, e4 + i * kQuadSlab) >> 2);
+    } else {
+        pair_quads(n, q);
+    }
     float acc[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k)
@@ -877,8 +901,29 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
         }
         pair_axpy(rad, c, sn, m.w_k, acc);
     }
+    if constexpr (kQuads) {
+        typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t* x = raw[i / 2] + 4 * (i % 2);
+            float m[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                m[k] = kMaster == 2 ? acc[4 * i + k] : __uint_as_float(x[k]);
+                if (kMaster == 1 && add) m[k] += acc[4 * i + k];
+            }
+            if (kMaster == 1 && add) {
+                const f32x4_t v = {m[0], m[1], m[2], m[3]};
+                __builtin_nontemporal_store(v, (ES_GLOBAL f32x4_t*)(mb + 4 * (e4 + i * kQuadSlab)));
+            }
+            const u32x2_t b = {es::pack_bf16x2(m[0], m[1]), es::pack_bf16x2(m[2], m[3])};
+            __builtin_nontemporal_store(b, (ES_GLOBAL u32x2_t*)(r.data + e4 + i * kQuadSlab));
+        }
+        return;
+    }
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
+        if constexpr (kQuads) break;
         if (!in[g]) break;
         const float* a = acc + 8 * g;
         uint32_t out[4];
