@@ -684,17 +684,23 @@ __device__ __forceinline__ void add_workgroup_sum(uint64_t acc, unsigned long lo
 // bf16 plan: full tiles with 16-byte loads and no per-element bound, then
 // tail tiles bounds-checked.  With kRows (tiles of strided blocks) each
 // term takes the element's whole-tensor index from the tile's row map.
-template <int kThreads, int kU, bool kRows>
+// kCut: a small plan's tiles are cut into 2^shift items each, since its few
+// tiles would keep as few CUs at eight group slots in a row (with the slots of
+// an item known to the compiler otherwise: 1 % on large plans).
+template <int kThreads, int kU, bool kRows, bool kCut>
 __global__ __launch_bounds__(kThreads) void es_checksum_kernel(const DevTile* __restrict__ tiles,
                                                                uint64_t n_full, uint64_t n_tail,
                                                                const DevRows* __restrict__ rows,
+                                                               uint32_t shift,
                                                                unsigned long long* __restrict__ out) {
     uint64_t acc = 0;
-    for (uint64_t tile = blockIdx.x; tile < n_full; tile += gridDim.x) {
-        const TileRef r = load_ref<kRows>(tiles, rows, tile);
+    const uint32_t cut = kCut ? shift : 0u, slots = kU >> cut, parts = (1u << cut) - 1u;
+    for (uint64_t i = blockIdx.x; i < n_full << cut; i += gridDim.x) {
+        const TileRef r = load_ref<kRows>(tiles, rows, i >> cut);
+        const uint32_t u0 = (static_cast<uint32_t>(i) & parts) * slots;
         const uint64_t salt = uint64_t(r.tensor_id) * kSumT;
 #pragma unroll 1
-        for (int u = 0; u < kU; ++u) {
+        for (uint32_t u = u0; u < u0 + slots; ++u) {
             const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
             uint32_t raw[4];
             load_group<true, true>(r.data, e, r.limit, raw);
@@ -702,11 +708,12 @@ __global__ __launch_bounds__(kThreads) void es_checksum_kernel(const DevTile* __
                                                           salt);
         }
     }
-    for (uint64_t tl = blockIdx.x; tl < n_tail; tl += gridDim.x) {
-        const TileRef r = load_ref<kRows>(tiles, rows, n_full + tl);
+    for (uint64_t i = blockIdx.x; i < n_tail << cut; i += gridDim.x) {
+        const TileRef r = load_ref<kRows>(tiles, rows, n_full + (i >> cut));
+        const uint32_t u0 = (static_cast<uint32_t>(i) & parts) * slots;
         const uint64_t salt = uint64_t(r.tensor_id) * kSumT;
 #pragma unroll 1
-        for (int u = 0; u < kU; ++u) {
+        for (uint32_t u = u0; u < u0 + slots; ++u) {
             const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
             if (e >= r.limit) break;
             uint32_t raw[4];
@@ -1186,13 +1193,16 @@ ApplyMasterKernel apply_master_kernel(bool rows) {
 // Tile shapes instantiated: T lanes per workgroup x U groups per lane.
 #define ES_TILE_SHAPES(X) X(256, 4) X(256, 8) X(512, 4) X(512, 8) X(1024, 4) X(1024, 8)
 
-using ChecksumKernel = void (*)(const DevTile*, uint64_t, uint64_t, const DevRows*,
+using ChecksumKernel = void (*)(const DevTile*, uint64_t, uint64_t, const DevRows*, uint32_t,
                                 unsigned long long*);
 
-ChecksumKernel checksum_kernel(int threads, int groups, bool rows) {
-#define ES_CASE(T, U)                                                                     \
-    if (threads == T && groups == U)                                                      \
-        return rows ? es_checksum_kernel<T, U, true> : es_checksum_kernel<T, U, false>;
+ChecksumKernel checksum_kernel(int threads, int groups, bool rows, bool cut) {
+#define ES_CASE(T, U)                                                                   \
+    if (threads == T && groups == U)                                                    \
+        return rows ? (cut ? es_checksum_kernel<T, U, true, true>                       \
+                           : es_checksum_kernel<T, U, true, false>)                     \
+                    : (cut ? es_checksum_kernel<T, U, false, true>                      \
+                           : es_checksum_kernel<T, U, false, false>);
     ES_TILE_SHAPES(ES_CASE)
 #undef ES_CASE
     return nullptr;
@@ -1483,29 +1493,32 @@ QPassKernel qpass_kernel(QKind kind, int format) {
 // Quantized plan: the same sum with b the code's 8 bits and j the element's
 // whole-tensor index (qnoise_index; a 16-code group's indices are
 // consecutive).
-template <int kThreads, int kU>
+template <int kThreads, int kU, bool kCut>
 __global__ __launch_bounds__(kThreads) void es_qchecksum_kernel(
     const esq::DevQTensor* __restrict__ tab, uint64_t n_full, uint64_t n_tail, uint32_t n_tensors,
-    unsigned long long* __restrict__ out) {
+    uint32_t shift, unsigned long long* __restrict__ out) {
     constexpr uint32_t kTileElems = uint32_t(kThreads) * kU * esq::kQGroup;
+    const uint32_t cut = kCut ? shift : 0u, slots = kU >> cut, parts = (1u << cut) - 1u;
     uint64_t acc = 0;
-    for (uint64_t tile = blockIdx.x; tile < n_full; tile += gridDim.x) {
-        const esq::QTileRef r = esq::qlocate_full(tab, n_tensors, tile, kTileElems);
+    for (uint64_t i = blockIdx.x; i < n_full << cut; i += gridDim.x) {
+        const esq::QTileRef r = esq::qlocate_full(tab, n_tensors, i >> cut, kTileElems);
+        const uint32_t u0 = (static_cast<uint32_t>(i) & parts) * slots;
         const uint64_t salt = uint64_t(r.tensor_id) * kSumT;
 #pragma unroll 1
-        for (int u = 0; u < kU; ++u) {
-            const uint32_t e = r.elem0 + (uint32_t(u) * kThreads + threadIdx.x) * esq::kQGroup;
+        for (uint32_t u = u0; u < u0 + slots; ++u) {
+            const uint32_t e = r.elem0 + (u * kThreads + threadIdx.x) * esq::kQGroup;
             uint32_t raw[4];
             esq::qload<true>(r.data, e, r.numel, raw);
             acc += checksum_terms<esq::kQGroup, 8, false>(raw, esq::qnoise_index(r, e), 0, salt);
         }
     }
-    for (uint64_t tile = blockIdx.x; tile < n_tail; tile += gridDim.x) {
-        const esq::QTileRef r = esq::qlocate_tail(tab, n_tensors, tile, kTileElems);
+    for (uint64_t i = blockIdx.x; i < n_tail << cut; i += gridDim.x) {
+        const esq::QTileRef r = esq::qlocate_tail(tab, n_tensors, i >> cut, kTileElems);
+        const uint32_t u0 = (static_cast<uint32_t>(i) & parts) * slots;
         const uint64_t salt = uint64_t(r.tensor_id) * kSumT;
 #pragma unroll 1
-        for (int u = 0; u < kU; ++u) {
-            const uint32_t e = r.elem0 + (uint32_t(u) * kThreads + threadIdx.x) * esq::kQGroup;
+        for (uint32_t u = u0; u < u0 + slots; ++u) {
+            const uint32_t e = r.elem0 + (u * kThreads + threadIdx.x) * esq::kQGroup;
             if (e >= r.numel) break;
             uint32_t raw[4];
             esq::qload<false>(r.data, e, r.numel, raw);
@@ -1517,11 +1530,13 @@ __global__ __launch_bounds__(kThreads) void es_qchecksum_kernel(
     add_workgroup_sum<kThreads>(acc, out);
 }
 
-using QChecksumKernel = void (*)(const esq::DevQTensor*, uint64_t, uint64_t, uint32_t,
+using QChecksumKernel = void (*)(const esq::DevQTensor*, uint64_t, uint64_t, uint32_t, uint32_t,
                                  unsigned long long*);
 
-QChecksumKernel qchecksum_kernel(int threads, int groups) {
-#define ES_CASE(T, U) if (threads == T && groups == U) return es_qchecksum_kernel<T, U>;
+QChecksumKernel qchecksum_kernel(int threads, int groups, bool cut) {
+#define ES_CASE(T, U)                                                                   \
+    if (threads == T && groups == U)                                                    \
+        return cut ? es_qchecksum_kernel<T, U, true> : es_qchecksum_kernel<T, U, false>;
     ES_TILE_SHAPES(ES_CASE)
 #undef ES_CASE
     return nullptr;
@@ -1655,6 +1670,23 @@ StepLaunch plan_steps(const es_plan_t* p, const Segment& g, int groups) {
 bool four_groups(const es_plan_t* p, const Segment& g) {
     const uint64_t elems = g.n_full * p->tile_elems + g.n_tail * g.tail_max;
     return elems >= uint64_t(p->cus) * 8 * (kStepThreads * 4 * kGroupElems);
+}
+
+// A checksum launch: tiles cut in halves down to single group slots while that
+// gives at most kSumItems workgroups, each with one atomic on the result, else
+// whole tiles over `grid` workgroups.  1 M parameters: 29 us whole, 14 in
+// slots; 24 M in 200 odd-sized tensors 46 whole, 34 in halves (800 workgroups),
+// 54 in slots (3600); 60 M in 216 (1800 halves) stay whole, 51 us.
+struct SumLaunch {
+    uint32_t shift, grid;
+};
+SumLaunch sum_launch(uint64_t n_full, uint64_t n_tail, int groups, uint32_t grid) {
+    constexpr uint64_t kSumItems = 1024;
+    const uint64_t tiles = std::max<uint64_t>(std::max(n_full, n_tail), 1);
+    SumLaunch l{0u, grid};
+    while ((2 << l.shift) <= groups && (tiles << (l.shift + 1)) <= kSumItems) ++l.shift;
+    if (l.shift > 0) l.grid = static_cast<uint32_t>(tiles << l.shift);
+    return l;
 }
 
 // One pass of the perturb kernel: streams = 1 (seed[0], coef[0]), 2 (two
@@ -1853,7 +1885,7 @@ void row_divisor(uint32_t r, uint32_t& magic, uint32_t& shift) {
 void launch_shape(int& threads, int& groups) {
     threads = env_int("ESOPT_THREADS", kDefaultThreads, 256, 1024);
     groups = env_int("ESOPT_GROUPS", kDefaultGroups, 2, 8);
-    if (checksum_kernel(threads, groups, false) == nullptr) {
+    if (checksum_kernel(threads, groups, false, false) == nullptr) {
         threads = kDefaultThreads;
         groups = kDefaultGroups;
     }
@@ -2379,7 +2411,7 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
         return fail(ES_ERR_INVALID_ARG, nm + ": format not ES_QFORMAT_INT8 or ES_QFORMAT_E4M3");
     int threads = env_int("ESOPT_THREADS", kDefaultThreads, 256, 1024);
     int groups = env_int("ESOPT_QGROUPS", kDefaultQGroups, 2, 8);
-    if (qchecksum_kernel(threads, groups) == nullptr) {
+    if (qchecksum_kernel(threads, groups, false) == nullptr) {
         threads = kDefaultThreads;
         groups = kDefaultQGroups;
     }
@@ -3069,9 +3101,11 @@ int es_plan_checksum(es_plan_t* plan, uint64_t* out_dev, es_stream_t stream) {
     const int n_seg = plan_segments(plan, seg);
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
-        hipLaunchKernelGGL(checksum_kernel(plan->threads, plan->groups, g.rows != nullptr),
-                           dim3(g.grid_sum), dim3(plan->threads), 0, s, g.tiles, g.n_full,
-                           g.n_tail, g.rows, out);
+        const SumLaunch l = sum_launch(g.n_full, g.n_tail, plan->groups, g.grid_sum);
+        hipLaunchKernelGGL(checksum_kernel(plan->threads, plan->groups, g.rows != nullptr,
+                                           l.shift > 0),
+                           dim3(l.grid), dim3(plan->threads), 0, s, g.tiles, g.n_full, g.n_tail,
+                           g.rows, l.shift, out);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "es_checksum_kernel launch");
     }
@@ -3092,9 +3126,10 @@ int es_qplan_checksum(es_qplan_t* plan, uint64_t* out_dev, es_stream_t stream) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "es_zero_u64_kernel launch");
     if (plan->n_full + plan->n_tail == 0) return ES_OK;
-    hipLaunchKernelGGL(qchecksum_kernel(plan->threads, plan->groups), dim3(plan->grid),
+    const SumLaunch l = sum_launch(plan->n_full, plan->n_tail, plan->groups, plan->grid);
+    hipLaunchKernelGGL(qchecksum_kernel(plan->threads, plan->groups, l.shift > 0), dim3(l.grid),
                        dim3(plan->threads), 0, s, plan->d_tab, plan->n_full, plan->n_tail,
-                       plan->n_tensors, out);
+                       plan->n_tensors, l.shift, out);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "es_qchecksum_kernel launch");
     return ES_OK;

@@ -282,3 +282,22 @@ def test_populations_at_the_table_limits(n):
     rep = report(to_host(t), exp, bits,
                  update_delta(0, seeds, signs, r, ALPHA, SIGMA, flags, np.arange(777, dtype=np.uint64)))
     assert_parity(rep, f"population of {n}")
+
+
+def test_checksum_of_a_plan_of_whole_tiles_is_its_parts():
+    """40 M elements run whole tiles over the grid, an eighth of them tiles cut
+    in eighths or halves; the parts' checksums add up to the whole's, and the
+    last part's is the oracle's."""
+    n = 40_000_000 + 24
+    bits = wl.random_bf16_bits(n, 8)
+    t = to_device(bits)
+    cuts = [0, 8 * 60_000, 8 * 700_000, 8 * 2_400_000, n - 100_003 - (n - 100_003) % 8, n]
+    with esopt.Plan([t], tensor_ids=[3]) as plan:
+        whole = plan.checksum()
+    total = 0
+    for a, b in zip(cuts, cuts[1:]):
+        with esopt.Plan([t[a:b]], tensor_ids=[3], offsets=[a]) as part:
+            last = part.checksum()
+            total += last
+    assert whole == total % (1 << 64)
+    assert last == oracle.plan_checksum([(bits[cuts[-2]:], 3, cuts[-2])])
