@@ -26,8 +26,8 @@
 //   * The passes run in 256-lane workgroups of one step each (StepShape): two
 //     or four 8-element groups per lane, loaded in one burst and stored in
 //     one, dispatched in the order of the plan's memory.  Perturb is
-//     HBM-bound: 0.5B-shaped set, perturb and restore, 677 -> 603 us (5.70 ->
-//     6.41 TB/s), against one 1024-lane workgroup per CU that strode over the
+//     HBM-bound: 0.5B-shaped set, perturb and restore, 678 -> 610 us (5.70 ->
+//     6.33 TB/s), against one 1024-lane workgroup per CU that strode over the
 //     tiles with its next tile's loads in flight.  The update is VALU-bound
 //     (N noise streams per element): two groups per lane, so that four Philox
 //     blocks run in lockstep (es_noise.hpp) and six or seven waves per SIMD
@@ -77,13 +77,12 @@ namespace {
 
 constexpr int kAuxBlock = 256;              // lanes per workgroup of the small kernels
 constexpr int kGroupElems = 8;              // bf16 per lane-group (one 16-byte access)
-// Default tile shape and grids (measured on MI355X; see the launch-shape
-// notes above).  The update is VALU-bound and wants every wave slot filled;
-// perturb is HBM-bound and wants large contiguous per-CU streams.
+constexpr int kStepThreads = 256;           // lanes per workgroup of the step kernels
+// Default tile shape of a plan, and the lanes per workgroup and workgroups per
+// CU of the checksum kernels, which stride over whole tiles.
 constexpr int kDefaultThreads = 1024;
 constexpr int kDefaultGroups = 8;
 constexpr int kDefaultUpdateWgPerCu = 8;
-constexpr int kStepThreads = 256;           // lanes per workgroup of the step kernels
 constexpr int kDefaultQGroups = 4;          // int8 tiles: 1024 x 4 x 16 codes (64 KB)
 constexpr double kSqrt2Ln2Double = 1.1774100225154746910;   // sqrt(2 ln 2)
 
@@ -1664,9 +1663,10 @@ StepLaunch plan_steps(const es_plan_t* p, const Segment& g, int groups) {
 }
 
 // Groups per lane and step of the memory-bound passes: four, or two where
-// four would leave wave slots empty (fewer than eight workgroups per CU).
-// Perturb and restore over 1 M parameters: 2 x 4.9 us with two; over the
-// 0.5B-shaped set 603 us with four, 618 with two, 686 with eight.
+// four would leave wave slots empty (fewer than eight workgroups per CU, 16.8 M
+// elements).  A perturb pass in a graph, two and four groups: 1 M elements 2.8
+// and 3.4 us, 8.4 M 7.7 and 8.0, 16.8 M 12.2 and 12.0, 134 M 85.1 and 83.7, 537
+// M 346 and 332.
 bool four_groups(const es_plan_t* p, const Segment& g) {
     const uint64_t elems = g.n_full * p->tile_elems + g.n_tail * g.tail_max;
     return elems >= uint64_t(p->cus) * 8 * (kStepThreads * 4 * kGroupElems);
