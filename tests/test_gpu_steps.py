@@ -301,3 +301,16 @@ def test_checksum_of_a_plan_of_whole_tiles_is_its_parts():
             total += last
     assert whole == total % (1 << 64)
     assert last == oracle.plan_checksum([(bits[cuts[-2]:], 3, cuts[-2])])
+
+
+def test_every_element_of_many_steps_is_passed_over_once():
+    """17 M zeros perturbed once hold sigma times their normals: the steps'
+    order over the XCDs leaves none out and takes none twice.  A bf16 value is
+    within 2^-9 of what it rounds, relatively."""
+    n = 17_000_000
+    t = torch.zeros(n, dtype=torch.bfloat16, device="cuda")
+    with esopt.Plan([t], tensor_ids=[6]) as plan:
+        plan.perturb(21, 1, SIGMA)
+    eps = esopt.normals(21, 6, 0, n)
+    torch.cuda.synchronize()
+    assert bool(((t.float() - SIGMA * eps).abs() <= 2.1e-3 * SIGMA * eps.abs() + 1e-9).all())
