@@ -305,12 +305,14 @@ def test_checksum_of_a_plan_of_whole_tiles_is_its_parts():
 
 def test_every_element_of_many_steps_is_passed_over_once():
     """17 M zeros perturbed once hold sigma times their normals: the steps'
-    order over the XCDs leaves none out and takes none twice.  A bf16 value is
-    within 2^-9 of what it rounds, relatively."""
+    order over the XCDs leaves none out and takes none twice.  bf16 carries 8
+    significant bits, so a nearest-even value is within 2^-8 = 3.91e-3 of what it
+    rounds, relatively (an element left out is off by 1, one taken twice too); the
+    binary32 products add under 1e-6."""
     n = 17_000_000
     t = torch.zeros(n, dtype=torch.bfloat16, device="cuda")
     with esopt.Plan([t], tensor_ids=[6]) as plan:
         plan.perturb(21, 1, SIGMA)
     eps = esopt.normals(21, 6, 0, n)
     torch.cuda.synchronize()
-    assert bool(((t.float() - SIGMA * eps).abs() <= 2.1e-3 * SIGMA * eps.abs() + 1e-9).all())
+    assert bool(((t.float() - SIGMA * eps).abs() <= 3.92e-3 * SIGMA * eps.abs() + 1e-9).all())
