@@ -688,7 +688,7 @@ def main():
                                      else median_s(per_sw["es_restore_update"]))}
 
     # the practical in-place streaming ceiling over the same memory: the same
-    # tiles and launch, loads and stores only, not pipelined (es_stream_pass),
+    # tiles and launch, loads and stores only (es_stream_pass),
     # timed after the steps; then the flat-buffer read / write / in-place rates
     plan.stream_pass()
     log.ev = []
@@ -793,7 +793,7 @@ def main():
             "ms_per_step": round(swap["ms_step"], 3),
             "speedup_vs_perturb_restore": round(ms_step / swap["ms_step"], 4),
             "wall_s_timed": round(swap["wall"], 3),
-            "roofline": valu_roofline(c_swap, t_sw, "es_perturb_kernel<..., 2> (es_swap, two keys)",
+            "roofline": valu_roofline(c_swap, t_sw, "es_perturb_kernel<2, ...> (es_swap, two keys)",
                                       True)}
     if cpu is not None:
         out["cpu_baseline"] = cpu
