@@ -446,6 +446,26 @@ __host__ __device__ __forceinline__ uint64_t xcd_run_item(uint64_t i) {
     return (j / kXcdRun) * (kXcds * kXcdRun) + (i % kXcds) * kXcdRun + j % kXcdRun;
 }
 
+// What workgroup i of a step launch over n_full full tiles and the tail tiles
+// behind them takes: part `part` of tile `tile`.  The host tests call this same
+// function.
+struct StepItem {
+    bool full;
+    uint32_t part;
+    uint64_t tile;
+};
+__host__ __device__ __forceinline__ StepItem step_item(uint64_t i, uint64_t n_full,
+                                                       const StepShape& sh) {
+    const uint64_t full_items = n_full << sh.full_shift;
+    if (i < (full_items & ~uint64_t(kXcds * kXcdRun - 1))) i = xcd_run_item(i);
+    if (i < full_items)
+        return StepItem{true, static_cast<uint32_t>(i) & ((1u << sh.full_shift) - 1u),
+                        i >> sh.full_shift};
+    const uint64_t j = i - full_items;
+    return StepItem{false, static_cast<uint32_t>(j) & ((1u << sh.tail_shift) - 1u),
+                    n_full + (j >> sh.tail_shift)};
+}
+
 // The step (or steps) of this workgroup: step(full, tile reference, tile
 // number, the lane's first element); its group g starts 8 kStepThreads g
 // elements on.  For a tail tile the first group starts below the bound (lanes
@@ -455,27 +475,19 @@ __device__ __forceinline__ void for_steps(const DevTile* __restrict__ tiles, uin
                                           const DevRows* __restrict__ rows, const StepShape& sh,
                                           Step step) {
     constexpr uint32_t kElems = kStepThreads * kG * kGroupElems;
-    const uint64_t full_items = n_full << sh.full_shift;
-    uint64_t i = blockIdx.x;
-    if (i < (full_items & ~uint64_t(kXcds * kXcdRun - 1))) i = xcd_run_item(i);
-    if (i < full_items) {
-        const uint64_t tile = i >> sh.full_shift;
-        const uint32_t part = static_cast<uint32_t>(i) & ((1u << sh.full_shift) - 1u);
-        const TileRef r = load_ref<kRows>(tiles, rows, tile);
-        step(std::true_type{}, r, tile,
-             r.elem0 + part * kElems + threadIdx.x * uint32_t(kGroupElems));
+    const StepItem it = step_item(blockIdx.x, n_full, sh);
+    const TileRef r = load_ref<kRows>(tiles, rows, it.tile);
+    if (it.full) {
+        step(std::true_type{}, r, it.tile,
+             r.elem0 + it.part * kElems + threadIdx.x * uint32_t(kGroupElems));
         return;
     }
-    const uint64_t j = i - full_items;
-    const uint64_t tile = n_full + (j >> sh.tail_shift);
-    const uint32_t part = static_cast<uint32_t>(j) & ((1u << sh.tail_shift) - 1u);
-    const TileRef r = load_ref<kRows>(tiles, rows, tile);
 #pragma unroll 1
     for (uint32_t k = 0; k < sh.tail_steps; ++k) {
-        const uint64_t e = r.elem0 + uint64_t(part * sh.tail_steps + k) * kElems +
+        const uint64_t e = r.elem0 + uint64_t(it.part * sh.tail_steps + k) * kElems +
                            threadIdx.x * uint32_t(kGroupElems);
         if (e >= r.limit) return;
-        step(std::false_type{}, r, tile, e);
+        step(std::false_type{}, r, it.tile, e);
     }
 }
 
@@ -1442,10 +1454,12 @@ __device__ __forceinline__ void qstep_group(const esq::QTileRef& r, uint32_t e,
 // of domain 1 under the rounding seed).  A workgroup takes full_steps (tail_
 // steps) steps of 256 lanes x 16 codes of one tile of tile_elems codes,
 // 2^full_shift (2^tail_shift) workgroups per tile.
+// first_full and first_tail are the launch's first full and tail tile.
 struct QShape {
     uint32_t tile_elems, n_tensors;
     uint32_t full_shift, full_steps;
     uint32_t tail_shift, tail_steps;
+    uint64_t first_full, first_tail;
 };
 constexpr uint32_t kQStepCodes = kStepThreads * esq::kQGroup;
 
@@ -1462,8 +1476,8 @@ __global__ __launch_bounds__(kStepThreads) void es_qpass_kernel(
     const uint64_t i = blockIdx.x;
     if (i < full_items) {
         const uint32_t part = static_cast<uint32_t>(i) & ((1u << sh.full_shift) - 1u);
-        const esq::QTileRef r = esq::qlocate_full(tab, sh.n_tensors, i >> sh.full_shift,
-                                                  sh.tile_elems);
+        const esq::QTileRef r = esq::qlocate_full(
+            tab, sh.n_tensors, sh.first_full + (i >> sh.full_shift), sh.tile_elems);
         const uint32_t e0 = r.elem0 + part * sh.full_steps * kQStepCodes +
                             threadIdx.x * esq::kQGroup;
 #pragma unroll 1
@@ -1473,8 +1487,8 @@ __global__ __launch_bounds__(kStepThreads) void es_qpass_kernel(
     }
     const uint64_t j = i - full_items;
     const uint32_t part = static_cast<uint32_t>(j) & ((1u << sh.tail_shift) - 1u);
-    const esq::QTileRef r = esq::qlocate_tail(tab, sh.n_tensors, j >> sh.tail_shift,
-                                              sh.tile_elems);
+    const esq::QTileRef r = esq::qlocate_tail(
+        tab, sh.n_tensors, sh.first_tail + (j >> sh.tail_shift), sh.tile_elems);
     const uint32_t e0 = r.elem0 + part * sh.tail_steps * kQStepCodes + threadIdx.x * esq::kQGroup;
     const uint32_t end = min(r.numel - r.elem0, sh.tile_elems) + r.elem0;   // the tile's
 #pragma unroll 1
@@ -1646,19 +1660,14 @@ int plan_segments(const es_plan_t* p, Segment seg[2]) {
     return n;
 }
 
-// The step launch over n_full full tiles of tile_elems elements (a power of
-// two, at least 8192) and n_tail tail tiles of at most tail_max, with steps of
-// step_elems elements.  A tail tile is cut for the longest one; where there are
+// The steps of a plan's tiles of tile_elems elements (a power of two, at least
+// 8192) and its n_tail tail tiles of at most tail_max, with steps of step_elems
+// elements.  A tail tile is cut for the longest one; where there are
 // so many of them (tens of thousands of tiny tensors) that they fill the chip
 // several times over, they are cut less and a workgroup goes on to the next
 // step instead, since the empty workgroups of the short ones only cost.
-struct StepLaunch {
-    StepShape shape;
-    uint32_t grid;
-};
-
-StepLaunch step_launch(uint64_t n_full, uint64_t n_tail, uint64_t tail_max, uint64_t tile_elems,
-                       uint64_t step_elems) {
+StepShape step_shape(uint64_t n_tail, uint64_t tail_max, uint64_t tile_elems,
+                     uint64_t step_elems) {
     constexpr uint64_t kManyTails = 65536;
     StepShape sh{};
     while ((step_elems << sh.full_shift) < tile_elems) ++sh.full_shift;
@@ -1666,13 +1675,56 @@ StepLaunch step_launch(uint64_t n_full, uint64_t n_tail, uint64_t tail_max, uint
         ++sh.tail_shift;
     const uint64_t part = step_elems << sh.tail_shift;
     sh.tail_steps = static_cast<uint32_t>(std::max<uint64_t>((tail_max + part - 1) / part, 1));
-    return StepLaunch{sh, static_cast<uint32_t>((n_full << sh.full_shift) +
-                                                (n_tail << sh.tail_shift))};
+    return sh;
 }
 
-StepLaunch plan_steps(const es_plan_t* p, const Segment& g, int groups) {
-    return step_launch(g.n_full, g.n_tail, g.tail_max, p->tile_elems,
-                       uint64_t(kStepThreads) * groups * kGroupElems);
+StepShape plan_steps(const es_plan_t* p, const Segment& g, int groups) {
+    return step_shape(g.n_tail, g.tail_max, p->tile_elems,
+                      uint64_t(kStepThreads) * groups * kGroupElems);
+}
+
+// The launches of a pass of one-step workgroups, in order: of n_full full tiles
+// in 2^full_shift workgroups each, then of n_tail tail tiles in 2^tail_shift
+// each.  A launch has fewer than 2^32 lanes (HIP's limit for a dimension), and a
+// plan's memory can hold more steps than that (an update from 2^36 elements,
+// 137 GB, on), so a pass over a larger plan is several launches over
+// consecutive tiles: launch(first tile, full tiles among its tiles, workgroups)
+// for each, until one fails.  `cap` (at least a tile's workgroups) is the most
+// of them in a launch.
+constexpr uint64_t kMaxStepGrid = (uint64_t(1) << 32) / kStepThreads - 1;
+
+template <class Launch>
+int for_step_launches(uint64_t n_full, uint64_t n_tail, uint32_t full_shift, uint32_t tail_shift,
+                      Launch launch, uint64_t cap = kMaxStepGrid) {
+    uint64_t f = 0, t = 0;
+    while (f < n_full || t < n_tail) {
+        const uint64_t full = std::min(n_full - f, cap >> full_shift);
+        const uint64_t room = f + full < n_full ? 0 : cap - (full << full_shift);
+        const uint64_t tail = std::min(n_tail - t, room >> tail_shift);
+        const int rc = launch(f + t, full, static_cast<uint32_t>((full << full_shift) +
+                                                                 (tail << tail_shift)));
+        if (rc != ES_OK) return rc;
+        f += full;
+        t += tail;
+    }
+    return ES_OK;
+}
+
+// The same over a segment of a plan, with that part of its tiles, row maps and
+// master deltas (each null where the pass takes none): launch(tiles, full tiles,
+// row maps, deltas, workgroups).  A launch that fails is named by the call and
+// the kernel (formatted only then).
+template <class Launch>
+int launch_steps(const Segment& g, const StepShape& sh, const uint64_t* mdelta, const char* call,
+                 const char* kernel, Launch launch) {
+    return for_step_launches(
+        g.n_full, g.n_tail, sh.full_shift, sh.tail_shift,
+        [&](uint64_t first, uint64_t full, uint32_t grid) {
+            launch(g.tiles + first, full, g.rows != nullptr ? g.rows + first : nullptr,
+                   mdelta != nullptr ? mdelta + first : nullptr, grid);
+            const hipError_t e = hipGetLastError();
+            return e != hipSuccess ? hip_fail(e, std::string(call) + kernel + " launch") : ES_OK;
+        });
 }
 
 // Groups per lane and step of the memory-bound passes: four, or two where
@@ -1719,14 +1771,18 @@ int launch_streams(es_plan_t* p, int streams, const uint64_t* seed, const double
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
         const bool four = four_groups(p, g);
-        const StepLaunch l = plan_steps(p, g, four ? 4 : 2);
+        const StepShape sh = plan_steps(p, g, four ? 4 : 2);
         const bool strided = g.rows != nullptr;
-        hipLaunchKernelGGL(four ? perturb_kernel<4>(streams, strided)
-                                : perturb_kernel<2>(streams, strided),
-                           dim3(l.grid), dim3(kStepThreads), 0, s, g.tiles, g.n_full, g.rows, st,
-                           l.shape);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "es_perturb_kernel launch");
+        const PerturbKernel kernel = four ? perturb_kernel<4>(streams, strided)
+                                          : perturb_kernel<2>(streams, strided);
+        const int rc = launch_steps(
+            g, sh, nullptr, "", "es_perturb_kernel",
+            [&](const DevTile* tiles, uint64_t n_full, const DevRows* rows, const uint64_t*,
+                uint32_t grid) {
+                hipLaunchKernelGGL(kernel, dim3(grid), dim3(kStepThreads), 0, s, tiles, n_full,
+                                   rows, st, sh);
+            });
+        if (rc != ES_OK) return rc;
     }
     return ES_OK;
 }
@@ -1756,34 +1812,43 @@ int check_qdevice(const es_qplan_t* p) {
     return ES_OK;
 }
 
-int launch_qpass(es_qplan_t* p, QKind kind, const QPass& ps, hipStream_t s) {
-    if (p->n_full + p->n_tail == 0) return ES_OK;
+// The steps of a quantized plan: up to eight per workgroup (it looks its tensor
+// up once), as many as leave three workgroups per slot of the chip.  int8 swap
+// over the 0.5B-shaped set 557 us with one, 524, 510 and 506 with two, four and
+// eight; fp8 update of 8 over an eighth of it 198, 195 and 204 us with one, two
+// and four.
+QShape qstep_shape(const es_qplan_t* p) {
     QShape sh{};
     sh.tile_elems = static_cast<uint32_t>(p->threads) * p->groups * esq::kQGroup;
     sh.n_tensors = p->n_tensors;
-    // up to eight steps per workgroup (it looks its tensor up once), as many
-    // as leave three workgroups per slot of the chip: int8 swap over the
-    // 0.5B-shaped set 557 us with one, 524, 510 and 506 with two, four and
-    // eight; fp8 update of 8 over an eighth of it 198, 195 and 204 us with
-    // one, two and four
     const uint64_t slots = uint64_t(p->cus) * 8;
     sh.full_steps = 1;
     while (sh.full_steps < 8 && 2 * sh.full_steps * kQStepCodes <= sh.tile_elems &&
            p->numel / (2 * sh.full_steps * kQStepCodes) >= 3 * slots)
         sh.full_steps *= 2;
     while ((sh.full_steps * kQStepCodes << sh.full_shift) < sh.tile_elems) ++sh.full_shift;
-    const StepLaunch l = step_launch(0, p->n_tail, p->tail_max, sh.tile_elems, kQStepCodes * sh.full_steps);
-    sh.tail_shift = l.shape.tail_shift;
-    sh.tail_steps = l.shape.tail_steps * sh.full_steps;
-    const uint32_t grid = static_cast<uint32_t>((p->n_full << sh.full_shift) +
-                                                (p->n_tail << sh.tail_shift));
-    hipLaunchKernelGGL(qpass_kernel(kind, p->format), dim3(grid), dim3(kStepThreads), 0, s,
-                       p->d_tab, p->n_full,
-                       reinterpret_cast<const Member*>(p->d_scratch + kOffMembers),
-                       reinterpret_cast<const UpdateHeader*>(p->d_scratch + kOffHeader), ps, sh);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "es_qpass_kernel launch");
-    return ES_OK;
+    const StepShape tail =
+        step_shape(p->n_tail, p->tail_max, sh.tile_elems, kQStepCodes * sh.full_steps);
+    sh.tail_shift = tail.tail_shift;
+    sh.tail_steps = tail.tail_steps * sh.full_steps;
+    return sh;
+}
+
+int launch_qpass(es_qplan_t* p, QKind kind, const QPass& ps, hipStream_t s) {
+    QShape sh = qstep_shape(p);
+    const QPassKernel kernel = qpass_kernel(kind, p->format);
+    return for_step_launches(
+        p->n_full, p->n_tail, sh.full_shift, sh.tail_shift,
+        [&](uint64_t first, uint64_t full, uint32_t grid) {
+            sh.first_full = std::min(first, p->n_full);
+            sh.first_tail = first - sh.first_full;
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(kStepThreads), 0, s, p->d_tab, full,
+                               reinterpret_cast<const Member*>(p->d_scratch + kOffMembers),
+                               reinterpret_cast<const UpdateHeader*>(p->d_scratch + kOffHeader),
+                               ps, sh);
+            const hipError_t e = hipGetLastError();
+            return e != hipSuccess ? hip_fail(e, "es_qpass_kernel launch") : ES_OK;
+        });
 }
 
 // The kernel argument of one perturbation member of a quantized pass: its
@@ -2163,13 +2228,17 @@ int update_impl(const char* name, es_plan_t* plan, uint8_t* d_scratch, const uin
         // the segment's masters: the delta table runs parallel to the tiles
         const uint64_t* mdelta =
             master ? plan->d_master + (strided ? plan->n_full + plan->n_tail : 0) : nullptr;
-        const StepLaunch l = plan_steps(plan, g, 2);
-        hipLaunchKernelGGL(kernel, dim3(l.grid), dim3(kStepThreads), 0, s, g.tiles, g.n_full,
-                           g.rows, reinterpret_cast<const Member*>(d_scratch + kOffMembers),
-                           reinterpret_cast<const UpdateHeader*>(d_scratch + kOffHeader), rk,
-                           rst, mdelta, l.shape);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, std::string(name) + ": es_update_kernel launch");
+        const StepShape sh = plan_steps(plan, g, 2);
+        rc = launch_steps(
+            g, sh, mdelta, name, ": es_update_kernel",
+            [&](const DevTile* tiles, uint64_t n_full, const DevRows* rows,
+                const uint64_t* delta, uint32_t grid) {
+                hipLaunchKernelGGL(kernel, dim3(grid), dim3(kStepThreads), 0, s, tiles, n_full,
+                                   rows, reinterpret_cast<const Member*>(d_scratch + kOffMembers),
+                                   reinterpret_cast<const UpdateHeader*>(d_scratch + kOffHeader),
+                                   rk, rst, delta, sh);
+            });
+        if (rc != ES_OK) return rc;
     }
     return ES_OK;
 }
@@ -2739,15 +2808,18 @@ int es_perturb_master(es_plan_t* plan, uint64_t seed, int32_t sign, float sigma,
             const Segment& g = seg[k];
             const bool strided = g.rows != nullptr;
             const bool four = four_groups(plan, g);
-            const StepLaunch l = plan_steps(plan, g, four ? 4 : 2);
-            hipLaunchKernelGGL(four ? apply_master_kernel<4>(strided)
-                                    : apply_master_kernel<2>(strided),
-                               dim3(l.grid), dim3(kStepThreads), 0, s, g.tiles, g.n_full, g.rows,
-                               st, plan->d_master + (strided ? plan->n_full + plan->n_tail : 0),
-                               l.shape);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess)
-                return hip_fail(e, "es_perturb_master: es_apply_master_kernel launch");
+            const StepShape sh = plan_steps(plan, g, four ? 4 : 2);
+            const ApplyMasterKernel kernel = four ? apply_master_kernel<4>(strided)
+                                                  : apply_master_kernel<2>(strided);
+            rc = launch_steps(
+                g, sh, plan->d_master + (strided ? plan->n_full + plan->n_tail : 0),
+                "es_perturb_master", ": es_apply_master_kernel",
+                [&](const DevTile* tiles, uint64_t n_full, const DevRows* rows,
+                    const uint64_t* delta, uint32_t grid) {
+                    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kStepThreads), 0, s, tiles,
+                                       n_full, rows, st, delta, sh);
+                });
+            if (rc != ES_OK) return rc;
         }
         return ES_OK;
     }
@@ -2763,15 +2835,20 @@ int es_perturb_master(es_plan_t* plan, uint64_t seed, int32_t sign, float sigma,
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
         const bool strided = g.rows != nullptr;
-        const StepLaunch l = plan_steps(plan, g, 2);
-        hipLaunchKernelGGL(update_master_kernel(strided, true), dim3(l.grid), dim3(kStepThreads),
-                           0, s, g.tiles, g.n_full, g.rows,
-                           reinterpret_cast<const Member*>(plan->d_scratch + kOffMembers),
-                           reinterpret_cast<const UpdateHeader*>(plan->d_scratch + kOffHeader),
-                           RoundKey{0u, 0u}, RestoreArg{0u, 0.0f},
-                           plan->d_master + (strided ? plan->n_full + plan->n_tail : 0), l.shape);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "es_perturb_master: es_update_kernel launch");
+        const StepShape sh = plan_steps(plan, g, 2);
+        const UpdateKernel kernel = update_master_kernel(strided, true);
+        rc = launch_steps(
+            g, sh, plan->d_master + (strided ? plan->n_full + plan->n_tail : 0),
+            "es_perturb_master", ": es_update_kernel",
+            [&](const DevTile* tiles, uint64_t n_full, const DevRows* rows,
+                const uint64_t* delta, uint32_t grid) {
+                hipLaunchKernelGGL(
+                    kernel, dim3(grid), dim3(kStepThreads), 0, s, tiles, n_full, rows,
+                    reinterpret_cast<const Member*>(plan->d_scratch + kOffMembers),
+                    reinterpret_cast<const UpdateHeader*>(plan->d_scratch + kOffHeader),
+                    RoundKey{0u, 0u}, RestoreArg{0u, 0.0f}, delta, sh);
+            });
+        if (rc != ES_OK) return rc;
     }
     return ES_OK;
 }
@@ -3045,12 +3122,16 @@ int es_stream_pass(es_plan_t* plan, es_stream_t stream) {
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
         const bool four = four_groups(plan, g);
-        const StepLaunch l = plan_steps(plan, g, four ? 4 : 2);
-        hipLaunchKernelGGL(four ? es_stream_kernel<4> : es_stream_kernel<2>, dim3(l.grid),
-                           dim3(kStepThreads), 0, static_cast<hipStream_t>(stream), g.tiles,
-                           g.n_full, 0u, l.shape);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "es_stream_kernel launch");
+        const StepShape sh = plan_steps(plan, g, four ? 4 : 2);
+        const int rc2 = launch_steps(
+            g, sh, nullptr, "", "es_stream_kernel",
+            [&](const DevTile* tiles, uint64_t n_full, const DevRows*, const uint64_t*,
+                uint32_t grid) {
+                hipLaunchKernelGGL(four ? es_stream_kernel<4> : es_stream_kernel<2>, dim3(grid),
+                                   dim3(kStepThreads), 0, static_cast<hipStream_t>(stream),
+                                   tiles, n_full, 0u, sh);
+            });
+        if (rc2 != ES_OK) return rc2;
     }
     return ES_OK;
 }

@@ -1,8 +1,8 @@
 // Host-side checks of the library's own host code, built with AddressSanitizer
 // and UndefinedBehaviorSanitizer (host pass only, no device code): the
 // population tables of the update, the tiling of tensors and of blocks, the
-// int8 row divisor, the geometry of quantized blocks, and every argument
-// check that fails before the device is touched.
+// int8 row divisor, the geometry of quantized blocks, the launches of the step
+// kernels, and every argument check that fails before the device is touched.
 // The library source is compiled into this translation unit, so its internal
 // (anonymous-namespace) routines are reachable; each is compared with a plain
 // reference written here.  Prints "ok" and exits 0, or names the first
@@ -350,6 +350,142 @@ void test_qblock_geometry(std::mt19937_64& rng) {
     check(accepted > 5000, "qblock geometry: enough accepted blocks");
 }
 
+// The launches of the one-step workgroups: the order over the XCDs is a
+// permutation, every element of every tile is taken by exactly one workgroup
+// (also when a pass is cut into several launches), and every launch stays below
+// 2^32 lanes whatever the plan's size.
+struct StepCover {
+    uint64_t n_full, tile_elems, step_elems;
+    std::vector<uint64_t> tails;                 // their lengths
+    // steps of every tile taken so far, by the kernels' own item map
+    std::vector<std::vector<uint8_t>> taken;
+    bool ok = true;
+    uint64_t steps_of(uint64_t tile) const {
+        const uint64_t n = tile < n_full ? tile_elems : tails[tile - n_full];
+        return (n + step_elems - 1) / step_elems;
+    }
+    void reset() {
+        taken.assign(n_full + tails.size(), {});
+        for (uint64_t t = 0; t < taken.size(); ++t) taken[t].assign(steps_of(t), 0);
+    }
+    void launch(uint64_t first, uint64_t full, uint32_t grid, const StepShape& sh) {
+        for (uint64_t i = 0; i < grid; ++i) {
+            const StepItem it = step_item(i, full, sh);
+            const uint64_t tile = first + it.tile;
+            if (tile >= taken.size() || it.full != (tile < n_full)) { ok = false; continue; }
+            const uint32_t n = it.full ? 1u : sh.tail_steps;
+            for (uint32_t k = 0; k < n; ++k) {
+                const uint64_t step = uint64_t(it.part) * n + k;
+                if (it.full && step >= taken[tile].size()) ok = false;
+                if (step < taken[tile].size()) ++taken[tile][step];   // beyond a tail's end: none
+            }
+        }
+    }
+    bool once() const {
+        bool good = ok;
+        for (const auto& t : taken)
+            for (uint8_t c : t) good &= c == 1;
+        return good;
+    }
+};
+
+void test_step_launches(std::mt19937_64& rng) {
+    for (uint64_t n : {512ull, 1024ull, 512ull * 37}) {
+        std::vector<uint8_t> seen(n, 0);
+        bool ok = true;
+        for (uint64_t i = 0; i < n; ++i) {
+            const uint64_t j = xcd_run_item(i);
+            ok &= j < n && !seen[j];
+            if (j < n) seen[j] = 1;
+        }
+        check(ok, "step launches: the order over the XCDs is a permutation");
+    }
+    for (int trial = 0; trial < 300; ++trial) {
+        StepCover c;
+        c.tile_elems = trial % 3 == 0 ? 8192 : 65536;
+        c.step_elems = trial % 2 == 0 ? 4096 : 8192;
+        c.n_full = trial % 5 == 0 ? 0 : rng() % 300;
+        const uint64_t n_tail = trial % 7 == 0 ? 0 : rng() % (trial % 11 == 0 ? 70000 : 300);
+        const uint64_t longest = 1 + rng() % (trial % 4 == 0 ? 64 : c.tile_elems);
+        uint64_t tail_max = 0;
+        for (uint64_t t = 0; t < n_tail; ++t) {
+            c.tails.push_back(1 + rng() % longest);
+            tail_max = std::max(tail_max, c.tails.back());
+        }
+        const StepShape sh = step_shape(n_tail, tail_max, c.tile_elems, c.step_elems);
+        for (const uint64_t cap : {kMaxStepGrid, uint64_t(1000), uint64_t(16)}) {
+            c.reset();
+            uint64_t launches = 0, items = 0;
+            for_step_launches(c.n_full, n_tail, sh.full_shift, sh.tail_shift,
+                              [&](uint64_t first, uint64_t full, uint32_t grid) {
+                                  check(grid > 0 && grid <= cap, "step launches: grid");
+                                  c.launch(first, full, grid, sh);
+                                  ++launches;
+                                  items += grid;
+                                  return ES_OK;
+                              }, cap);
+            check(c.once(), "step launches: every step once");
+            check(cap != kMaxStepGrid || launches <= 1, "step launches: one for a small plan");
+            check(launches >= items / cap, "step launches: cut at the cap");
+        }
+    }
+    // up to and beyond the card's memory: aligned plans, unaligned ones (all
+    // tails) and the smallest tiles
+    for (const uint64_t elems : {(uint64_t(1) << 36) - 1, uint64_t(1) << 36,
+                                 (uint64_t(1) << 36) + 65536, uint64_t(1) << 37,
+                                 uint64_t(160) << 30})
+        for (const uint64_t tile : {8192ull, 65536ull})
+            for (const uint64_t step : {4096ull, 8192ull})
+                for (const bool aligned : {true, false}) {
+                    const uint64_t n_full = aligned ? elems / tile : 0;
+                    const uint64_t n_tail = aligned ? 1 : (elems + tile - 1) / tile;
+                    const StepShape sh = step_shape(n_tail, tile, tile, step);
+                    uint64_t f = 0, t = 0;
+                    for_step_launches(
+                        n_full, n_tail, sh.full_shift, sh.tail_shift,
+                        [&](uint64_t first, uint64_t full, uint32_t grid) {
+                            check(uint64_t(grid) * kStepThreads < (uint64_t(1) << 32),
+                                  "step launches: below 2^32 lanes");
+                            check(first == f + t, "step launches: consecutive tiles");
+                            const uint64_t tail_items = grid - (full << sh.full_shift);
+                            check(tail_items % (1u << sh.tail_shift) == 0 &&
+                                      (tail_items == 0 || f + full == n_full),
+                                  "step launches: whole tiles, the full ones first");
+                            f += full;
+                            t += tail_items >> sh.tail_shift;
+                            return ES_OK;
+                        });
+                    check(f == n_full && t == n_tail, "step launches: every tile");
+                }
+    // quantized plans, with the fewest and the most codes per workgroup
+    for (const int threads : {256, 1024})
+        for (const uint64_t codes : {uint64_t(5000), uint64_t(1) << 30, uint64_t(320) << 30}) {
+            es_qplan_t q;
+            q.cus = 256;
+            q.threads = threads;
+            q.numel = codes;
+            const uint64_t tile = uint64_t(q.threads) * q.groups * esq::kQGroup;
+            q.n_full = codes / tile;
+            q.n_tail = 2;
+            q.tail_max = std::min(codes, tile);
+            const QShape sh = qstep_shape(&q);
+            check((uint64_t(sh.full_steps) * kQStepCodes << sh.full_shift) == tile &&
+                      (uint64_t(sh.tail_steps) * kQStepCodes << sh.tail_shift) >= q.tail_max,
+                  "step launches: a quantized tile's steps");
+            uint64_t next = 0;
+            for_step_launches(q.n_full, q.n_tail, sh.full_shift, sh.tail_shift,
+                              [&](uint64_t first, uint64_t full, uint32_t grid) {
+                                  check(uint64_t(grid) * kStepThreads < (uint64_t(1) << 32) &&
+                                            first == next,
+                                        "step launches: quantized");
+                                  next += full + ((grid - (full << sh.full_shift)) >>
+                                                  sh.tail_shift);
+                                  return ES_OK;
+                              });
+            check(next == q.n_full + q.n_tail, "step launches: every quantized tile");
+        }
+}
+
 // Argument checks that must fail before any device access.
 void test_validation() {
     const uint64_t seeds[3] = {1, 2, 3};
@@ -437,6 +573,7 @@ int main() {
     test_block_tiling(rng);
     test_row_divisor(rng);
     test_qblock_geometry(rng);
+    test_step_launches(rng);
     test_validation();
     if (g_failures) {
         std::printf("%d failures\n", g_failures);

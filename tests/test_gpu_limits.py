@@ -1,8 +1,9 @@
-"""A plan at the maximum tensor count (ES_MAX_TENSORS = 2^20): views of 0 to
+"""Plans at the limits.  The maximum tensor count (ES_MAX_TENSORS = 2^20): views of 0 to
 8 elements each, every one a tail tile of its own.  Perturb and update leave
 the same bits as the same tensors planned in reverse order (the noise depends
 only on each tensor's id and element index), sampled tensors match the
-oracle, and the bytes between the views are untouched."""
+oracle, and the bytes between the views are untouched.  And a plan of more
+elements than one launch of the update covers."""
 import numpy as np
 import pytest
 import torch
@@ -120,3 +121,50 @@ def test_quantized_plan_at_the_maximum_tensor_count():
     print("2^20 int8 tensors, sampled perturb:", rep)
     assert_qparity(rep, "int8 perturb at 2^20 tensors")
 
+
+
+def test_update_of_a_plan_beyond_one_launch():
+    """2^36 elements and some (137 GB): an update's one-step workgroups would
+    have 2^32 lanes there, more than a launch takes, so the pass is two launches.
+    Elements around the start, the cut between them, a counter's high word and
+    the end, each pass against the oracle."""
+    n = (1 << 36) + 3 * 65536 + 4099
+    if torch.cuda.mem_get_info()[0] < 2 * n + (8 << 30):
+        pytest.skip("not enough free device memory")
+    t = torch.zeros(n, dtype=torch.bfloat16, device="cuda")
+    first_launch = ((1 << 24) - 1) // 16 * 65536          # elements in its whole tiles
+    marks = [0, 1 << 34, first_launch - 65536, first_launch, 1 << 36, n - 9000]
+    at = np.unique(np.concatenate([np.arange(max(0, m - 4500), min(n, m + 9000), dtype=np.uint64)
+                                   for m in marks]))
+    runs = np.split(at, np.flatnonzero(np.diff(at) > 1) + 1)
+    bits = wl.random_bf16_bits(at.size, 93)
+
+    def spans():
+        return [t[int(r[0]):int(r[-1]) + 1] for r in runs]
+    done = 0
+    for v in spans():
+        v.copy_(to_device(bits[done:done + v.numel()]))
+        done += v.numel()
+
+    def host():
+        torch.cuda.synchronize()
+        return np.concatenate([to_host(v) for v in spans()])
+    seeds, signs, rr = [1, 2, 1], [1, 1, -1], np.array([0.3, 0.8, 0.1], np.float32)
+    r = torch.from_numpy(rr).cuda()
+    with esopt.Plan([t], tensor_ids=[5]) as p:
+        p.perturb(2, 1, 1e-3)
+        x1 = host()
+        assert_parity(report(x1, oracle.perturb(bits, 2, 5, 1, 1e-3, elems=at), bits,
+                             perturb_delta(2, 5, 1, 1e-3, at)), "perturb beyond 2^36")
+        p.restore(2, 1, 1e-3)
+        x2 = host()
+        assert_parity(report(x2, oracle.restore(x1, 2, 5, 1, 1e-3, elems=at), x1,
+                             perturb_delta(2, 5, -1, 1e-3, at)), "restore beyond 2^36")
+        p.update(seeds, signs, r, 5e-4)
+        x3 = host()
+    assert_parity(report(x3, oracle.update(x2, 5, seeds, signs, rr, 5e-4, 1e-3, elems=at)[0], x2,
+                         update_delta(5, seeds, signs, rr, 5e-4, 1e-3, 0, at)),
+                  "update beyond 2^36")
+    # 256 elements in every 2^30 held zeros, which the passes left as noise
+    far = torch.stack([t[k << 30:(k << 30) + 256] for k in range(1, 64)])
+    assert int((far != 0).sum()) > 0.99 * far.numel()
