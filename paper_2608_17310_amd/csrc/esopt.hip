@@ -14,9 +14,10 @@
 //     65536 elements, 128 KB): full tiles on tile-sized boundaries of the
 //     address space, then tail tiles (each tensor's head and remainder, or
 //     every tile of an unaligned tensor), each described by a 32-byte
-//     descriptor.  One launch covers the whole parameter list, the full tiles
-//     and then the tails, reading one descriptor per workgroup with a scalar
-//     load, so a tile's tensor, address and noise identity are wave-uniform.
+//     descriptor.  One launch covers the whole parameter list (several where it
+//     would have 2^32 lanes), the full tiles and then the tails, reading a
+//     workgroup's descriptor with scalar loads, so a tile's tensor, address and
+//     noise identity are wave-uniform.
 //   * Within a step of 256 x G groups, lane l of group slot g owns elements
 //     e0 + 8 (256 g + l) .. +7: one 16-byte load and one 16-byte store, 64
 //     lanes covering 1 KB contiguous per instruction.  Its two Philox calls
@@ -93,20 +94,29 @@ constexpr double kSqrt2Ln2Double = 1.1774100225154746910;   // sqrt(2 ln 2)
 // or every tile of a tensor whose base is not 16-byte aligned); the tiles of
 // strided blocks (es_plan_create_blocks) follow in two more runs of the same
 // kinds, each with a row map (DevRows), and are passed over in a second
-// launch.  A workgroup reads one descriptor per tile with a single scalar
+// launch.  A workgroup reads a full tile's descriptor with a single scalar
 // load and no search (searching a per-tensor table is a chain of dependent
-// scalar loads).
+// scalar loads), a tail tile's after one of its guide.
 // Full tiles aligned to the address space, not to their tensor's base: with
 // hundreds of tensors at unrelated offsets, tiles at mixed offsets streamed
 // ~4 % slower.  32 bytes per 65 536-element tile.
-struct DevTile {
+struct TileDesc {
     uint16_t* data;                         // the tensor's base
     uint64_t elem0;                         // the tile's first element in its tensor
-    uint64_t limit;                         // one past the last element a tail tile may touch
+    uint32_t len;                           // its elements, at most a full tile's
     uint32_t tensor_id;
-    uint32_t aligned16;                     // base 16-byte aligned
+    uint32_t first, guide;                  // tail tiles: see TailIndex
 };
-static_assert(sizeof(DevTile) == 32, "tile descriptor layout");
+static_assert(sizeof(TileDesc) == 32, "tile descriptor layout");
+
+// A tile as the host lays it out.
+struct DevTile {
+    uint16_t* data;
+    uint64_t elem0;
+    uint64_t limit;                         // one past its last element
+    uint32_t tensor_id;
+    uint32_t aligned16;                     // the tensor's base is 16-byte aligned
+};
 
 // Row map of a tile of a strided block (es_block_t with rows > 1 and
 // cols < row_len): the block is cut into pieces of whole rows, each tiled by
@@ -381,23 +391,22 @@ struct TileRef {
     uint64_t limit;
     uint64_t elem0;
     uint32_t tensor_id;
-    uint32_t aligned16;
     uint64_t n0 = 0;                        // row map (strided blocks only)
     uint32_t skip = 0, magic = 0, shift = 0, hi = 0;
 };
 
-__device__ __forceinline__ TileRef tile_ref(const DevTile& d) {
-    return TileRef{d.data, d.limit, d.elem0, d.tensor_id, d.aligned16};
+__device__ __forceinline__ TileRef tile_ref(const TileDesc& d) {
+    return TileRef{d.data, d.elem0 + d.len, d.elem0, d.tensor_id};
 }
 
-__device__ __forceinline__ TileRef tile_ref(const DevTile& d, const DevRows& m) {
-    return TileRef{d.data, d.limit, d.elem0, d.tensor_id, d.aligned16, m.n0, m.skip, m.magic,
-                   m.shift, m.hi};
+__device__ __forceinline__ TileRef tile_ref(const TileDesc& d, const DevRows& m) {
+    return TileRef{d.data, d.elem0 + d.len, d.elem0, d.tensor_id, m.n0, m.skip, m.magic, m.shift,
+                   m.hi};
 }
 
 // Tile i of a launch: its descriptor, and with kRows its row map.
 template <bool kRows>
-__device__ __forceinline__ TileRef load_ref(const DevTile* __restrict__ tiles,
+__device__ __forceinline__ TileRef load_ref(const TileDesc* __restrict__ tiles,
                                             const DevRows* __restrict__ rows, uint64_t i) {
     if constexpr (kRows) return tile_ref(tiles[i], rows[i]);
     else return tile_ref(tiles[i]);
@@ -419,19 +428,41 @@ __device__ __forceinline__ uint32_t tile_high_word(const TileRef& r) {
 }
 
 // How a launch of kStepThreads-lane workgroups covers a plan's tiles, one step
-// (kG 8-element groups per lane, 256 x 8 kG elements) per workgroup: a full
-// tile is 2^full_shift steps, a tail tile 2^tail_shift workgroups of
-// tail_steps steps each (one, except where there are very many tail tiles).
-// Workgroups are dispatched in order, so those in flight work on one
-// contiguous stretch of the plan's memory, and a step's loads leave in one
+// per workgroup: a full tile is 2^full_shift steps of kG 8-element groups per
+// lane (256 x 8 kG elements), and a tail tile as many steps of two groups as it
+// needs (TailIndex).  Workgroups are dispatched in order, so those in flight work
+// on one contiguous stretch of the plan's memory, and a step's loads leave in one
 // burst and its stores in another.  In place over the 0.5B-shaped set (perturb
 // and restore, kG = 4): 6.41 TB/s with one step per workgroup, 6.22 with two,
 // 5.66 with four; 5.67 with two steps over a grid that strides (the order is
 // lost), 5.70 with one 1024-lane workgroup per CU striding over 128 KB tiles
 // with its next tile's loads in flight.
+constexpr uint32_t kTailStep = kStepThreads * 2 * kGroupElems;   // elements of a tail's step
+
+// The steps of a run of tail tiles, numbered tile by tile: tail t's are first(t)
+// .. first(t + 1) - 1.  The tail of step j is found from guide(k), k = j n_tail /
+// n_steps, which is the tail of the first step with that k (a guide table: a k
+// stands for n_steps / n_tail steps, so the search goes on over the few tails
+// that these lie in).  So every workgroup has a step, whatever the tails'
+// lengths, and none has two: with every tail cut for the longest, a plan of
+// many short tensors and a longer one launched mostly empty workgroups, which
+// cost 0.7 (perturb) to 2 ns each (update of 4), and with several steps per
+// workgroup where the tails are many, those of an unaligned plan, whose every
+// tile is a tail, lost their order.  10 000 tensors of 64 elements and one of
+// 60 000, perturb 53 -> 8 us and update of 4 members 163 -> 29; 6 G unaligned
+// elements, perturb 5.35 -> 4.29 ms.  Two groups per lane in every pass: 200 M
+// unaligned elements, perturb 138 us with two and 144 with four, swap 200 with
+// either.
+struct TailIndex {
+    uint32_t n_tail;
+    uint32_t n_steps;
+    uint64_t ratio;                         // n_tail / n_steps in units of 2^-32
+};
 struct StepShape {
     uint32_t full_shift;
-    uint32_t tail_shift, tail_steps;
+    uint32_t step0;                         // the launch's first tail step
+    uint64_t tail0;                         // the first tail tile, from the launch's first tile
+    TailIndex tails;
 };
 
 // Workgroups go to the 8 XCDs in turn.  Within each 512 of them, item
@@ -446,49 +477,58 @@ __host__ __device__ __forceinline__ uint64_t xcd_run_item(uint64_t i) {
     return (j / kXcdRun) * (kXcds * kXcdRun) + (i % kXcds) * kXcdRun + j % kXcdRun;
 }
 
-// What workgroup i of a step launch over n_full full tiles and the tail tiles
-// behind them takes: part `part` of tile `tile`.  The host tests call this same
-// function.
+// What workgroup i of a step launch takes, first the n_full full tiles' steps
+// and then tail steps: part `part` of tile `tile`.  The host tests call this
+// same function.
 struct StepItem {
     bool full;
     uint32_t part;
     uint64_t tile;
+    TileDesc desc;                          // the tile's
 };
 __host__ __device__ __forceinline__ StepItem step_item(uint64_t i, uint64_t n_full,
-                                                       const StepShape& sh) {
+                                                       const StepShape& sh,
+                                                       const TileDesc* __restrict__ tiles) {
     const uint64_t full_items = n_full << sh.full_shift;
     if (i < (full_items & ~uint64_t(kXcds * kXcdRun - 1))) i = xcd_run_item(i);
-    if (i < full_items)
-        return StepItem{true, static_cast<uint32_t>(i) & ((1u << sh.full_shift) - 1u),
-                        i >> sh.full_shift};
-    const uint64_t j = i - full_items;
-    return StepItem{false, static_cast<uint32_t>(j) & ((1u << sh.tail_shift) - 1u),
-                    n_full + (j >> sh.tail_shift)};
+    if (i < full_items) {
+        const uint64_t tile = i >> sh.full_shift;
+        return StepItem{true, static_cast<uint32_t>(i) & ((1u << sh.full_shift) - 1u), tile,
+                        tiles[tile]};
+    }
+    const uint32_t j = static_cast<uint32_t>(i - full_items) + sh.step0;
+    const TileDesc* const tails = tiles + sh.tail0;
+    if (sh.tails.n_steps == sh.tails.n_tail)               // a step per tail
+        return StepItem{false, 0u, sh.tail0 + j, tails[j]};
+    const uint32_t last = sh.tails.n_tail - 1u;
+    uint32_t t = tails[(j * sh.tails.ratio) >> 32].guide;
+    TileDesc d = tails[t];
+    uint32_t end = tails[min(t + 1u, last)].first;         // of t's steps (not the last tail's)
+    while (t < last && end <= j) {
+        ++t;
+        d = tails[t];
+        end = tails[min(t + 1u, last)].first;
+    }
+    return StepItem{false, j - d.first, sh.tail0 + t, d};
 }
 
-// The step (or steps) of this workgroup: step(full, tile reference, tile
-// number, the lane's first element); its group g starts 8 kStepThreads g
-// elements on.  For a tail tile the first group starts below the bound (lanes
-// beyond it are left out) and the others may not.
+// The step of this workgroup: step(full, tile reference, tile number, the
+// lane's first element); its group g starts 8 kStepThreads g elements on.  For a
+// tail tile the first group starts below the bound (lanes beyond it are left
+// out) and the second may not.
 template <bool kRows, int kG, class Step>
-__device__ __forceinline__ void for_steps(const DevTile* __restrict__ tiles, uint64_t n_full,
+__device__ __forceinline__ void for_steps(const TileDesc* __restrict__ tiles, uint64_t n_full,
                                           const DevRows* __restrict__ rows, const StepShape& sh,
                                           Step step) {
     constexpr uint32_t kElems = kStepThreads * kG * kGroupElems;
-    const StepItem it = step_item(blockIdx.x, n_full, sh);
-    const TileRef r = load_ref<kRows>(tiles, rows, it.tile);
-    if (it.full) {
-        step(std::true_type{}, r, it.tile,
-             r.elem0 + it.part * kElems + threadIdx.x * uint32_t(kGroupElems));
-        return;
-    }
-#pragma unroll 1
-    for (uint32_t k = 0; k < sh.tail_steps; ++k) {
-        const uint64_t e = r.elem0 + uint64_t(it.part * sh.tail_steps + k) * kElems +
-                           threadIdx.x * uint32_t(kGroupElems);
-        if (e >= r.limit) return;
-        step(std::false_type{}, r, it.tile, e);
-    }
+    const StepItem it = step_item(blockIdx.x, n_full, sh, tiles);
+    TileRef r;
+    if constexpr (kRows) r = tile_ref(it.desc, rows[it.tile]);
+    else r = tile_ref(it.desc);
+    const uint64_t e = r.elem0 + it.part * (it.full ? kElems : kTailStep) +
+                       threadIdx.x * uint32_t(kGroupElems);
+    if (it.full) step(std::true_type{}, r, it.tile, e);
+    else if (e < r.limit) step(std::false_type{}, r, it.tile, e);
 }
 
 // One pass over the whole parameter list applying kM noise streams: each lane
@@ -498,7 +538,7 @@ __device__ __forceinline__ void for_steps(const DevTile* __restrict__ tiles, uin
 // blocks, each with its row map in `rows` (same index as its descriptor);
 // otherwise `rows` is unused.
 template <int kM, bool kRows, int kG>
-__global__ __launch_bounds__(kStepThreads) void es_perturb_kernel(const DevTile* __restrict__ tiles,
+__global__ __launch_bounds__(kStepThreads) void es_perturb_kernel(const TileDesc* __restrict__ tiles,
                                                                   uint64_t n_full,
                                                                   const DevRows* __restrict__ rows,
                                                                   Streams st, StepShape sh) {
@@ -506,9 +546,10 @@ __global__ __launch_bounds__(kStepThreads) void es_perturb_kernel(const DevTile*
     for_steps<kRows, kG>(tiles, n_full, rows, sh,
                          [&](auto full, const TileRef& r, uint64_t, uint64_t e) {
         constexpr bool kFast = decltype(full)::value;
-        uint32_t raw[kG][4];
+        constexpr int kN = kFast ? kG : 2;
+        uint32_t raw[kN][4];
 #pragma unroll
-        for (int g = 0; g < kG; ++g) {
+        for (int g = 0; g < kN; ++g) {
             if (kFast || e + g * kSlab < r.limit)
                 load_group<kFast, true>(r.data, e + g * kSlab, r.limit, raw[g]);
             else
@@ -516,14 +557,14 @@ __global__ __launch_bounds__(kStepThreads) void es_perturb_kernel(const DevTile*
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int g = 0; g < kG; g += 2) {
+        for (int g = 0; g < kN; g += 2) {
             const uint64_t n[2] = {noise_index<kRows>(r, e + g * kSlab),
                                    noise_index<kRows>(r, e + (g + 1) * kSlab)};
             perturb_pair<kM>(raw + g, n, tile_high_word<kRows>(r), r.tensor_id, st);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int g = 0; g < kG; ++g)
+        for (int g = 0; g < kN; ++g)
             if (kFast || e + g * kSlab < r.limit)
                 store_group<kFast, true>(r.data, e + g * kSlab, r.limit, raw[g]);
     });
@@ -547,20 +588,21 @@ __device__ __forceinline__ uintptr_t master_base(const uint64_t* __restrict__ md
 // of the other passes with bounds-checked accesses.
 template <bool kRows, int kG>
 __global__ __launch_bounds__(kStepThreads) void es_apply_master_kernel(
-    const DevTile* __restrict__ tiles, uint64_t n_full, const DevRows* __restrict__ rows,
+    const TileDesc* __restrict__ tiles, uint64_t n_full, const DevRows* __restrict__ rows,
     Streams st, const uint64_t* __restrict__ mdelta, StepShape sh) {
     typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
     constexpr uint64_t kSlab = uint64_t(kStepThreads) * kGroupElems;
     for_steps<kRows, kG>(tiles, n_full, rows, sh,
                          [&](auto full, const TileRef& r, uint64_t tile, uint64_t e) {
         constexpr bool kFast = decltype(full)::value;
+        constexpr int kN = kFast ? kG : 2;
         const uintptr_t mb = master_base(mdelta, r, tile);
         const uint32_t q_hi = tile_high_word<kRows>(r);
-        float m[kG][8];
+        float m[kN][8];
         if constexpr (kFast) {
             const uint64_t e4 = e - threadIdx.x * 4u;        // the lane's first quad
 #pragma unroll
-            for (int i = 0; i < 2 * kG; ++i) {
+            for (int i = 0; i < 2 * kN; ++i) {
                 const f32x4_t v = __builtin_nontemporal_load(
                     (const ES_GLOBAL f32x4_t*)(mb + 4 * (e4 + i * (kSlab / 2))));
                 float* x = m[i / 2] + 4 * (i % 2);
@@ -568,7 +610,7 @@ __global__ __launch_bounds__(kStepThreads) void es_apply_master_kernel(
             }
         } else {
 #pragma unroll
-            for (int g = 0; g < kG; ++g) {
+            for (int g = 0; g < kN; ++g) {
                 if (e + g * kSlab < r.limit)
                     load_master<false, true>(mb, e + g * kSlab, r.limit, m[g]);
                 else
@@ -576,9 +618,9 @@ __global__ __launch_bounds__(kStepThreads) void es_apply_master_kernel(
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        uint32_t out[kG][4];
+        uint32_t out[kN][4];
 #pragma unroll
-        for (int g = 0; g < kG; g += 2) {
+        for (int g = 0; g < kN; g += 2) {
             uint32_t q[4];
             if constexpr (kFast) {
 #pragma unroll
@@ -602,14 +644,14 @@ __global__ __launch_bounds__(kStepThreads) void es_apply_master_kernel(
         if constexpr (kFast) {
             const uint64_t e4 = e - threadIdx.x * 4u;
 #pragma unroll
-            for (int i = 0; i < 2 * kG; ++i) {
+            for (int i = 0; i < 2 * kN; ++i) {
                 const u32x2_t v = {out[i / 2][2 * (i % 2)], out[i / 2][2 * (i % 2) + 1]};
                 __builtin_nontemporal_store(v,
                                             (ES_GLOBAL u32x2_t*)(r.data + e4 + i * (kSlab / 2)));
             }
         } else {
 #pragma unroll
-            for (int g = 0; g < kG; ++g)
+            for (int g = 0; g < kN; ++g)
                 if (e + g * kSlab < r.limit)
                     store_group<false, true>(r.data, e + g * kSlab, r.limit, out[g]);
         }
@@ -622,21 +664,22 @@ __global__ __launch_bounds__(kStepThreads) void es_apply_master_kernel(
 // nontemporal accesses as the passes above but without arithmetic, so it
 // bounds what any pass over the plan can reach.
 template <int kG>
-__global__ __launch_bounds__(kStepThreads) void es_stream_kernel(const DevTile* __restrict__ tiles,
+__global__ __launch_bounds__(kStepThreads) void es_stream_kernel(const TileDesc* __restrict__ tiles,
                                                                  uint64_t n_full, uint32_t flip,
                                                                  StepShape sh) {
     constexpr uint64_t kSlab = uint64_t(kStepThreads) * kGroupElems;
     for_steps<false, kG>(tiles, n_full, nullptr, sh,
                          [&](auto full, const TileRef& r, uint64_t, uint64_t e) {
         constexpr bool kFast = decltype(full)::value;
-        uint32_t raw[kG][4];
+        constexpr int kN = kFast ? kG : 2;
+        uint32_t raw[kN][4];
 #pragma unroll
-        for (int g = 0; g < kG; ++g)
+        for (int g = 0; g < kN; ++g)
             if (kFast || e + g * kSlab < r.limit)
                 load_group<kFast, true>(r.data, e + g * kSlab, r.limit, raw[g]);
         __builtin_amdgcn_sched_barrier(0);      // all loads issued before the first wait
 #pragma unroll
-        for (int g = 0; g < kG; ++g)
+        for (int g = 0; g < kN; ++g)
             if (kFast || e + g * kSlab < r.limit) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) raw[g][k] ^= flip;
@@ -712,7 +755,7 @@ __device__ __forceinline__ void add_workgroup_sum(uint64_t acc, unsigned long lo
 // tiles would keep as few CUs at eight group slots in a row (with the slots of
 // an item known to the compiler otherwise: 1 % on large plans).
 template <int kThreads, int kU, bool kRows, bool kCut>
-__global__ __launch_bounds__(kThreads) void es_checksum_kernel(const DevTile* __restrict__ tiles,
+__global__ __launch_bounds__(kThreads) void es_checksum_kernel(const TileDesc* __restrict__ tiles,
                                                                uint64_t n_full, uint64_t n_tail,
                                                                const DevRows* __restrict__ rows,
                                                                uint32_t shift,
@@ -1000,7 +1043,7 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
 // maps; with kRestore the member rst reverted in the same pass.
 template <bool kNT, bool kSR, bool kRows, bool kRestore, int kMaster>
 __global__ __launch_bounds__(kStepThreads) void es_update_kernel(
-    const DevTile* __restrict__ tiles, uint64_t n_full, const DevRows* __restrict__ rows,
+    const TileDesc* __restrict__ tiles, uint64_t n_full, const DevRows* __restrict__ rows,
     const Member* __restrict__ members, const UpdateHeader* __restrict__ hdr, RoundKey rk, RestoreArg rst,
     const uint64_t* __restrict__ mdelta, StepShape sh) {
     const bool add = hdr->n_live != 0u;
@@ -1191,11 +1234,11 @@ __global__ __launch_bounds__(kAuxBlock) void es_normals_kernel(uint32_t k0, uint
     }
 }
 
-using PerturbKernel = void (*)(const DevTile*, uint64_t, const DevRows*, Streams, StepShape);
-using UpdateKernel = void (*)(const DevTile*, uint64_t, const DevRows*, const Member*,
+using PerturbKernel = void (*)(const TileDesc*, uint64_t, const DevRows*, Streams, StepShape);
+using UpdateKernel = void (*)(const TileDesc*, uint64_t, const DevRows*, const Member*,
                               const UpdateHeader*, RoundKey, RestoreArg, const uint64_t*,
                               StepShape);
-using ApplyMasterKernel = void (*)(const DevTile*, uint64_t, const DevRows*, Streams,
+using ApplyMasterKernel = void (*)(const TileDesc*, uint64_t, const DevRows*, Streams,
                                    const uint64_t*, StepShape);
 
 // streams: 1 (perturb / restore), 2 (swap, two keys), 3 (swap, one key);
@@ -1217,7 +1260,7 @@ ApplyMasterKernel apply_master_kernel(bool rows) {
 // Tile shapes instantiated: T lanes per workgroup x U groups per lane.
 #define ES_TILE_SHAPES(X) X(256, 4) X(256, 8) X(512, 4) X(512, 8) X(1024, 4) X(1024, 8)
 
-using ChecksumKernel = void (*)(const DevTile*, uint64_t, uint64_t, const DevRows*, uint32_t,
+using ChecksumKernel = void (*)(const TileDesc*, uint64_t, uint64_t, const DevRows*, uint32_t,
                                 unsigned long long*);
 
 ChecksumKernel checksum_kernel(int threads, int groups, bool rows, bool cut) {
@@ -1582,15 +1625,15 @@ struct es_plan {
     uint64_t n_tail = 0;            // tail tiles (bounds-checked path)
     uint64_t n_rfull = 0;           // full and tail tiles of strided blocks, after the
     uint64_t n_rtail = 0;           //   others, each with a row map
-    uint64_t tail_max = 0;          // elements of the longest tail tile
-    uint64_t rtail_max = 0;         //   and of the longest of strided blocks
+    TailIndex tails = {};           // the tail tiles' steps,
+    TailIndex rtails = {};          //   and those of strided blocks
     int cus = 0;                    // compute units of the device
     uint32_t grid_sum = 0;          // workgroups of the checksum launch
     uint32_t grid_sum_rows = 0;     //   and of its launch over strided blocks
     int threads = kDefaultThreads;  // lanes per workgroup of the tile kernels
     int groups = kDefaultGroups;    // 8-element groups per lane per tile
     uint64_t tile_elems = 0;        // threads * groups * 8
-    DevTile* d_tiles = nullptr;     // n_full full-tile then n_tail tail-tile descriptors, then
+    TileDesc* d_tiles = nullptr;    // n_full full-tile then n_tail tail-tile descriptors, then
                                     //   n_rfull + n_rtail of strided blocks
     DevRows* d_rows = nullptr;      // their row maps (same allocation, after the descriptors)
     uint8_t* d_scratch = nullptr;   // kScratchBytes
@@ -1643,54 +1686,82 @@ int check_device(const es_plan_t* p) {
 // contiguous blocks, and one over the tiles of strided blocks with their
 // row maps; a part with no tiles is left out.
 struct Segment {
-    const DevTile* tiles;
+    const TileDesc* tiles;
     uint64_t n_full, n_tail;
     const DevRows* rows;            // null for the first part
-    uint64_t tail_max;
+    TailIndex tails;
     uint32_t grid_sum;
 };
 
 int plan_segments(const es_plan_t* p, Segment seg[2]) {
     int n = 0;
     if (p->n_full + p->n_tail > 0)
-        seg[n++] = Segment{p->d_tiles, p->n_full, p->n_tail, nullptr, p->tail_max, p->grid_sum};
+        seg[n++] = Segment{p->d_tiles, p->n_full, p->n_tail, nullptr, p->tails, p->grid_sum};
     if (p->n_rfull + p->n_rtail > 0)
         seg[n++] = Segment{p->d_tiles + p->n_full + p->n_tail, p->n_rfull, p->n_rtail, p->d_rows,
-                           p->rtail_max, p->grid_sum_rows};
+                           p->rtails, p->grid_sum_rows};
     return n;
 }
 
-// The steps of a plan's tiles of tile_elems elements (a power of two, at least
-// 8192) and its n_tail tail tiles of at most tail_max, with steps of step_elems
-// elements.  A tail tile is cut for the longest one; where there are
+// Steps per full tile of tile_elems elements (a power of two, at least 8192)
+// with `groups` groups per lane.
+uint32_t full_tile_shift(uint64_t tile_elems, int groups) {
+    const uint64_t step = uint64_t(kStepThreads) * groups * kGroupElems;
+    uint32_t shift = 0;
+    while ((step << shift) < tile_elems) ++shift;
+    return shift;
+}
+
+// The device's descriptor of a tile.
+TileDesc tile_desc(const DevTile& d) {
+    return TileDesc{d.data, d.elem0, static_cast<uint32_t>(d.limit - d.elem0), d.tensor_id, 0u,
+                    0u};
+}
+
+// The first and guide entries of n tail descriptors, and their index.  A plan
+// has fewer than 2^32 tail steps: each is 8 KB of the device's memory or the end
+// of one of 2^20 tensors or 2^28 rows.
+TailIndex index_tails(TileDesc* tails, uint64_t n) {
+    uint64_t steps = 0;
+    for (uint64_t t = 0; t < n; ++t) {
+        tails[t].first = static_cast<uint32_t>(steps);
+        steps += (tails[t].len + kTailStep - 1) / kTailStep;
+    }
+    const TailIndex ix{static_cast<uint32_t>(n), static_cast<uint32_t>(steps),
+                       steps > 0 ? (n << 32) / steps : 0};
+    uint64_t next = 0;                      // first guide entry not yet written
+    for (uint64_t t = 0, j = 0; t < n; ++t)
+        for (const uint64_t end = t + 1 < n ? tails[t + 1].first : steps; j < end; ++j)
+            if ((j * ix.ratio) >> 32 == next) tails[next++].guide = static_cast<uint32_t>(t);
+    while (next < n) tails[next++].guide = static_cast<uint32_t>(n - 1);
+    return ix;
+}
+
+// How the tail tiles of a quantized plan, of at most tail_max codes, are cut:
+// for the longest one into parts of step codes; where there are
 // so many of them (tens of thousands of tiny tensors) that they fill the chip
 // several times over, they are cut less and a workgroup goes on to the next
 // step instead, since the empty workgroups of the short ones only cost.
-StepShape step_shape(uint64_t n_tail, uint64_t tail_max, uint64_t tile_elems,
-                     uint64_t step_elems) {
+struct QTailShape {
+    uint32_t shift, steps;
+};
+QTailShape qtail_shape(uint64_t n_tail, uint64_t tail_max, uint64_t step) {
     constexpr uint64_t kManyTails = 65536;
-    StepShape sh{};
-    while ((step_elems << sh.full_shift) < tile_elems) ++sh.full_shift;
-    while ((step_elems << sh.tail_shift) < tail_max && (n_tail << sh.tail_shift) < kManyTails)
-        ++sh.tail_shift;
-    const uint64_t part = step_elems << sh.tail_shift;
-    sh.tail_steps = static_cast<uint32_t>(std::max<uint64_t>((tail_max + part - 1) / part, 1));
+    QTailShape sh{};
+    while ((step << sh.shift) < tail_max && (n_tail << sh.shift) < kManyTails) ++sh.shift;
+    const uint64_t part = step << sh.shift;
+    sh.steps = static_cast<uint32_t>(std::max<uint64_t>((tail_max + part - 1) / part, 1));
     return sh;
 }
 
-StepShape plan_steps(const es_plan_t* p, const Segment& g, int groups) {
-    return step_shape(g.n_tail, g.tail_max, p->tile_elems,
-                      uint64_t(kStepThreads) * groups * kGroupElems);
-}
-
 // The launches of a pass of one-step workgroups, in order: of n_full full tiles
-// in 2^full_shift workgroups each, then of n_tail tail tiles in 2^tail_shift
-// each.  A launch has fewer than 2^32 lanes (HIP's limit for a dimension), and a
+// in 2^full_shift workgroups each, then of n_tail tails in 2^tail_shift each.  A
+// launch has fewer than 2^32 lanes (HIP's limit for a dimension), and a
 // plan's memory can hold more steps than that (an update from 2^36 elements,
-// 137 GB, on), so a pass over a larger plan is several launches over
-// consecutive tiles: launch(first tile, full tiles among its tiles, workgroups)
-// for each, until one fails.  `cap` (at least a tile's workgroups) is the most
-// of them in a launch.
+// 137 GB, on), so a pass over a larger plan is several launches:
+// launch(first full tile, full tiles, first tail, workgroups) for each, until
+// one fails.  `cap` (at least a tile's workgroups) is the most of them in a
+// launch.
 constexpr uint64_t kMaxStepGrid = (uint64_t(1) << 32) / kStepThreads - 1;
 
 template <class Launch>
@@ -1701,8 +1772,8 @@ int for_step_launches(uint64_t n_full, uint64_t n_tail, uint32_t full_shift, uin
         const uint64_t full = std::min(n_full - f, cap >> full_shift);
         const uint64_t room = f + full < n_full ? 0 : cap - (full << full_shift);
         const uint64_t tail = std::min(n_tail - t, room >> tail_shift);
-        const int rc = launch(f + t, full, static_cast<uint32_t>((full << full_shift) +
-                                                                 (tail << tail_shift)));
+        const int rc = launch(f, full, t, static_cast<uint32_t>((full << full_shift) +
+                                                                (tail << tail_shift)));
         if (rc != ES_OK) return rc;
         f += full;
         t += tail;
@@ -1710,30 +1781,45 @@ int for_step_launches(uint64_t n_full, uint64_t n_tail, uint32_t full_shift, uin
     return ES_OK;
 }
 
-// The same over a segment of a plan, with that part of its tiles, row maps and
-// master deltas (each null where the pass takes none): launch(tiles, full tiles,
-// row maps, deltas, workgroups).  A launch that fails is named by the call and
-// the kernel (formatted only then).
+// The arguments of one launch over part of a segment: its tiles, the full ones
+// among them, and their row maps and master deltas (each null where the pass
+// takes none).
+struct StepLaunch {
+    const TileDesc* tiles;
+    uint64_t n_full;
+    const DevRows* rows;
+    const uint64_t* mdelta;
+    StepShape shape;
+    dim3 grid;
+};
+
+// launch(StepLaunch) for each launch of a pass of `groups` groups per lane over
+// a segment.  One that fails is named by the call and the kernel (formatted only
+// then).
 template <class Launch>
-int launch_steps(const Segment& g, const StepShape& sh, const uint64_t* mdelta, const char* call,
-                 const char* kernel, Launch launch) {
+int launch_steps(const es_plan_t* p, const Segment& g, int groups, const uint64_t* mdelta,
+                 const char* call, const char* kernel, Launch launch) {
+    const uint32_t shift = full_tile_shift(p->tile_elems, groups);
     return for_step_launches(
-        g.n_full, g.n_tail, sh.full_shift, sh.tail_shift,
-        [&](uint64_t first, uint64_t full, uint32_t grid) {
-            launch(g.tiles + first, full, g.rows != nullptr ? g.rows + first : nullptr,
-                   mdelta != nullptr ? mdelta + first : nullptr, grid);
+        g.n_full, g.tails.n_steps, shift, 0,
+        [&](uint64_t first, uint64_t full, uint64_t step0, uint32_t grid) {
+            launch(StepLaunch{
+                g.tiles + first, full, g.rows != nullptr ? g.rows + first : nullptr,
+                mdelta != nullptr ? mdelta + first : nullptr,
+                StepShape{shift, static_cast<uint32_t>(step0), g.n_full - first, g.tails},
+                dim3(grid)});
             const hipError_t e = hipGetLastError();
             return e != hipSuccess ? hip_fail(e, std::string(call) + kernel + " launch") : ES_OK;
         });
 }
 
-// Groups per lane and step of the memory-bound passes: four, or two where
+// Groups per lane and step of the memory-bound passes in full tiles: four, or two where
 // four would leave wave slots empty (fewer than eight workgroups per CU, 16.8 M
 // elements).  A perturb pass in a graph, two and four groups: 1 M elements 2.8
 // and 3.4 us, 8.4 M 7.7 and 8.0, 16.8 M 12.2 and 12.0, 134 M 85.1 and 83.7, 537
 // M 346 and 332.
 bool four_groups(const es_plan_t* p, const Segment& g) {
-    const uint64_t elems = g.n_full * p->tile_elems + g.n_tail * g.tail_max;
+    const uint64_t elems = g.n_full * p->tile_elems;
     return elems >= uint64_t(p->cus) * 8 * (kStepThreads * 4 * kGroupElems);
 }
 
@@ -1771,16 +1857,13 @@ int launch_streams(es_plan_t* p, int streams, const uint64_t* seed, const double
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
         const bool four = four_groups(p, g);
-        const StepShape sh = plan_steps(p, g, four ? 4 : 2);
         const bool strided = g.rows != nullptr;
         const PerturbKernel kernel = four ? perturb_kernel<4>(streams, strided)
                                           : perturb_kernel<2>(streams, strided);
         const int rc = launch_steps(
-            g, sh, nullptr, "", "es_perturb_kernel",
-            [&](const DevTile* tiles, uint64_t n_full, const DevRows* rows, const uint64_t*,
-                uint32_t grid) {
-                hipLaunchKernelGGL(kernel, dim3(grid), dim3(kStepThreads), 0, s, tiles, n_full,
-                                   rows, st, sh);
+            p, g, four ? 4 : 2, nullptr, "", "es_perturb_kernel", [&](const StepLaunch& l) {
+                hipLaunchKernelGGL(kernel, l.grid, dim3(kStepThreads), 0, s, l.tiles, l.n_full,
+                                   l.rows, st, l.shape);
             });
         if (rc != ES_OK) return rc;
     }
@@ -1827,10 +1910,9 @@ QShape qstep_shape(const es_qplan_t* p) {
            p->numel / (2 * sh.full_steps * kQStepCodes) >= 3 * slots)
         sh.full_steps *= 2;
     while ((sh.full_steps * kQStepCodes << sh.full_shift) < sh.tile_elems) ++sh.full_shift;
-    const StepShape tail =
-        step_shape(p->n_tail, p->tail_max, sh.tile_elems, kQStepCodes * sh.full_steps);
-    sh.tail_shift = tail.tail_shift;
-    sh.tail_steps = tail.tail_steps * sh.full_steps;
+    const QTailShape tail = qtail_shape(p->n_tail, p->tail_max, kQStepCodes * sh.full_steps);
+    sh.tail_shift = tail.shift;
+    sh.tail_steps = tail.steps * sh.full_steps;
     return sh;
 }
 
@@ -1839,9 +1921,9 @@ int launch_qpass(es_qplan_t* p, QKind kind, const QPass& ps, hipStream_t s) {
     const QPassKernel kernel = qpass_kernel(kind, p->format);
     return for_step_launches(
         p->n_full, p->n_tail, sh.full_shift, sh.tail_shift,
-        [&](uint64_t first, uint64_t full, uint32_t grid) {
-            sh.first_full = std::min(first, p->n_full);
-            sh.first_tail = first - sh.first_full;
+        [&](uint64_t first, uint64_t full, uint64_t tail, uint32_t grid) {
+            sh.first_full = first;
+            sh.first_tail = tail;
             hipLaunchKernelGGL(kernel, dim3(grid), dim3(kStepThreads), 0, s, p->d_tab, full,
                                reinterpret_cast<const Member*>(p->d_scratch + kOffMembers),
                                reinterpret_cast<const UpdateHeader*>(p->d_scratch + kOffHeader),
@@ -2228,15 +2310,12 @@ int update_impl(const char* name, es_plan_t* plan, uint8_t* d_scratch, const uin
         // the segment's masters: the delta table runs parallel to the tiles
         const uint64_t* mdelta =
             master ? plan->d_master + (strided ? plan->n_full + plan->n_tail : 0) : nullptr;
-        const StepShape sh = plan_steps(plan, g, 2);
         rc = launch_steps(
-            g, sh, mdelta, name, ": es_update_kernel",
-            [&](const DevTile* tiles, uint64_t n_full, const DevRows* rows,
-                const uint64_t* delta, uint32_t grid) {
-                hipLaunchKernelGGL(kernel, dim3(grid), dim3(kStepThreads), 0, s, tiles, n_full,
-                                   rows, reinterpret_cast<const Member*>(d_scratch + kOffMembers),
+            plan, g, 2, mdelta, name, ": es_update_kernel", [&](const StepLaunch& l) {
+                hipLaunchKernelGGL(kernel, l.grid, dim3(kStepThreads), 0, s, l.tiles, l.n_full,
+                                   l.rows, reinterpret_cast<const Member*>(d_scratch + kOffMembers),
                                    reinterpret_cast<const UpdateHeader*>(d_scratch + kOffHeader),
-                                   rk, rst, delta, sh);
+                                   rk, rst, l.mdelta, l.shape);
             });
         if (rc != ES_OK) return rc;
     }
@@ -2363,12 +2442,12 @@ int finish_plan(const char* name, int device, uint32_t n_tensors, uint64_t numel
     const std::string nm(name);
     const uint64_t n_full = t.full.size(), n_tail = t.tail.size();
     const uint64_t n_rfull = t.rfull.size(), n_rtail = t.rtail.size();
-    std::vector<DevTile> tiles;
+    std::vector<TileDesc> tiles;
     tiles.reserve(n_full + n_tail + n_rfull + n_rtail);
-    tiles.insert(tiles.end(), t.full.begin(), t.full.end());
-    tiles.insert(tiles.end(), t.tail.begin(), t.tail.end());
-    tiles.insert(tiles.end(), t.rfull.begin(), t.rfull.end());
-    tiles.insert(tiles.end(), t.rtail.begin(), t.rtail.end());
+    for (const std::vector<DevTile>* v : {&t.full, &t.tail, &t.rfull, &t.rtail})
+        for (const DevTile& d : *v) tiles.push_back(tile_desc(d));
+    const TailIndex tails = index_tails(tiles.data() + n_full, n_tail);
+    const TailIndex rtails = index_tails(tiles.data() + n_full + n_tail + n_rfull, n_rtail);
     std::vector<DevRows> rows;
     rows.reserve(n_rfull + n_rtail);
     rows.insert(rows.end(), t.rows_full.begin(), t.rows_full.end());
@@ -2396,14 +2475,9 @@ int finish_plan(const char* name, int device, uint32_t n_tensors, uint64_t numel
     p->grid_sum = grid(n_full, n_tail, wg_update);
     p->grid_sum_rows = grid(n_rfull, n_rtail, wg_update);
     p->cus = cus;
-    auto longest = [](const std::vector<DevTile>& v) {
-        uint64_t m = 0;
-        for (const DevTile& d : v) m = std::max(m, d.limit - d.elem0);
-        return m;
-    };
-    p->tail_max = longest(t.tail);
-    p->rtail_max = longest(t.rtail);
-    const size_t tile_bytes = sizeof(DevTile) * std::max<size_t>(tiles.size(), 1);
+    p->tails = tails;
+    p->rtails = rtails;
+    const size_t tile_bytes = sizeof(TileDesc) * std::max<size_t>(tiles.size(), 1);
     const size_t rows_bytes = sizeof(DevRows) * rows.size();
     e = hipMalloc(reinterpret_cast<void**>(&p->d_tiles), tile_bytes + rows_bytes);
     if (e != hipSuccess) { delete p; return fail(ES_ERR_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e)); }
@@ -2417,7 +2491,7 @@ int finish_plan(const char* name, int device, uint32_t n_tensors, uint64_t numel
         return fail(ES_ERR_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
     }
     if (!tiles.empty())
-        e = hipMemcpy(p->d_tiles, tiles.data(), sizeof(DevTile) * tiles.size(), hipMemcpyHostToDevice);
+        e = hipMemcpy(p->d_tiles, tiles.data(), sizeof(TileDesc) * tiles.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && !rows.empty())
         e = hipMemcpy(p->d_rows, rows.data(), rows_bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(p->d_scratch, 0, kScratchBytes);
@@ -2748,10 +2822,10 @@ int es_plan_set_master(es_plan_t* plan, void* const* masters, uint32_t n) try {
     // each tile's owner: the tensor whose bf16 bytes hold the tile's first
     // element (tensors do not overlap), found by bisection over their starts
     const uint64_t n_tiles = plan->n_full + plan->n_tail + plan->n_rfull + plan->n_rtail;
-    std::vector<DevTile> tiles(n_tiles);
+    std::vector<TileDesc> tiles(n_tiles);
     hipError_t e = hipSuccess;
     if (n_tiles > 0)
-        e = hipMemcpy(tiles.data(), plan->d_tiles, sizeof(DevTile) * n_tiles,
+        e = hipMemcpy(tiles.data(), plan->d_tiles, sizeof(TileDesc) * n_tiles,
                       hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(e, "es_plan_set_master: tile table read-back");
     std::vector<std::pair<uintptr_t, uint32_t>> starts;      // (bf16 start, owner)
@@ -2808,16 +2882,14 @@ int es_perturb_master(es_plan_t* plan, uint64_t seed, int32_t sign, float sigma,
             const Segment& g = seg[k];
             const bool strided = g.rows != nullptr;
             const bool four = four_groups(plan, g);
-            const StepShape sh = plan_steps(plan, g, four ? 4 : 2);
             const ApplyMasterKernel kernel = four ? apply_master_kernel<4>(strided)
                                                   : apply_master_kernel<2>(strided);
             rc = launch_steps(
-                g, sh, plan->d_master + (strided ? plan->n_full + plan->n_tail : 0),
-                "es_perturb_master", ": es_apply_master_kernel",
-                [&](const DevTile* tiles, uint64_t n_full, const DevRows* rows,
-                    const uint64_t* delta, uint32_t grid) {
-                    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kStepThreads), 0, s, tiles,
-                                       n_full, rows, st, delta, sh);
+                plan, g, four ? 4 : 2,
+                plan->d_master + (strided ? plan->n_full + plan->n_tail : 0),
+                "es_perturb_master", ": es_apply_master_kernel", [&](const StepLaunch& l) {
+                    hipLaunchKernelGGL(kernel, l.grid, dim3(kStepThreads), 0, s, l.tiles,
+                                       l.n_full, l.rows, st, l.mdelta, l.shape);
                 });
             if (rc != ES_OK) return rc;
         }
@@ -2835,18 +2907,15 @@ int es_perturb_master(es_plan_t* plan, uint64_t seed, int32_t sign, float sigma,
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
         const bool strided = g.rows != nullptr;
-        const StepShape sh = plan_steps(plan, g, 2);
         const UpdateKernel kernel = update_master_kernel(strided, true);
         rc = launch_steps(
-            g, sh, plan->d_master + (strided ? plan->n_full + plan->n_tail : 0),
-            "es_perturb_master", ": es_update_kernel",
-            [&](const DevTile* tiles, uint64_t n_full, const DevRows* rows,
-                const uint64_t* delta, uint32_t grid) {
+            plan, g, 2, plan->d_master + (strided ? plan->n_full + plan->n_tail : 0),
+            "es_perturb_master", ": es_update_kernel", [&](const StepLaunch& l) {
                 hipLaunchKernelGGL(
-                    kernel, dim3(grid), dim3(kStepThreads), 0, s, tiles, n_full, rows,
+                    kernel, l.grid, dim3(kStepThreads), 0, s, l.tiles, l.n_full, l.rows,
                     reinterpret_cast<const Member*>(plan->d_scratch + kOffMembers),
                     reinterpret_cast<const UpdateHeader*>(plan->d_scratch + kOffHeader),
-                    RoundKey{0u, 0u}, RestoreArg{0u, 0.0f}, delta, sh);
+                    RoundKey{0u, 0u}, RestoreArg{0u, 0.0f}, l.mdelta, l.shape);
             });
         if (rc != ES_OK) return rc;
     }
@@ -2859,7 +2928,7 @@ uint64_t es_plan_device_bytes(const es_plan_t* plan) {
     if (plan == nullptr) return 0;
     const uint64_t tiles =
         std::max<uint64_t>(plan->n_full + plan->n_tail + plan->n_rfull + plan->n_rtail, 1);
-    return sizeof(DevTile) * tiles + sizeof(DevRows) * (plan->n_rfull + plan->n_rtail) +
+    return sizeof(TileDesc) * tiles + sizeof(DevRows) * (plan->n_rfull + plan->n_rtail) +
            kScratchBytes + (plan->d_master != nullptr ? sizeof(uint64_t) * tiles : 0);
 }
 uint64_t es_plan_tiles(const es_plan_t* plan) {
@@ -3122,14 +3191,11 @@ int es_stream_pass(es_plan_t* plan, es_stream_t stream) {
     for (int k = 0; k < n_seg; ++k) {
         const Segment& g = seg[k];
         const bool four = four_groups(plan, g);
-        const StepShape sh = plan_steps(plan, g, four ? 4 : 2);
         const int rc2 = launch_steps(
-            g, sh, nullptr, "", "es_stream_kernel",
-            [&](const DevTile* tiles, uint64_t n_full, const DevRows*, const uint64_t*,
-                uint32_t grid) {
-                hipLaunchKernelGGL(four ? es_stream_kernel<4> : es_stream_kernel<2>, dim3(grid),
+            plan, g, four ? 4 : 2, nullptr, "", "es_stream_kernel", [&](const StepLaunch& l) {
+                hipLaunchKernelGGL(four ? es_stream_kernel<4> : es_stream_kernel<2>, l.grid,
                                    dim3(kStepThreads), 0, static_cast<hipStream_t>(stream),
-                                   tiles, n_full, 0u, sh);
+                                   l.tiles, l.n_full, 0u, l.shape);
             });
         if (rc2 != ES_OK) return rc2;
     }

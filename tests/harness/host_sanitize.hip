@@ -351,34 +351,42 @@ void test_qblock_geometry(std::mt19937_64& rng) {
 }
 
 // The launches of the one-step workgroups: the order over the XCDs is a
-// permutation, every element of every tile is taken by exactly one workgroup
-// (also when a pass is cut into several launches), and every launch stays below
-// 2^32 lanes whatever the plan's size.
+// permutation, every step of every tile is taken by exactly one workgroup and no
+// workgroup is without one, whatever the tail tiles' lengths (also when a pass
+// is cut into several launches), and every launch stays below 2^32 lanes
+// whatever the plan's size.
 struct StepCover {
-    uint64_t n_full, tile_elems, step_elems;
-    std::vector<uint64_t> tails;                 // their lengths
-    // steps of every tile taken so far, by the kernels' own item map
-    std::vector<std::vector<uint8_t>> taken;
-    bool ok = true;
-    uint64_t steps_of(uint64_t tile) const {
-        const uint64_t n = tile < n_full ? tile_elems : tails[tile - n_full];
-        return (n + step_elems - 1) / step_elems;
+    uint64_t n_full;
+    uint32_t full_shift;
+    std::vector<TileDesc> tiles;                 // the full ones, then the tails
+    TailIndex index;
+    std::vector<std::vector<uint8_t>> taken;     // steps of every tile taken so far
+    bool ok;
+    StepCover(uint64_t full, uint32_t tile_elems, int groups, const std::vector<uint32_t>& tails)
+        : n_full(full), full_shift(full_tile_shift(tile_elems, groups)) {
+        for (uint64_t t = 0; t < full; ++t) tiles.push_back(TileDesc{nullptr, 0, tile_elems, 0, 0, 0});
+        for (uint32_t n : tails) tiles.push_back(TileDesc{nullptr, 0, n, 0, 0, 0});
+        index = index_tails(tiles.data() + full, tails.size());
+    }
+    uint64_t steps_of(uint64_t t) const {
+        return t < n_full ? uint64_t(1) << full_shift : (tiles[t].len + kTailStep - 1) / kTailStep;
     }
     void reset() {
-        taken.assign(n_full + tails.size(), {});
+        ok = true;
+        taken.assign(tiles.size(), {});
         for (uint64_t t = 0; t < taken.size(); ++t) taken[t].assign(steps_of(t), 0);
     }
-    void launch(uint64_t first, uint64_t full, uint32_t grid, const StepShape& sh) {
+    // the launch as launch_steps passes it to the kernels
+    void launch(uint64_t first, uint64_t full, uint64_t step0, uint32_t grid) {
+        const StepShape sh{full_shift, static_cast<uint32_t>(step0), n_full - first, index};
         for (uint64_t i = 0; i < grid; ++i) {
-            const StepItem it = step_item(i, full, sh);
+            const StepItem it = step_item(i, full, sh, tiles.data() + first);
             const uint64_t tile = first + it.tile;
-            if (tile >= taken.size() || it.full != (tile < n_full)) { ok = false; continue; }
-            const uint32_t n = it.full ? 1u : sh.tail_steps;
-            for (uint32_t k = 0; k < n; ++k) {
-                const uint64_t step = uint64_t(it.part) * n + k;
-                if (it.full && step >= taken[tile].size()) ok = false;
-                if (step < taken[tile].size()) ++taken[tile][step];   // beyond a tail's end: none
-            }
+            if (tile >= taken.size() || it.full != (tile < n_full) ||
+                it.part >= taken[tile].size())
+                ok = false;
+            else
+                ++taken[tile][it.part];
         }
     }
     bool once() const {
@@ -401,30 +409,40 @@ void test_step_launches(std::mt19937_64& rng) {
         check(ok, "step launches: the order over the XCDs is a permutation");
     }
     for (int trial = 0; trial < 300; ++trial) {
-        StepCover c;
-        c.tile_elems = trial % 3 == 0 ? 8192 : 65536;
-        c.step_elems = trial % 2 == 0 ? 4096 : 8192;
-        c.n_full = trial % 5 == 0 ? 0 : rng() % 300;
+        const uint32_t tile = trial % 3 == 0 ? 8192 : 65536;
+        const uint64_t n_full = trial % 5 == 0 ? 0 : rng() % 300;
         const uint64_t n_tail = trial % 7 == 0 ? 0 : rng() % (trial % 11 == 0 ? 70000 : 300);
-        const uint64_t longest = 1 + rng() % (trial % 4 == 0 ? 64 : c.tile_elems);
-        uint64_t tail_max = 0;
+        // tails of one length or of any, or short ones with longer ones among
+        // them or at one end
+        std::vector<uint32_t> tails;
+        const int kind = trial % 6;
+        const uint32_t same = 1 + rng() % tile;
         for (uint64_t t = 0; t < n_tail; ++t) {
-            c.tails.push_back(1 + rng() % longest);
-            tail_max = std::max(tail_max, c.tails.back());
+            const bool longer = kind == 2 ? rng() % 50 == 0
+                                : kind == 3 ? t + 1 == n_tail
+                                : kind == 4 ? t == 0
+                                            : t < n_tail / 2;
+            tails.push_back(kind == 0   ? same
+                            : kind == 1 ? 1 + rng() % tile
+                            : longer    ? tile - rng() % 4096
+                                        : 1 + rng() % 64);
         }
-        const StepShape sh = step_shape(n_tail, tail_max, c.tile_elems, c.step_elems);
+        StepCover c(n_full, tile, trial % 2 == 0 ? 2 : 4, tails);
+        uint64_t needed = 0;
+        for (uint64_t t = 0; t < c.tiles.size(); ++t) needed += c.steps_of(t);
         for (const uint64_t cap : {kMaxStepGrid, uint64_t(1000), uint64_t(16)}) {
             c.reset();
             uint64_t launches = 0, items = 0;
-            for_step_launches(c.n_full, n_tail, sh.full_shift, sh.tail_shift,
-                              [&](uint64_t first, uint64_t full, uint32_t grid) {
+            for_step_launches(n_full, c.index.n_steps, c.full_shift, 0,
+                              [&](uint64_t first, uint64_t full, uint64_t step0, uint32_t grid) {
                                   check(grid > 0 && grid <= cap, "step launches: grid");
-                                  c.launch(first, full, grid, sh);
+                                  c.launch(first, full, step0, grid);
                                   ++launches;
                                   items += grid;
                                   return ES_OK;
                               }, cap);
             check(c.once(), "step launches: every step once");
+            check(items == needed, "step launches: no workgroup without a step");
             check(cap != kMaxStepGrid || launches <= 1, "step launches: one for a small plan");
             check(launches >= items / cap, "step launches: cut at the cap");
         }
@@ -435,27 +453,26 @@ void test_step_launches(std::mt19937_64& rng) {
                                  (uint64_t(1) << 36) + 65536, uint64_t(1) << 37,
                                  uint64_t(160) << 30})
         for (const uint64_t tile : {8192ull, 65536ull})
-            for (const uint64_t step : {4096ull, 8192ull})
+            for (const int groups : {2, 4})
                 for (const bool aligned : {true, false}) {
                     const uint64_t n_full = aligned ? elems / tile : 0;
-                    const uint64_t n_tail = aligned ? 1 : (elems + tile - 1) / tile;
-                    const StepShape sh = step_shape(n_tail, tile, tile, step);
+                    const uint64_t n_steps = aligned ? 3 : (elems + kTailStep - 1) / kTailStep;
+                    const uint32_t shift = full_tile_shift(tile, groups);
                     uint64_t f = 0, t = 0;
                     for_step_launches(
-                        n_full, n_tail, sh.full_shift, sh.tail_shift,
-                        [&](uint64_t first, uint64_t full, uint32_t grid) {
+                        n_full, n_steps, shift, 0,
+                        [&](uint64_t first, uint64_t full, uint64_t step0, uint32_t grid) {
                             check(uint64_t(grid) * kStepThreads < (uint64_t(1) << 32),
                                   "step launches: below 2^32 lanes");
-                            check(first == f + t, "step launches: consecutive tiles");
-                            const uint64_t tail_items = grid - (full << sh.full_shift);
-                            check(tail_items % (1u << sh.tail_shift) == 0 &&
-                                      (tail_items == 0 || f + full == n_full),
-                                  "step launches: whole tiles, the full ones first");
+                            check(first == f && step0 == t, "step launches: in order");
+                            const uint64_t tail_items = grid - (full << shift);
+                            check(tail_items == 0 || f + full == n_full,
+                                  "step launches: the full tiles first");
                             f += full;
-                            t += tail_items >> sh.tail_shift;
+                            t += tail_items;
                             return ES_OK;
                         });
-                    check(f == n_full && t == n_tail, "step launches: every tile");
+                    check(f == n_full && t == n_steps, "step launches: every step");
                 }
     // quantized plans, with the fewest and the most codes per workgroup
     for (const int threads : {256, 1024})
@@ -472,17 +489,17 @@ void test_step_launches(std::mt19937_64& rng) {
             check((uint64_t(sh.full_steps) * kQStepCodes << sh.full_shift) == tile &&
                       (uint64_t(sh.tail_steps) * kQStepCodes << sh.tail_shift) >= q.tail_max,
                   "step launches: a quantized tile's steps");
-            uint64_t next = 0;
+            uint64_t f = 0, t = 0;
             for_step_launches(q.n_full, q.n_tail, sh.full_shift, sh.tail_shift,
-                              [&](uint64_t first, uint64_t full, uint32_t grid) {
+                              [&](uint64_t first, uint64_t full, uint64_t tail, uint32_t grid) {
                                   check(uint64_t(grid) * kStepThreads < (uint64_t(1) << 32) &&
-                                            first == next,
+                                            first == f && tail == t,
                                         "step launches: quantized");
-                                  next += full + ((grid - (full << sh.full_shift)) >>
-                                                  sh.tail_shift);
+                                  f += full;
+                                  t += (grid - (full << sh.full_shift)) >> sh.tail_shift;
                                   return ES_OK;
                               });
-            check(next == q.n_full + q.n_tail, "step launches: every quantized tile");
+            check(f == q.n_full && t == q.n_tail, "step launches: every quantized tile");
         }
 }
 

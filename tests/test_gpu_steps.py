@@ -2,8 +2,8 @@
 8-element groups, a workgroup's step of 4096 or 8192 elements, the 65
 536-element tile), at bases that are 16-byte aligned and not: the update in
 its forms, perturb, swap and a member applied from masters against the oracle,
-the bytes around each tensor untouched, and a plan of so many tiny tensors
-that its tail tiles are not cut into steps."""
+the bytes around each tensor untouched, and a plan of very many tiny tensors
+and a long one."""
 import numpy as np
 import pytest
 import torch
@@ -139,8 +139,8 @@ def test_restore_update_and_masters_at_the_edges(pad):
 
 
 def test_many_tiny_tensors_and_a_long_one():
-    """Above 65 536 tail tiles the tail items are whole tiles, whose longest
-    then takes sixteen steps."""
+    """Tail tiles of one step each, among them two of several: each step's
+    workgroup finds its tile."""
     n_tiny, big = 66_000, 150_001
     bits = wl.random_bf16_bits(8 * n_tiny + big, 77)
     flat = to_device(bits)
