@@ -66,7 +66,8 @@ struct DevQTensor {
     uint32_t tensor_id;
     uint32_t magic;
     uint32_t shift;
-    uint32_t n_tensors;                         // entries before the sentinel (same in all)
+    uint32_t first_step;                        // steps of the tails before this one's (a pass's
+                                                //   workgroups over the tails, numbered in order)
     uint32_t aligned16;                         // base 16-byte aligned
     uint32_t skip;                              // 0, or whole-tensor codes between block rows
     uint32_t cmagic;                            // j / cols (read only when skip > 0)
@@ -97,8 +98,8 @@ __device__ __forceinline__ uint32_t qnoise_index(const QTileRef& r, uint32_t e) 
     return n;
 }
 
-// The entry that owns global tile `tile`: the last one, of the n before the
-// sentinel, whose first(i) is not beyond it (first() does not decrease, and
+// The entry that owns global tile (or tail step) `tile`: the last one, of the n
+// before the sentinel, whose first(i) is not beyond it (first() does not decrease, and
 // first(0) = 0).  One load per 64-fold step: the lanes of a wave probe the
 // range in parallel, so a workgroup that starts anywhere in the list finds its
 // tensor in two round trips for up to 4096 tensors.  All lanes must be active.
@@ -134,6 +135,15 @@ __device__ __forceinline__ QTileRef qlocate_tail(const DevQTensor* __restrict__ 
     const uint64_t n_full = tab[t + 1].first_full - tab[t].first_full;
     return qtile_ref(tab[t],
                      static_cast<uint32_t>(n_full + tile - tab[t].first_tail) * tile_elems);
+}
+
+// Tail step `step` of the plan, of part_codes codes: from its first code on.
+__device__ __forceinline__ QTileRef qlocate_step(const DevQTensor* __restrict__ tab, uint32_t n,
+                                                 uint32_t step, uint32_t tile_elems,
+                                                 uint32_t part_codes) {
+    const uint32_t t = find_tensor(step, n, [tab](uint32_t i) { return tab[i].first_step; });
+    const uint32_t n_full = static_cast<uint32_t>(tab[t + 1].first_full - tab[t].first_full);
+    return qtile_ref(tab[t], n_full * tile_elems + (step - tab[t].first_step) * part_codes);
 }
 
 typedef uint32_t q32x4_t __attribute__((ext_vector_type(4)));

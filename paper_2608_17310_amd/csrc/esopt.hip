@@ -1494,15 +1494,18 @@ __device__ __forceinline__ void qstep_group(const esq::QTileRef& r, uint32_t e,
 // A pass over the whole quantized parameter list: perturb / restore (one
 // inline member, draws from its own noise words), swap (two inline members)
 // or the update (member table and header written by es_prepare_kernel, draws
-// of domain 1 under the rounding seed).  A workgroup takes full_steps (tail_
-// steps) steps of 256 lanes x 16 codes of one tile of tile_elems codes,
-// 2^full_shift (2^tail_shift) workgroups per tile.
-// first_full and first_tail are the launch's first full and tail tile.
+// of domain 1 under the rounding seed).  A workgroup takes `steps` steps of 256
+// lanes x 16 codes, 2^full_shift workgroups per full tile of tile_elems codes; a
+// tensor's codes beyond its full tiles have as many workgroups as they need, so
+// that short tensors leave none without work (10 000 tensors of 64 codes and one
+// of 60 000: swap 24 us, update of 4 36; with every tail cut alike, for the
+// longest, 155 and 205).
+// first_full and first_step are the launch's first full tile and tail workgroup.
 struct QShape {
     uint32_t tile_elems, n_tensors;
-    uint32_t full_shift, full_steps;
-    uint32_t tail_shift, tail_steps;
-    uint64_t first_full, first_tail;
+    uint32_t full_shift, steps;
+    uint64_t first_full;
+    uint32_t first_step;
 };
 constexpr uint32_t kQStepCodes = kStepThreads * esq::kQGroup;
 
@@ -1521,23 +1524,20 @@ __global__ __launch_bounds__(kStepThreads) void es_qpass_kernel(
         const uint32_t part = static_cast<uint32_t>(i) & ((1u << sh.full_shift) - 1u);
         const esq::QTileRef r = esq::qlocate_full(
             tab, sh.n_tensors, sh.first_full + (i >> sh.full_shift), sh.tile_elems);
-        const uint32_t e0 = r.elem0 + part * sh.full_steps * kQStepCodes +
-                            threadIdx.x * esq::kQGroup;
+        const uint32_t e0 = r.elem0 + part * sh.steps * kQStepCodes + threadIdx.x * esq::kQGroup;
 #pragma unroll 1
-        for (uint32_t k = 0; k < sh.full_steps; ++k)
+        for (uint32_t k = 0; k < sh.steps; ++k)
             qstep_group<true, kKind, kFmt>(r, e0 + k * kQStepCodes, members, n_members, ps);
         return;
     }
-    const uint64_t j = i - full_items;
-    const uint32_t part = static_cast<uint32_t>(j) & ((1u << sh.tail_shift) - 1u);
-    const esq::QTileRef r = esq::qlocate_tail(
-        tab, sh.n_tensors, sh.first_tail + (j >> sh.tail_shift), sh.tile_elems);
-    const uint32_t e0 = r.elem0 + part * sh.tail_steps * kQStepCodes + threadIdx.x * esq::kQGroup;
-    const uint32_t end = min(r.numel - r.elem0, sh.tile_elems) + r.elem0;   // the tile's
+    const esq::QTileRef r =
+        esq::qlocate_step(tab, sh.n_tensors, static_cast<uint32_t>(i - full_items) + sh.first_step,
+                          sh.tile_elems, sh.steps * kQStepCodes);
+    const uint32_t e0 = r.elem0 + threadIdx.x * esq::kQGroup;
 #pragma unroll 1
-    for (uint32_t k = 0; k < sh.tail_steps; ++k) {
+    for (uint32_t k = 0; k < sh.steps; ++k) {
         const uint32_t e = e0 + k * kQStepCodes;
-        if (e >= end) return;
+        if (e >= r.numel) return;
         qstep_group<false, kKind, kFmt>(r, e, members, n_members, ps);
     }
 }
@@ -1651,8 +1651,8 @@ struct es_qplan {
     uint64_t numel = 0;
     uint64_t n_full = 0;
     uint64_t n_tail = 0;
-    uint64_t tail_max = 0;          // codes of the longest tail tile
-    int cus = 0;                    // compute units of the device
+    uint32_t steps = 1;             // steps per workgroup of a pass
+    uint32_t n_tail_steps = 0;      // its workgroups over the tail tiles
     uint32_t grid = 0;              // workgroups of the checksum launch
     int threads = kDefaultThreads;
     int groups = kDefaultQGroups;   // 16-code groups per lane per tile
@@ -1737,43 +1737,25 @@ TailIndex index_tails(TileDesc* tails, uint64_t n) {
     return ix;
 }
 
-// How the tail tiles of a quantized plan, of at most tail_max codes, are cut:
-// for the longest one into parts of step codes; where there are
-// so many of them (tens of thousands of tiny tensors) that they fill the chip
-// several times over, they are cut less and a workgroup goes on to the next
-// step instead, since the empty workgroups of the short ones only cost.
-struct QTailShape {
-    uint32_t shift, steps;
-};
-QTailShape qtail_shape(uint64_t n_tail, uint64_t tail_max, uint64_t step) {
-    constexpr uint64_t kManyTails = 65536;
-    QTailShape sh{};
-    while ((step << sh.shift) < tail_max && (n_tail << sh.shift) < kManyTails) ++sh.shift;
-    const uint64_t part = step << sh.shift;
-    sh.steps = static_cast<uint32_t>(std::max<uint64_t>((tail_max + part - 1) / part, 1));
-    return sh;
-}
-
-// The launches of a pass of one-step workgroups, in order: of n_full full tiles
-// in 2^full_shift workgroups each, then of n_tail tails in 2^tail_shift each.  A
-// launch has fewer than 2^32 lanes (HIP's limit for a dimension), and a
+// The launches of a pass, in order: of n_full full tiles in 2^full_shift
+// workgroups each, then of n_steps tail steps in a workgroup each.  A launch has fewer than 2^32 lanes (HIP's limit for a dimension), and a
 // plan's memory can hold more steps than that (an update from 2^36 elements,
 // 137 GB, on), so a pass over a larger plan is several launches:
-// launch(first full tile, full tiles, first tail, workgroups) for each, until
-// one fails.  `cap` (at least a tile's workgroups) is the most of them in a
+// launch(first full tile, full tiles, first tail step, workgroups) for each,
+// until one fails.  `cap` (at least a tile's workgroups) is the most of them in a
 // launch.
 constexpr uint64_t kMaxStepGrid = (uint64_t(1) << 32) / kStepThreads - 1;
 
 template <class Launch>
-int for_step_launches(uint64_t n_full, uint64_t n_tail, uint32_t full_shift, uint32_t tail_shift,
-                      Launch launch, uint64_t cap = kMaxStepGrid) {
+int for_step_launches(uint64_t n_full, uint64_t n_steps, uint32_t full_shift, Launch launch,
+                      uint64_t cap = kMaxStepGrid) {
     uint64_t f = 0, t = 0;
-    while (f < n_full || t < n_tail) {
+    while (f < n_full || t < n_steps) {
         const uint64_t full = std::min(n_full - f, cap >> full_shift);
         const uint64_t room = f + full < n_full ? 0 : cap - (full << full_shift);
-        const uint64_t tail = std::min(n_tail - t, room >> tail_shift);
-        const int rc = launch(f, full, t, static_cast<uint32_t>((full << full_shift) +
-                                                                (tail << tail_shift)));
+        const uint64_t tail = std::min(n_steps - t, room);
+        const int rc = launch(f, full, static_cast<uint32_t>(t),
+                              static_cast<uint32_t>((full << full_shift) + tail));
         if (rc != ES_OK) return rc;
         f += full;
         t += tail;
@@ -1801,12 +1783,12 @@ int launch_steps(const es_plan_t* p, const Segment& g, int groups, const uint64_
                  const char* call, const char* kernel, Launch launch) {
     const uint32_t shift = full_tile_shift(p->tile_elems, groups);
     return for_step_launches(
-        g.n_full, g.tails.n_steps, shift, 0,
-        [&](uint64_t first, uint64_t full, uint64_t step0, uint32_t grid) {
+        g.n_full, g.tails.n_steps, shift,
+        [&](uint64_t first, uint64_t full, uint32_t step0, uint32_t grid) {
             launch(StepLaunch{
                 g.tiles + first, full, g.rows != nullptr ? g.rows + first : nullptr,
                 mdelta != nullptr ? mdelta + first : nullptr,
-                StepShape{shift, static_cast<uint32_t>(step0), g.n_full - first, g.tails},
+                StepShape{shift, step0, g.n_full - first, g.tails},
                 dim3(grid)});
             const hipError_t e = hipGetLastError();
             return e != hipSuccess ? hip_fail(e, std::string(call) + kernel + " launch") : ES_OK;
@@ -1895,35 +1877,42 @@ int check_qdevice(const es_qplan_t* p) {
     return ES_OK;
 }
 
-// The steps of a quantized plan: up to eight per workgroup (it looks its tensor
-// up once), as many as leave three workgroups per slot of the chip.  int8 swap
+// Steps per workgroup of a quantized pass: up to eight (it looks its tensor up
+// once), as many as leave three workgroups per slot of the chip.  int8 swap
 // over the 0.5B-shaped set 557 us with one, 524, 510 and 506 with two, four and
 // eight; fp8 update of 8 over an eighth of it 198, 195 and 204 us with one, two
 // and four.
-QShape qstep_shape(const es_qplan_t* p) {
-    QShape sh{};
-    sh.tile_elems = static_cast<uint32_t>(p->threads) * p->groups * esq::kQGroup;
-    sh.n_tensors = p->n_tensors;
-    const uint64_t slots = uint64_t(p->cus) * 8;
-    sh.full_steps = 1;
-    while (sh.full_steps < 8 && 2 * sh.full_steps * kQStepCodes <= sh.tile_elems &&
-           p->numel / (2 * sh.full_steps * kQStepCodes) >= 3 * slots)
-        sh.full_steps *= 2;
-    while ((sh.full_steps * kQStepCodes << sh.full_shift) < sh.tile_elems) ++sh.full_shift;
-    const QTailShape tail = qtail_shape(p->n_tail, p->tail_max, kQStepCodes * sh.full_steps);
-    sh.tail_shift = tail.shift;
-    sh.tail_steps = tail.steps * sh.full_steps;
-    return sh;
+uint32_t qsteps_per_workgroup(uint64_t numel, uint64_t tile_elems, int cus) {
+    const uint64_t slots = uint64_t(cus) * 8;
+    uint32_t steps = 1;
+    while (steps < 8 && 2 * steps * kQStepCodes <= tile_elems &&
+           numel / (2 * steps * kQStepCodes) >= 3 * slots)
+        steps *= 2;
+    return steps;
+}
+
+// The tail steps' numbers, of part_codes codes, in the n entries of a table (and
+// its sentinel).
+void index_qtails(esq::DevQTensor* tab, uint32_t n, uint64_t tile_elems, uint64_t part_codes) {
+    uint64_t steps = 0;
+    for (uint32_t i = 0; i <= n; ++i) {
+        tab[i].first_step = static_cast<uint32_t>(steps);
+        if (i == n) break;
+        const uint64_t tail = tab[i].numel - (tab[i + 1].first_full - tab[i].first_full) * tile_elems;
+        steps += (tail + part_codes - 1) / part_codes;
+    }
 }
 
 int launch_qpass(es_qplan_t* p, QKind kind, const QPass& ps, hipStream_t s) {
-    QShape sh = qstep_shape(p);
+    const uint32_t tile_elems = static_cast<uint32_t>(p->threads) * p->groups * esq::kQGroup;
+    QShape sh{tile_elems, p->n_tensors, 0u, p->steps, 0u, 0u};
+    while ((p->steps * kQStepCodes << sh.full_shift) < tile_elems) ++sh.full_shift;
     const QPassKernel kernel = qpass_kernel(kind, p->format);
     return for_step_launches(
-        p->n_full, p->n_tail, sh.full_shift, sh.tail_shift,
-        [&](uint64_t first, uint64_t full, uint64_t tail, uint32_t grid) {
+        p->n_full, p->n_tail_steps, sh.full_shift,
+        [&](uint64_t first, uint64_t full, uint32_t step0, uint32_t grid) {
             sh.first_full = first;
-            sh.first_tail = tail;
+            sh.first_step = step0;
             hipLaunchKernelGGL(kernel, dim3(grid), dim3(kStepThreads), 0, s, p->d_tab, full,
                                reinterpret_cast<const Member*>(p->d_scratch + kOffMembers),
                                reinterpret_cast<const UpdateHeader*>(p->d_scratch + kOffHeader),
@@ -2576,7 +2565,7 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
     std::vector<esq::DevQTensor> tab(n_tensors + 1);
     std::unordered_map<uint32_t, uint32_t> ids;
     std::vector<std::pair<uintptr_t, uintptr_t>> ranges;
-    uint64_t n_full = 0, n_tail = 0, numel = 0, tail_max = 0;
+    uint64_t n_full = 0, n_tail = 0, numel = 0;
     for (uint32_t i = 0; i < n_tensors; ++i) {
         const QSpec& t = specs[i];
         const std::string where = nm + ": " + kind + " " + std::to_string(i);
@@ -2596,11 +2585,10 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
         if (t.skip != 0) row_divisor(static_cast<uint32_t>(t.cols), cmagic, cshift);
         tab[i] = esq::DevQTensor{static_cast<int8_t*>(t.data), t.scales,
                                  static_cast<uint32_t>(t.numel), static_cast<uint32_t>(t.n0),
-                                 n_full, n_tail, t.row, t.tensor_id, magic, shift, n_tensors,
+                                 n_full, n_tail, t.row, t.tensor_id, magic, shift, 0u,
                                  (a % 16 == 0) ? 1u : 0u, static_cast<uint32_t>(t.skip), cmagic,
                                  cshift, 0u};
         if (t.numel > 0) ranges.emplace_back(a, a + t.numel);
-        tail_max = std::max(tail_max, std::min(tile_elems, t.numel - full * tile_elems));
         n_full += full;
         n_tail += tail;
         numel += t.numel;
@@ -2610,7 +2598,7 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
         if (ranges[i].first < ranges[i - 1].second)
             return fail(ES_ERR_INVALID_ARG, nm + ": " + kind + "s overlap in memory");
     tab[n_tensors] = esq::DevQTensor{nullptr, nullptr, 0u, 0u, n_full, n_tail, 0u, 0xFFFFFFFFu,
-                                     0u, 0u, n_tensors, 0u, 0u, 0u, 0u, 0u};
+                                     0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
 
     int device = -1;
     int rc = current_device(&device);
@@ -2624,15 +2612,17 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
             rc = check_access(t.scales, 4 * n_scales, device, where + " scales");
     }
     if (rc != ES_OK) return rc;
+    int cus = 0;
+    hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
+    if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
+    const uint32_t steps = qsteps_per_workgroup(numel, tile_elems, cus);
+    index_qtails(tab.data(), n_tensors, tile_elems, uint64_t(steps) * kQStepCodes);
     es_qplan_t* p = new (std::nothrow) es_qplan_t;
     if (p == nullptr) return fail(ES_ERR_NOMEM, nm + ": host allocation");
     p->device = device;
-    hipError_t e = hipSuccess;
-    int cus = 0;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
-    if (e != hipSuccess) { delete p; return hip_fail(e, "hipDeviceGetAttribute"); }
     const int wg = env_int("ESOPT_UPDATE_WG_PER_CU", kDefaultUpdateWgPerCu, 1, 32);
-    p->cus = cus;
+    p->steps = steps;
+    p->n_tail_steps = tab[n_tensors].first_step;
     p->threads = threads;
     p->groups = groups;
     p->format = static_cast<int>(format);
@@ -2640,7 +2630,6 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
     p->numel = numel;
     p->n_full = n_full;
     p->n_tail = n_tail;
-    p->tail_max = tail_max;
     const uint64_t cap = std::max<uint64_t>(std::max(n_full, n_tail), 1);
     p->grid = static_cast<uint32_t>(std::min<uint64_t>(cap, uint64_t(cus) * wg));
     e = hipMalloc(reinterpret_cast<void**>(&p->d_tab), sizeof(esq::DevQTensor) * tab.size());

@@ -377,7 +377,7 @@ struct StepCover {
         for (uint64_t t = 0; t < taken.size(); ++t) taken[t].assign(steps_of(t), 0);
     }
     // the launch as launch_steps passes it to the kernels
-    void launch(uint64_t first, uint64_t full, uint64_t step0, uint32_t grid) {
+    void launch(uint64_t first, uint64_t full, uint32_t step0, uint32_t grid) {
         const StepShape sh{full_shift, static_cast<uint32_t>(step0), n_full - first, index};
         for (uint64_t i = 0; i < grid; ++i) {
             const StepItem it = step_item(i, full, sh, tiles.data() + first);
@@ -433,8 +433,8 @@ void test_step_launches(std::mt19937_64& rng) {
         for (const uint64_t cap : {kMaxStepGrid, uint64_t(1000), uint64_t(16)}) {
             c.reset();
             uint64_t launches = 0, items = 0;
-            for_step_launches(n_full, c.index.n_steps, c.full_shift, 0,
-                              [&](uint64_t first, uint64_t full, uint64_t step0, uint32_t grid) {
+            for_step_launches(n_full, c.index.n_steps, c.full_shift,
+                              [&](uint64_t first, uint64_t full, uint32_t step0, uint32_t grid) {
                                   check(grid > 0 && grid <= cap, "step launches: grid");
                                   c.launch(first, full, step0, grid);
                                   ++launches;
@@ -460,8 +460,8 @@ void test_step_launches(std::mt19937_64& rng) {
                     const uint32_t shift = full_tile_shift(tile, groups);
                     uint64_t f = 0, t = 0;
                     for_step_launches(
-                        n_full, n_steps, shift, 0,
-                        [&](uint64_t first, uint64_t full, uint64_t step0, uint32_t grid) {
+                        n_full, n_steps, shift,
+                        [&](uint64_t first, uint64_t full, uint32_t step0, uint32_t grid) {
                             check(uint64_t(grid) * kStepThreads < (uint64_t(1) << 32),
                                   "step launches: below 2^32 lanes");
                             check(first == f && step0 == t, "step launches: in order");
@@ -474,33 +474,60 @@ void test_step_launches(std::mt19937_64& rng) {
                         });
                     check(f == n_full && t == n_steps, "step launches: every step");
                 }
-    // quantized plans, with the fewest and the most codes per workgroup
-    for (const int threads : {256, 1024})
+    // quantized plans up to the card's memory, with the fewest and the most codes
+    // per workgroup: legal launches
+    for (const uint64_t tile : {16384ull, 65536ull})
         for (const uint64_t codes : {uint64_t(5000), uint64_t(1) << 30, uint64_t(320) << 30}) {
-            es_qplan_t q;
-            q.cus = 256;
-            q.threads = threads;
-            q.numel = codes;
-            const uint64_t tile = uint64_t(q.threads) * q.groups * esq::kQGroup;
-            q.n_full = codes / tile;
-            q.n_tail = 2;
-            q.tail_max = std::min(codes, tile);
-            const QShape sh = qstep_shape(&q);
-            check((uint64_t(sh.full_steps) * kQStepCodes << sh.full_shift) == tile &&
-                      (uint64_t(sh.tail_steps) * kQStepCodes << sh.tail_shift) >= q.tail_max,
-                  "step launches: a quantized tile's steps");
-            uint64_t f = 0, t = 0;
-            for_step_launches(q.n_full, q.n_tail, sh.full_shift, sh.tail_shift,
-                              [&](uint64_t first, uint64_t full, uint64_t tail, uint32_t grid) {
-                                  check(uint64_t(grid) * kStepThreads < (uint64_t(1) << 32) &&
-                                            first == f && tail == t,
-                                        "step launches: quantized");
-                                  f += full;
-                                  t += (grid - (full << sh.full_shift)) >> sh.tail_shift;
-                                  return ES_OK;
-                              });
-            check(f == q.n_full && t == q.n_tail, "step launches: every quantized tile");
+            const uint64_t part = qsteps_per_workgroup(codes, tile, 256) * uint64_t(kQStepCodes);
+            uint32_t shift = 0;
+            while ((part << shift) < tile) ++shift;
+            check(part << shift == tile, "step launches: a quantized tile's steps");
+            for (const bool aligned : {true, false}) {
+                const uint64_t n_full = aligned ? codes / tile : 0;
+                const uint64_t n_steps = (codes - n_full * tile + part - 1) / part;
+                uint64_t f = 0, t = 0;
+                for_step_launches(n_full, n_steps, shift,
+                                  [&](uint64_t first, uint64_t full, uint32_t step0,
+                                      uint32_t grid) {
+                                      check(uint64_t(grid) * kStepThreads < (uint64_t(1) << 32) &&
+                                                first == f && step0 == t,
+                                            "step launches: quantized");
+                                      f += full;
+                                      t += grid - (full << shift);
+                                      return ES_OK;
+                                  });
+                check(f == n_full && t == n_steps, "step launches: every quantized step");
+            }
         }
+    // and their tails: every code beyond a tensor's full tiles in one step of the
+    // entry that a lookup of the step finds (the last one not beyond it), none empty
+    for (int trial = 0; trial < 60; ++trial) {
+        const uint32_t n = 1 + rng() % 200;
+        const uint64_t tile = trial % 2 ? 16384 : 65536, part = kQStepCodes << (rng() % 3);
+        std::vector<esq::DevQTensor> tab(n + 1);
+        uint64_t n_full = 0;
+        for (uint32_t i = 0; i < n; ++i) {
+            tab[i].numel = uint32_t(rng() % 5 == 0 ? 0 : rng() % (trial % 3 ? 400000 : 100));
+            tab[i].first_full = n_full;
+            n_full += rng() % 2 ? tab[i].numel / tile : 0;       // aligned or not
+        }
+        tab[n].first_full = n_full;
+        index_qtails(tab.data(), n, tile, part);
+        std::vector<uint64_t> next(n);
+        for (uint32_t i = 0; i < n; ++i) next[i] = (tab[i + 1].first_full - tab[i].first_full) * tile;
+        bool ok = true;
+        for (uint32_t j = 0; j < tab[n].first_step; ++j) {
+            uint32_t t = 0;
+            for (uint32_t i = 0; i < n; ++i)
+                if (tab[i].first_step <= j) t = i;
+            const uint64_t full = (tab[t + 1].first_full - tab[t].first_full) * tile;
+            const uint64_t e0 = full + (j - tab[t].first_step) * part;
+            ok &= e0 == next[t] && e0 < tab[t].numel;
+            next[t] = std::min<uint64_t>(e0 + part, tab[t].numel);
+        }
+        for (uint32_t i = 0; i < n; ++i) ok &= next[i] == tab[i].numel;
+        check(ok, "step launches: quantized tails");
+    }
 }
 
 // Argument checks that must fail before any device access.
