@@ -1249,7 +1249,12 @@ def _short_name(name, width=90):
     n = name.replace("(anonymous namespace)::", "")
     if n.startswith("void "):
         n = n[5:]
-    n = n.split("(")[0]
+    depth = 0                       # an enum argument holds a parenthesis too
+    for i, c in enumerate(n):
+        depth += (c == "<") - (c == ">")
+        if c == "(" and depth == 0:
+            n = n[:i]
+            break
     return n if len(n) <= width else n[:width - 3] + "..."
 
 

@@ -134,3 +134,18 @@ def test_summarize_joins_labels_with_dispatches(tmp_path):
     import pytest
     with pytest.raises(RuntimeError):
         bench.summarize(str(bad), profiles_dir=str(out))
+
+
+def test_kernel_names_keep_their_template_arguments():
+    ns = "(anonymous namespace)::"
+    for name, short in (
+            (f"void {ns}es_qpass_kernel<({ns}QKind)3, 1>({ns}QPass, {ns}QShape)",
+             "es_qpass_kernel<(QKind)3, 1>"),
+            (f"void {ns}es_perturb_kernel<2, false, 4>({ns}TileDesc const*, unsigned long)",
+             "es_perturb_kernel<2, false, 4>"),
+            (f"void {ns}es_prepare_kernel<{ns}InlineTables>(float const*)",
+             "es_prepare_kernel<InlineTables>"),
+            (f"{ns}es_zero_u64_kernel(unsigned long long*)", "es_zero_u64_kernel"),
+            ("__amd_rocclr_copyBuffer", "__amd_rocclr_copyBuffer")):
+        assert bench._short_name(name) == short
+    assert bench._short_name("void f<" + "x" * 200 + ">(int)") == "f<" + "x" * 85 + "..."
