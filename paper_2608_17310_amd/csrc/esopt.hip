@@ -1923,11 +1923,14 @@ int launch_qpass(es_qplan_t* p, QKind kind, const QPass& ps, hipStream_t s) {
 }
 
 // The kernel argument of one perturbation member of a quantized pass: its
-// key and sign * sigma * sqrt(2 ln 2) (a restore negates in the kernel).
+// key and sign * sigma * sqrt(2 ln 2) (a restore negates in the kernel), kept
+// finite so that its product with the zero that stands for an invalid scale's
+// reciprocal is zero and not a NaN.
 Member qmember(uint64_t seed, int32_t sign, float sigma) {
-    const double coef = sign > 0 ? double(sigma) : -double(sigma);
+    const double w = std::min(double(sigma) * kSqrt2Ln2Double,
+                              double(std::numeric_limits<float>::max()));
     return Member{static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32),
-                  static_cast<float>(coef * kSqrt2Ln2Double), 0u};
+                  static_cast<float>(sign > 0 ? w : -w), 0u};
 }
 
 int qperturb_impl(es_qplan_t* p, uint64_t seed, int32_t sign, float sigma, es_stream_t stream,

@@ -530,6 +530,18 @@ void test_step_launches(std::mt19937_64& rng) {
     }
 }
 
+// A quantized member's coefficient is finite for every sigma a call takes.
+void test_qmember() {
+    for (const float sigma : {1e-3f, 2.8e38f, 2.9e38f, std::numeric_limits<float>::max()})
+        for (const int32_t sign : {1, -1}) {
+            const float w = qmember(7, sign, sigma).w_k;
+            const double exact = sign * double(sigma) * kSqrt2Ln2Double;
+            check(std::isfinite(w) && (w > 0) == (sign > 0), "quantized member: finite");
+            check(std::abs(exact) > 3.4e38 || std::abs(w - exact) <= std::abs(exact) * 0x1p-24,
+                  "quantized member: coefficient");
+        }
+}
+
 // Argument checks that must fail before any device access.
 void test_validation() {
     const uint64_t seeds[3] = {1, 2, 3};
@@ -618,6 +630,7 @@ int main() {
     test_row_divisor(rng);
     test_qblock_geometry(rng);
     test_step_launches(rng);
+    test_qmember();
     test_validation();
     if (g_failures) {
         std::printf("%d failures\n", g_failures);

@@ -257,6 +257,24 @@ def test_int8_steps_beyond_every_code(sigma):
         assert np.array_equal(flat[:5000].cpu().numpy(), -want)
 
 
+@pytest.mark.parametrize("fmt", ["int8", "e4m3"])
+def test_invalid_scales_keep_their_codes_at_the_largest_sigma(fmt):
+    """sigma sqrt(2 ln 2) is beyond binary32 at sigma 3e38; rows whose scale is
+    not a normal positive finite value keep every code all the same."""
+    rows, n = 64, 6 * 64
+    codes = np.arange(n).astype(np.uint8) if fmt == "e4m3" else np.arange(n).astype(np.int8)
+    flat = torch.from_numpy(codes).cuda()
+    s = np.array([0.0, -1.0, np.inf, np.nan, 1e-40, 1e-3], dtype=np.float32)
+    with esopt.QPlan([flat], [torch.from_numpy(s).cuda()], [rows], format=fmt) as plan:
+        plan.perturb(3, 1, 3e38)
+        plan.swap(3, 1, 4, -1, 3e38)
+        plan.restore(4, -1, 3e38)
+    torch.cuda.synchronize()
+    got = flat.cpu().numpy()
+    assert np.array_equal(got[:5 * rows], codes[:5 * rows])
+    assert np.mean(got[5 * rows:] != codes[5 * rows:]) > 0.9
+
+
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 128, 129, 1024])
 def test_populations_at_the_table_limits(n):
     """Up to 128 members the tables travel in the kernel arguments, above that
