@@ -31,8 +31,6 @@ def test_random_layout(case, monkeypatch):
     threads, groups = SHAPES[rng.integers(len(SHAPES))]
     monkeypatch.setenv("ESOPT_THREADS", str(threads))
     monkeypatch.setenv("ESOPT_GROUPS", str(groups))
-    monkeypatch.setenv("ESOPT_PERTURB_WG_PER_CU", str(int(rng.integers(1, 4))))
-    monkeypatch.setenv("ESOPT_UPDATE_WG_PER_CU", str(int(rng.integers(1, 9))))
     n_t = int(rng.integers(1, 25))
     sizes = [int(x) for x in np.where(rng.random(n_t) < 0.15, rng.integers(0, 20, n_t),
                                       rng.integers(1, 300_000, n_t))]
@@ -126,8 +124,6 @@ def test_random_master_layout(case, monkeypatch):
     threads, groups = SHAPES[rng.integers(len(SHAPES))]
     monkeypatch.setenv("ESOPT_THREADS", str(threads))
     monkeypatch.setenv("ESOPT_GROUPS", str(groups))
-    monkeypatch.setenv("ESOPT_PERTURB_WG_PER_CU", str(int(rng.integers(1, 4))))
-    monkeypatch.setenv("ESOPT_UPDATE_WG_PER_CU", str(int(rng.integers(1, 9))))
     n_t = int(rng.integers(1, 17))
     sizes = [int(x) for x in np.where(rng.random(n_t) < 0.15, rng.integers(0, 20, n_t),
                                       rng.integers(1, 300_000, n_t))]
@@ -221,7 +217,6 @@ def test_random_int8_layout(case, monkeypatch):
     threads, groups = SHAPES[rng.integers(len(SHAPES))]
     monkeypatch.setenv("ESOPT_THREADS", str(threads))
     monkeypatch.setenv("ESOPT_QGROUPS", str(groups))
-    monkeypatch.setenv("ESOPT_UPDATE_WG_PER_CU", str(int(rng.integers(1, 9))))
     n_t = int(rng.integers(1, 16))
     sizes = [int(x) for x in rng.integers(1, 400_000, n_t)]
     rows = [int(rng.choice([0, 8, 24, 64, 1024, 5120])) for _ in range(n_t)]

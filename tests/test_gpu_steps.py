@@ -302,10 +302,14 @@ def test_populations_at_the_table_limits(n):
     assert_parity(rep, f"population of {n}")
 
 
-def test_checksum_of_a_plan_of_whole_tiles_is_its_parts():
-    """40 M elements run whole tiles over the grid, an eighth of them tiles cut
-    in eighths or halves; the parts' checksums add up to the whole's, and the
-    last part's is the oracle's."""
+@pytest.mark.parametrize("per_cu", [None, "1"])
+def test_checksum_of_a_plan_of_whole_tiles_is_its_parts(per_cu, monkeypatch):
+    """40 M elements run whole tiles, one per workgroup or, with a workgroup per
+    compute unit, two or three in turn, an eighth of them tiles cut in eighths or
+    halves; the parts' checksums add up to the whole's, and the last part's is
+    the oracle's."""
+    if per_cu is not None:
+        monkeypatch.setenv("ESOPT_UPDATE_WG_PER_CU", per_cu)
     n = 40_000_000 + 24
     bits = wl.random_bf16_bits(n, 8)
     t = to_device(bits)
@@ -334,3 +338,105 @@ def test_every_element_of_many_steps_is_passed_over_once():
     eps = esopt.normals(21, 6, 0, n)
     torch.cuda.synchronize()
     assert bool(((t.float() - SIGMA * eps).abs() <= 3.92e-3 * SIGMA * eps.abs() + 1e-9).all())
+
+
+@pytest.mark.parametrize("per_cu", ["1", "8"])
+def test_quantized_checksum_of_whole_tiles_is_its_parts(per_cu, monkeypatch):
+    """The same for codes (610 tiles of 65 536)."""
+    monkeypatch.setenv("ESOPT_UPDATE_WG_PER_CU", per_cu)
+    n, s = 40_000_000 + 32, torch.ones(1, device="cuda")
+    codes = np.random.default_rng(9).integers(-127, 128, n).astype(np.int8)
+    t = torch.from_numpy(codes).cuda()
+    cuts = [0, 16 * 30_000, 16 * 900_000, n - 100_003 - (n - 100_003) % 16, n]
+    with esopt.QPlan([t], [s], [0], tensor_ids=[3]) as plan:
+        whole = plan.checksum()
+    total = 0
+    for a, b in zip(cuts, cuts[1:]):
+        with esopt.QPlan([t[a:b]], [s], [0], tensor_ids=[3], offsets=[a]) as part:
+            last = part.checksum()
+            total += last
+    assert whole == total % (1 << 64)
+    assert last == oracle.qchecksum(codes[cuts[-2]:], 3, cuts[-2])
+
+
+# ---------------------------------------------------- cuts chosen by plan size --
+# Groups per lane, the steps' order over the XCDs and the quantized passes' steps
+# per workgroup follow from a plan's size, so one large plan is compared with the
+# plans of its parts, which are too small for any of them: the same bits.
+
+def test_parts_of_a_plan_hold_the_bits_of_the_whole():
+    """20 M elements take four groups per lane in full tiles and runs of steps per
+    XCD, a tenth of them two groups and no runs."""
+    n, parts = 20_000_003, 10
+    cuts = [n * i // parts // 8 * 8 for i in range(parts)] + [n]
+    bits = to_device(wl.random_bf16_bits(n, 71))
+    master = bits.float() + 1e-5
+    r = torch.from_numpy(REWARDS).cuda()
+
+    def run(spans):
+        t, m, seen = bits.clone(), master.clone(), []
+        plans = [esopt.Plan([t[a:b]], tensor_ids=[9], offsets=[a]) for a, b in spans]
+        for i, (p, (a, b)) in enumerate(zip(plans, spans)):
+            own = torch.zeros(b - a, device="cuda").copy_(m[a:b])     # 16-byte aligned
+            p.set_master([own])
+            spans[i] = (a, b, own)
+
+        def each(call):
+            for p in plans:
+                call(p)
+            seen.append(t.clone())
+        each(lambda p: p.perturb(5, -1, SIGMA))
+        each(lambda p: p.swap(5, -1, 6, 1, SIGMA))
+        each(lambda p: p.swap(6, 1, 6, -1, SIGMA))
+        each(lambda p: p.stream_pass())
+        each(lambda p: p.restore_update(6, -1, SIGMA, [6, 7], [-1, 1], r[:2], ALPHA))
+        each(lambda p: p.update(SEEDS, SIGNS, r, ALPHA, flags=esopt.ES_UPDATE_STOCHASTIC_ROUND,
+                                round_seed=4))
+        each(lambda p: p.perturb_master(8, 1, SIGMA))
+        each(lambda p: p.update(SEEDS, SIGNS, r, ALPHA, flags=esopt.ES_UPDATE_MASTER))
+        seen.append(torch.cat([own for *_, own in spans]))
+        each(lambda p: p.perturb_master(8, 1, 0.0))
+        torch.cuda.synchronize()
+        for p in plans:
+            p.close()
+        return seen
+    for i, (x, y) in enumerate(zip(run([(0, n)]), run(list(zip(cuts, cuts[1:]))))):
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), i
+
+
+@pytest.mark.parametrize("fmt", ["int8", "e4m3"])
+@pytest.mark.parametrize("n", [51_000_000, 101_000_000, 202_000_000])
+def test_parts_of_a_quantized_plan_hold_the_codes_of_the_whole(fmt, n):
+    """Two, four and eight steps per workgroup against the one of the parts; the
+    whole at an odd base too, where all of it is tail steps."""
+    row, parts = 64, 5
+    n -= n % row
+    cuts = [n * i // parts // row * row for i in range(parts)] + [n]
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    codes = torch.randint(0, 127, (n,), device="cuda", dtype=torch.uint8, generator=gen)
+    scales = torch.empty(n // row, device="cuda").uniform_(4e-4, 9e-4, generator=gen)
+    r = torch.from_numpy(REWARDS).cuda()
+
+    def run(spans, pad=0):
+        buf = torch.zeros(n + 16, dtype=torch.uint8, device="cuda")
+        t, seen = buf[pad:pad + n].copy_(codes), []
+        v = t if fmt == "e4m3" else t.view(torch.int8)
+        plans = [esopt.QPlan([v[a:b]], [scales[a // row:b // row].clone()], [row],
+                             tensor_ids=[9], offsets=[a], format=fmt) for a, b in spans]
+
+        def each(call):
+            for p in plans:
+                call(p)
+            seen.append(t.clone())
+        each(lambda p: p.perturb(5, -1, SIGMA))
+        each(lambda p: p.swap(5, -1, 6, 1, SIGMA))
+        each(lambda p: p.restore(6, 1, SIGMA))
+        each(lambda p: p.update(SEEDS, SIGNS, r, ALPHA, round_seed=4))
+        torch.cuda.synchronize()
+        for p in plans:
+            p.close()
+        return seen
+    want = run(list(zip(cuts, cuts[1:])))
+    for pad in (0, 3):
+        for i, (x, y) in enumerate(zip(run([(0, n)], pad), want)):
+            assert torch.equal(x, y), (pad, i)

@@ -11,7 +11,7 @@ import pytest
 
 from paper_2608_17310_amd import esopt
 
-TILE = 1024 * 8 * 8            # default launch shape: 1024 lanes x 8 groups x 8 elements
+TILE = 1024 * 8 * 8            # default tile shape: 1024 lanes x 8 groups x 8 elements
 HI = 1 << 34
 
 
