@@ -308,8 +308,4 @@ __device__ __forceinline__ uint32_t pack_bf16x2_sr(float lo, float hi, uint32_t 
     return (b & 0xFFFF0000u) | (a >> 16);
 }
 
-__device__ __forceinline__ uint16_t to_bf16(float x) {
-    return static_cast<uint16_t>(pack_bf16x2(x, 0.0f) & 0xFFFFu);
-}
-
 }  // namespace es

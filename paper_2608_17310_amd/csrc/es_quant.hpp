@@ -68,11 +68,10 @@ struct DevQTensor {
     uint32_t shift;
     uint32_t first_step;                        // steps of the tails before this one's (a pass's
                                                 //   workgroups over the tails, numbered in order)
-    uint32_t aligned16;                         // base 16-byte aligned
     uint32_t skip;                              // 0, or whole-tensor codes between block rows
     uint32_t cmagic;                            // j / cols (read only when skip > 0)
     uint32_t cshift;
-    uint32_t pad;
+    uint32_t pad[2];
 };
 static_assert(sizeof(DevQTensor) == 80, "quantized tensor table entry layout");
 
@@ -293,18 +292,14 @@ __device__ __forceinline__ int32_t qstep9(int32_t q, float v, int32_t lo) {
     return r;
 }
 
-// Update code: clamp(q + s * floor(d + r 2^-16), -127, 127) with s = -1 when
-// kNegate (a restore subtracts the offset its perturb added).  d + r 2^-16
-// is one fused multiply-add (one rounding of the exact sum).  |d| is capped
-// at 2^30 quanta, far beyond what any code can absorb, so the integer
-// arithmetic cannot overflow.
-template <bool kNegate>
+// Update code: clamp(q + floor(d + r 2^-16), -127, 127).  d + r 2^-16 is one
+// fused multiply-add (one rounding of the exact sum).  |d| is capped at 2^30
+// quanta, far beyond what any code can absorb, so the integer arithmetic cannot
+// overflow.
 __device__ __forceinline__ int32_t qstep(int32_t q, float d, uint32_t draw16) {
     const float dc = __builtin_amdgcn_fmed3f(d, -0x1p30f, 0x1p30f);
     const float v = __builtin_fmaf(static_cast<float>(draw16), 0x1p-16f, dc);
-    const int32_t k = floor_to_int(v);
-    const int32_t x = kNegate ? q - k : q + k;
-    return min(max(x, -127), 127);
+    return min(max(q + floor_to_int(v), -127), 127);
 }
 
 }  // namespace esq

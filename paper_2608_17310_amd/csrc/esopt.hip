@@ -211,7 +211,7 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 #define ES_GLOBAL __attribute__((address_space(1)))
 
 // Load the 8 bf16 of one group (packed in 4 words): one 16-byte load
-// (nontemporal when kNT: the parameters are streamed once per pass).  The
+// (nontemporal: the parameters are streamed once per pass).  The
 // checked path (tail tiles) takes it for every group that lies wholly below
 // the bound `limit`, and 2-byte loads below the bound for a partial group.  A
 // tensor whose base is only 2-byte aligned takes the same 16-byte accesses at
@@ -220,16 +220,16 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 // for its eight.
 typedef uint32_t u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
 
-template <bool kFast, bool kNT>
+template <bool kFast>
 __device__ __forceinline__ void load_group(const uint16_t* __restrict__ p, uint64_t e,
                                            uint64_t limit, uint32_t raw[4]) {
     if (kFast) {
         const ES_GLOBAL u32x4_t* a = (const ES_GLOBAL u32x4_t*)(p + e);
-        const u32x4_t v = kNT ? __builtin_nontemporal_load(a) : *a;
+        const u32x4_t v = __builtin_nontemporal_load(a);
         raw[0] = v.x; raw[1] = v.y; raw[2] = v.z; raw[3] = v.w;
     } else if (e + 8 <= limit) {
         const ES_GLOBAL u32x4_any_t* a = (const ES_GLOBAL u32x4_any_t*)(p + e);
-        const u32x4_t v = kNT ? __builtin_nontemporal_load(a) : *a;
+        const u32x4_t v = __builtin_nontemporal_load(a);
         raw[0] = v.x; raw[1] = v.y; raw[2] = v.z; raw[3] = v.w;
     } else {
         const ES_GLOBAL uint16_t* g = (const ES_GLOBAL uint16_t*)p;
@@ -242,18 +242,16 @@ __device__ __forceinline__ void load_group(const uint16_t* __restrict__ p, uint6
     }
 }
 
-template <bool kFast, bool kNT>
+template <bool kFast>
 __device__ __forceinline__ void store_group(uint16_t* __restrict__ p, uint64_t e, uint64_t limit,
                                             const uint32_t out[4]) {
     const u32x4_t v = {out[0], out[1], out[2], out[3]};
     if (kFast) {
         ES_GLOBAL u32x4_t* a = (ES_GLOBAL u32x4_t*)(p + e);
-        if constexpr (kNT) __builtin_nontemporal_store(v, a);
-        else *a = v;
+        __builtin_nontemporal_store(v, a);
     } else if (e + 8 <= limit) {
         ES_GLOBAL u32x4_any_t* a = (ES_GLOBAL u32x4_any_t*)(p + e);
-        if constexpr (kNT) __builtin_nontemporal_store(v, a);
-        else *a = v;
+        __builtin_nontemporal_store(v, a);
     } else {
         ES_GLOBAL uint16_t* g = (ES_GLOBAL uint16_t*)p;
 #pragma unroll
@@ -271,12 +269,10 @@ __device__ __forceinline__ void store_group(uint16_t* __restrict__ p, uint64_t e
 // bf16 base; element-wise accesses below the bound otherwise.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <bool kFast, bool kNT>
 __device__ __forceinline__ void load_master(uintptr_t mb, uint64_t e, uint64_t limit, float m[8]) {
-    if (kFast || e + 8 <= limit) {
+    if (e + 8 <= limit) {
         const ES_GLOBAL f32x4_t* a = (const ES_GLOBAL f32x4_t*)(mb + 4 * e);
-        const f32x4_t v0 = kNT ? __builtin_nontemporal_load(a) : a[0];
-        const f32x4_t v1 = kNT ? __builtin_nontemporal_load(a + 1) : a[1];
+        const f32x4_t v0 = __builtin_nontemporal_load(a), v1 = __builtin_nontemporal_load(a + 1);
         m[0] = v0.x; m[1] = v0.y; m[2] = v0.z; m[3] = v0.w;
         m[4] = v1.x; m[5] = v1.y; m[6] = v1.z; m[7] = v1.w;
     } else {
@@ -286,20 +282,14 @@ __device__ __forceinline__ void load_master(uintptr_t mb, uint64_t e, uint64_t l
     }
 }
 
-template <bool kFast, bool kNT>
 __device__ __forceinline__ void store_master(uintptr_t mb, uint64_t e, uint64_t limit,
                                              const float m[8]) {
-    if (kFast || e + 8 <= limit) {
+    if (e + 8 <= limit) {
         ES_GLOBAL f32x4_t* a = (ES_GLOBAL f32x4_t*)(mb + 4 * e);
         const f32x4_t v0 = {m[0], m[1], m[2], m[3]};
         const f32x4_t v1 = {m[4], m[5], m[6], m[7]};
-        if constexpr (kNT) {
-            __builtin_nontemporal_store(v0, a);
-            __builtin_nontemporal_store(v1, a + 1);
-        } else {
-            a[0] = v0;
-            a[1] = v1;
-        }
+        __builtin_nontemporal_store(v0, a);
+        __builtin_nontemporal_store(v1, a + 1);
     } else {
         ES_GLOBAL float* g = (ES_GLOBAL float*)mb;
 #pragma unroll
@@ -551,7 +541,7 @@ __global__ __launch_bounds__(kStepThreads) void es_perturb_kernel(const TileDesc
 #pragma unroll
         for (int g = 0; g < kN; ++g) {
             if (kFast || e + g * kSlab < r.limit)
-                load_group<kFast, true>(r.data, e + g * kSlab, r.limit, raw[g]);
+                load_group<kFast>(r.data, e + g * kSlab, r.limit, raw[g]);
             else
                 raw[g][0] = raw[g][1] = raw[g][2] = raw[g][3] = 0u;
         }
@@ -566,7 +556,7 @@ __global__ __launch_bounds__(kStepThreads) void es_perturb_kernel(const TileDesc
 #pragma unroll
         for (int g = 0; g < kN; ++g)
             if (kFast || e + g * kSlab < r.limit)
-                store_group<kFast, true>(r.data, e + g * kSlab, r.limit, raw[g]);
+                store_group<kFast>(r.data, e + g * kSlab, r.limit, raw[g]);
     });
 }
 
@@ -612,7 +602,7 @@ __global__ __launch_bounds__(kStepThreads) void es_apply_master_kernel(
 #pragma unroll
             for (int g = 0; g < kN; ++g) {
                 if (e + g * kSlab < r.limit)
-                    load_master<false, true>(mb, e + g * kSlab, r.limit, m[g]);
+                    load_master(mb, e + g * kSlab, r.limit, m[g]);
                 else
                     for (int k = 0; k < 8; ++k) m[g][k] = 0.0f;
             }
@@ -653,7 +643,7 @@ __global__ __launch_bounds__(kStepThreads) void es_apply_master_kernel(
 #pragma unroll
             for (int g = 0; g < kN; ++g)
                 if (e + g * kSlab < r.limit)
-                    store_group<false, true>(r.data, e + g * kSlab, r.limit, out[g]);
+                    store_group<false>(r.data, e + g * kSlab, r.limit, out[g]);
         }
     });
 }
@@ -676,14 +666,14 @@ __global__ __launch_bounds__(kStepThreads) void es_stream_kernel(const TileDesc*
 #pragma unroll
         for (int g = 0; g < kN; ++g)
             if (kFast || e + g * kSlab < r.limit)
-                load_group<kFast, true>(r.data, e + g * kSlab, r.limit, raw[g]);
+                load_group<kFast>(r.data, e + g * kSlab, r.limit, raw[g]);
         __builtin_amdgcn_sched_barrier(0);      // all loads issued before the first wait
 #pragma unroll
         for (int g = 0; g < kN; ++g)
             if (kFast || e + g * kSlab < r.limit) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) raw[g][k] ^= flip;
-                store_group<kFast, true>(r.data, e + g * kSlab, r.limit, raw[g]);
+                store_group<kFast>(r.data, e + g * kSlab, r.limit, raw[g]);
             }
     });
 }
@@ -770,7 +760,7 @@ __global__ __launch_bounds__(kThreads) void es_checksum_kernel(const TileDesc* _
         for (uint32_t u = u0; u < u0 + slots; ++u) {
             const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
             uint32_t raw[4];
-            load_group<true, true>(r.data, e, r.limit, raw);
+            load_group<true>(r.data, e, r.limit, raw);
             acc += checksum_terms<kGroupElems, 16, false>(raw, noise_index<kRows>(r, e), r.limit,
                                                           salt);
         }
@@ -784,7 +774,7 @@ __global__ __launch_bounds__(kThreads) void es_checksum_kernel(const TileDesc* _
             const uint64_t e = r.elem0 + uint64_t(u * kThreads + threadIdx.x) * kGroupElems;
             if (e >= r.limit) break;
             uint32_t raw[4];
-            load_group<false, true>(r.data, e, r.limit, raw);
+            load_group<false>(r.data, e, r.limit, raw);
             const uint64_t n = noise_index<kRows>(r, e);
             // the bound moves with the index: n + (limit - e) for a row map
             acc += checksum_terms<kGroupElems, 16, true>(raw, n, kRows ? n + (r.limit - e) : r.limit,
@@ -892,7 +882,7 @@ struct RestoreArg {
 // blocks in lockstep, and the step's input is loaded before the member loop
 // and first used after it (or by the reverted member), so its latency lies
 // under the loop.
-template <bool kFast, bool kNT, bool kSR, bool kRows, bool kRestore, int kMaster>
+template <bool kFast, bool kSR, bool kRows, bool kRestore, int kMaster>
 __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
                                             const Member* __restrict__ members,
                                             uint32_t n_distinct, RoundKey rk, RestoreArg rst,
@@ -929,11 +919,11 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
         if (in[g]) {
             if constexpr (kMaster != 0) {
                 float m[8];
-                load_master<kFast, kNT>(mb, eg[g], r.limit, m);
+                load_master(mb, eg[g], r.limit, m);
 #pragma unroll
                 for (int k = 0; k < 8; ++k) raw[g][k] = __builtin_bit_cast(uint32_t, m[k]);
             } else {
-                load_group<kFast, kNT>(r.data, eg[g], r.limit, raw[g]);
+                load_group<kFast>(r.data, eg[g], r.limit, raw[g]);
             }
         } else {
 #pragma unroll
@@ -1011,7 +1001,7 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
             if (add) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) m[k] += a[k];
-                store_master<kFast, kNT>(mb, eg[g], r.limit, m);
+                store_master(mb, eg[g], r.limit, m);
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) out[k] = es::pack_bf16x2(m[2 * k], m[2 * k + 1]);
@@ -1033,7 +1023,7 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
                 out[k] = es::pack_bf16x2(es::bf16_lo(raw[g][k]) + a[2 * k],
                                          es::bf16_hi(raw[g][k]) + a[2 * k + 1]);
         }
-        store_group<kFast, kNT>(r.data, eg[g], r.limit, out);
+        store_group<kFast>(r.data, eg[g], r.limit, out);
     }
 }
 
@@ -1041,7 +1031,7 @@ __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
 // written by es_prepare_kernel): the steps of the full tiles, then those of
 // the tail tiles; with kRows the tiles of strided blocks, through their row
 // maps; with kRestore the member rst reverted in the same pass.
-template <bool kNT, bool kSR, bool kRows, bool kRestore, int kMaster>
+template <bool kSR, bool kRows, bool kRestore, int kMaster>
 __global__ __launch_bounds__(kStepThreads) void es_update_kernel(
     const TileDesc* __restrict__ tiles, uint64_t n_full, const DevRows* __restrict__ rows,
     const Member* __restrict__ members, const UpdateHeader* __restrict__ hdr, RoundKey rk, RestoreArg rst,
@@ -1055,7 +1045,7 @@ __global__ __launch_bounds__(kStepThreads) void es_update_kernel(
     };
     for_steps<kRows, 2>(tiles, n_full, rows, sh,
                         [&](auto full, const TileRef& r, uint64_t tile, uint64_t e) {
-        update_step<decltype(full)::value, kNT, kSR, kRows, kRestore, kMaster>(
+        update_step<decltype(full)::value, kSR, kRows, kRestore, kMaster>(
             r, e, members, n_distinct, rk, rst, add, mbase(r, tile));
     });
 }
@@ -1278,20 +1268,20 @@ ChecksumKernel checksum_kernel(int threads, int groups, bool rows, bool cut) {
 template <bool kRestore>
 UpdateKernel update_kernel_for(bool stochastic, bool rows) {
     if (rows)
-        return stochastic ? es_update_kernel<true, true, true, kRestore, 0>
-                          : es_update_kernel<true, false, true, kRestore, 0>;
-    return stochastic ? es_update_kernel<true, true, false, kRestore, 0>
-                      : es_update_kernel<true, false, false, kRestore, 0>;
+        return stochastic ? es_update_kernel<true, true, kRestore, 0>
+                          : es_update_kernel<false, true, kRestore, 0>;
+    return stochastic ? es_update_kernel<true, false, kRestore, 0>
+                      : es_update_kernel<false, false, kRestore, 0>;
 }
 
 // The update into binary32 masters (mode 1) and the application of members
 // from the masters (mode 2), both rewriting the bf16 values.
 UpdateKernel update_master_kernel(bool rows, bool apply = false) {
     if (apply)
-        return rows ? es_update_kernel<true, false, true, false, 2>
-                    : es_update_kernel<true, false, false, false, 2>;
-    return rows ? es_update_kernel<true, false, true, false, 1>
-                : es_update_kernel<true, false, false, false, 1>;
+        return rows ? es_update_kernel<false, true, false, 2>
+                    : es_update_kernel<false, false, false, 2>;
+    return rows ? es_update_kernel<false, true, false, 1>
+                : es_update_kernel<false, false, false, 1>;
 }
 
 // restore: the update with one member reverted in the same pass.
@@ -1481,7 +1471,7 @@ __device__ __forceinline__ void qstep_group(const esq::QTileRef& r, uint32_t e,
                     const int32_t q = static_cast<int8_t>(raw[k] >> (8 * i));
                     const uint32_t draw = (dw[c >> 1] >> (16 * (c & 1))) & 0xFFFFu;
                     const int32_t v =
-                        inv[c / 8] != 0.0f ? esq::qstep<false>(q, acc[c] * inv[c / 8], draw) : q;
+                        inv[c / 8] != 0.0f ? esq::qstep(q, acc[c] * inv[c / 8], draw) : q;
                     w |= (static_cast<uint32_t>(v) & 0xFFu) << (8 * i);
                 }
                 out[k] = w;
@@ -2073,7 +2063,7 @@ void tile_tensor(uint16_t* data, uint64_t numel, uint64_t offset, uint32_t tenso
         }
     };
     const uintptr_t a = reinterpret_cast<uintptr_t>(data);
-    if (a % 16 != 0) {                                      // element-wise accesses throughout
+    if (a % 16 != 0) {                                      // tail tiles throughout
         for (uint64_t e0 = 0; e0 < numel; e0 += tile_elems)
             add_tail(e0, std::min(numel, e0 + tile_elems), 0u);
         return;
@@ -2182,12 +2172,6 @@ void build_member_tables(const uint64_t* seeds, const int32_t* signs, uint32_t n
     t.n_distinct = nd;
 }
 
-// Hand the population to the device: the member tables go through kernel
-// arguments (staged into the scratch first when they are too many), and one wave z-scores the rewards and
-// merges the weights per distinct seed, leaving the weighted member table
-// and its header in the scratch.  Allocates nothing.  With `find`, *found is
-// set to the distinct-table entry of seed *find before anything is launched
-// (or the call fails with INVALID_ARG when no member has that seed).
 // Host words into device scratch at dst_off, in launches of es_stage_kernel
 // carrying 1 KB of kernel arguments each (no staging buffer, no host
 // synchronisation).
@@ -2207,6 +2191,12 @@ int stage_words(uint8_t* d_scratch, size_t dst_off, const void* src, size_t byte
     return ES_OK;
 }
 
+// Hand the population to the device: the member tables go through kernel
+// arguments (staged into the scratch first when they are too many), and one wave
+// z-scores the rewards and merges the weights per distinct seed, leaving the
+// weighted member table and its header in the scratch.  Allocates nothing.  With
+// `find`, *found is set to the distinct-table entry of seed *find before anything
+// is launched (or the call fails with INVALID_ARG when no member has that seed).
 int prepare_update(uint8_t* d_scratch, const uint64_t* seeds, const int32_t* signs,
                    const float* rewards_dev, uint32_t n_members, const es_update_opts_t* opts,
                    float* z_out_dev, int32_t* status_out_dev, hipStream_t s,
@@ -2589,8 +2579,7 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
         tab[i] = esq::DevQTensor{static_cast<int8_t*>(t.data), t.scales,
                                  static_cast<uint32_t>(t.numel), static_cast<uint32_t>(t.n0),
                                  n_full, n_tail, t.row, t.tensor_id, magic, shift, 0u,
-                                 (a % 16 == 0) ? 1u : 0u, static_cast<uint32_t>(t.skip), cmagic,
-                                 cshift, 0u};
+                                 static_cast<uint32_t>(t.skip), cmagic, cshift, {0u, 0u}};
         if (t.numel > 0) ranges.emplace_back(a, a + t.numel);
         n_full += full;
         n_tail += tail;
@@ -2601,7 +2590,7 @@ int qplan_build(const std::vector<QSpec>& specs, uint32_t format, es_qplan_t** o
         if (ranges[i].first < ranges[i - 1].second)
             return fail(ES_ERR_INVALID_ARG, nm + ": " + kind + "s overlap in memory");
     tab[n_tensors] = esq::DevQTensor{nullptr, nullptr, 0u, 0u, n_full, n_tail, 0u, 0xFFFFFFFFu,
-                                     0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+                                     0u, 0u, 0u, 0u, 0u, 0u, {0u, 0u}};
 
     int device = -1;
     int rc = current_device(&device);
