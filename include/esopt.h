@@ -170,9 +170,11 @@ uint64_t es_plan_device_bytes(const es_plan_t* plan);
 
 /* Perturb in place (Section 3; Appendix D.6):
  *   theta_j <- RNE_bf16(theta_j + sign * sigma * eps_j(seed))
- * for every element of every tensor of the plan, one kernel launch.
- * sign is +1 or -1 (antithetic member); sigma is finite and >= 0; sigma == 0
- * leaves theta bit-for-bit unchanged and launches nothing. */
+ * for every element of every tensor of the plan, one kernel launch (one per
+ * part of a plan that has strided blocks, and several where a pass takes 2^32
+ * lanes or more: an update from 2^36 elements on, this from 2^37).  sign is +1 or
+ * -1 (antithetic member); sigma is finite and >= 0; sigma == 0 leaves theta
+ * bit-for-bit unchanged and launches nothing. */
 int es_perturb(es_plan_t* plan, uint64_t seed, int32_t sign, float sigma, es_stream_t stream);
 
 /* Revert a perturbation (Section 3; Appendix D.6): es_perturb with -sign,

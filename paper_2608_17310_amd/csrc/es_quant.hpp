@@ -25,7 +25,7 @@
 // Layout: a lane owns 16 consecutive codes (one 16-byte access, four Philox
 // blocks in lockstep); a tile is T lanes x U groups x 16 codes, taken in steps
 // of 256 groups.  All passes are VALU-bound (16 normals per 16 bytes).  Of the
-// int8 perturbation's 23.5 instructions per code 15.2 are the noise; the
+// int8 perturbation's 24.4 instructions per code 15.2 are the noise; the
 // step's float work is done for the 16 codes in a simple phase and its
 // conversions, saturating sums, clamps and packing in a heavy one (swap over
 // the 0.5B-shaped set 563 us without the split, 524 with it).

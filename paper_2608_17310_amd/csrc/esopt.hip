@@ -26,14 +26,16 @@
 //     counter's high word is uniform per tile.
 //   * The passes run in 256-lane workgroups of one step each (StepShape): two
 //     or four 8-element groups per lane, loaded in one burst and stored in
-//     one, dispatched in the order of the plan's memory.  Perturb is
-//     HBM-bound: 0.5B-shaped set, perturb and restore, 678 -> 610 us (5.70 ->
-//     6.33 TB/s), against one 1024-lane workgroup per CU that strode over the
+//     one, dispatched in the order of the plan's memory, the tail tiles' steps
+//     (TailIndex) after the full tiles'.  Perturb is
+//     HBM-bound: 0.5B-shaped set, perturb and restore, 678 -> 600 us (5.70 ->
+//     6.44 TB/s), against one 1024-lane workgroup per CU that strode over the
 //     tiles with its next tile's loads in flight.  The update is VALU-bound
 //     (N noise streams per element): two groups per lane, so that four Philox
-//     blocks run in lockstep (es_noise.hpp) and six or seven waves per SIMD
-//     pair their issue.  4B-shaped set, N = 32: 50.8 -> 43.7 ms.  Swap is the
-//     perturb kernel with two streams and a bf16 rounding between them.
+//     blocks run in lockstep (es_noise.hpp) and the waves of a SIMD (70 - 76
+//     VGPRs: seven or six; 84 into masters: five) pair their issue.  4B-shaped
+//     set, N = 32: 50.8 -> 43.0 ms.  Swap is the perturb kernel with two streams
+//     and a bf16 rounding between them.
 //   * The quantized path (int8 codes, es_quant.hpp; fp8 E4M3 codes,
 //     es_fp8.hpp) has a tensor table, searched once per workgroup, and
 //     256-lane workgroups of up to eight steps of one 16-code group per lane;
@@ -575,24 +577,25 @@ __device__ __forceinline__ uintptr_t master_base(const uint64_t* __restrict__ md
 // two loads of 16 bytes at a 32-byte stride, and streamed lines were fetched
 // twice), and an 8-byte bf16 store 512 consecutive bytes.  A quad is one Philox
 // block: its two Box-Muller pairs are its elements.  Tail tiles take the groups
-// of the other passes with bounds-checked accesses.
-template <bool kRows, int kG>
+// of the other passes with bounds-checked accesses.  Two groups per lane (57
+// VGPRs, eight waves per SIMD) and four (88, five): 0.5B-shaped set 465 and 477
+// us, 4B 3875 and 3961, 503 M in column blocks 498 and 507.
+template <bool kRows>
 __global__ __launch_bounds__(kStepThreads) void es_apply_master_kernel(
     const TileDesc* __restrict__ tiles, uint64_t n_full, const DevRows* __restrict__ rows,
     Streams st, const uint64_t* __restrict__ mdelta, StepShape sh) {
     typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
     constexpr uint64_t kSlab = uint64_t(kStepThreads) * kGroupElems;
-    for_steps<kRows, kG>(tiles, n_full, rows, sh,
+    for_steps<kRows, 2>(tiles, n_full, rows, sh,
                          [&](auto full, const TileRef& r, uint64_t tile, uint64_t e) {
         constexpr bool kFast = decltype(full)::value;
-        constexpr int kN = kFast ? kG : 2;
         const uintptr_t mb = master_base(mdelta, r, tile);
         const uint32_t q_hi = tile_high_word<kRows>(r);
-        float m[kN][8];
+        float m[2][8];
         if constexpr (kFast) {
             const uint64_t e4 = e - threadIdx.x * 4u;        // the lane's first quad
 #pragma unroll
-            for (int i = 0; i < 2 * kN; ++i) {
+            for (int i = 0; i < 4; ++i) {
                 const f32x4_t v = __builtin_nontemporal_load(
                     (const ES_GLOBAL f32x4_t*)(mb + 4 * (e4 + i * (kSlab / 2))));
                 float* x = m[i / 2] + 4 * (i % 2);
@@ -600,7 +603,7 @@ __global__ __launch_bounds__(kStepThreads) void es_apply_master_kernel(
             }
         } else {
 #pragma unroll
-            for (int g = 0; g < kN; ++g) {
+            for (int g = 0; g < 2; ++g) {
                 if (e + g * kSlab < r.limit)
                     load_master(mb, e + g * kSlab, r.limit, m[g]);
                 else
@@ -608,40 +611,34 @@ __global__ __launch_bounds__(kStepThreads) void es_apply_master_kernel(
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        uint32_t out[kN][4];
+        uint32_t out[2][4];
+        uint32_t q[4];
+        if constexpr (kFast) {
 #pragma unroll
-        for (int g = 0; g < kN; g += 2) {
-            uint32_t q[4];
-            if constexpr (kFast) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    q[i] = static_cast<uint32_t>(
-                        noise_index<kRows>(r, e - threadIdx.x * 4u + (2 * g + i) * (kSlab / 2)) >>
-                        2);
-            } else {
-                const uint64_t n[2] = {noise_index<kRows>(r, e + g * kSlab),
-                                       noise_index<kRows>(r, e + (g + 1) * kSlab)};
-                pair_quads(n, q);
-            }
-            es::Words w[4];
-            float rad[8], c[8], sn[8];
-            es::philox_quads<4>(q, q_hi, r.tensor_id, st.k0[0], st.k1[0], w);
-            es::box_muller_quads<4>(w, rad, c, sn);
-            pair_axpy(rad, c, sn, st.coef_k[0], &m[g][0]);
-            pack_pair(&m[g][0], out + g);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < 4; ++i)
+                q[i] = static_cast<uint32_t>(
+                    noise_index<kRows>(r, e - threadIdx.x * 4u + i * (kSlab / 2)) >> 2);
+        } else {
+            const uint64_t n[2] = {noise_index<kRows>(r, e), noise_index<kRows>(r, e + kSlab)};
+            pair_quads(n, q);
         }
+        es::Words w[4];
+        float rad[8], c[8], sn[8];
+        es::philox_quads<4>(q, q_hi, r.tensor_id, st.k0[0], st.k1[0], w);
+        es::box_muller_quads<4>(w, rad, c, sn);
+        pair_axpy(rad, c, sn, st.coef_k[0], &m[0][0]);
+        pack_pair(&m[0][0], out);
         if constexpr (kFast) {
             const uint64_t e4 = e - threadIdx.x * 4u;
 #pragma unroll
-            for (int i = 0; i < 2 * kN; ++i) {
+            for (int i = 0; i < 4; ++i) {
                 const u32x2_t v = {out[i / 2][2 * (i % 2)], out[i / 2][2 * (i % 2) + 1]};
                 __builtin_nontemporal_store(v,
                                             (ES_GLOBAL u32x2_t*)(r.data + e4 + i * (kSlab / 2)));
             }
         } else {
 #pragma unroll
-            for (int g = 0; g < kN; ++g)
+            for (int g = 0; g < 2; ++g)
                 if (e + g * kSlab < r.limit)
                     store_group<false>(r.data, e + g * kSlab, r.limit, out[g]);
         }
@@ -878,10 +875,9 @@ struct RestoreArg {
 // masters in registers, m + sum w eps with one rounding for one member (the
 // accumulation starts from m), and only the bf16 values are written.
 //
-// VALU-bound (about 12.7 issue slots per normal, es_noise.hpp): four Philox
-// blocks in lockstep, and the step's input is loaded before the member loop
-// and first used after it (or by the reverted member), so its latency lies
-// under the loop.
+// VALU-bound (es_noise.hpp): four Philox blocks in lockstep, and the step's
+// input is loaded before the member loop and first used after it (or by the
+// reverted member), so its latency lies under the loop.
 template <bool kFast, bool kSR, bool kRows, bool kRestore, int kMaster>
 __device__ __forceinline__ void update_step(const TileRef& r, uint64_t e,
                                             const Member* __restrict__ members,
@@ -1242,9 +1238,8 @@ PerturbKernel perturb_kernel(int streams, bool rows) {
     }
 }
 
-template <int kG>
 ApplyMasterKernel apply_master_kernel(bool rows) {
-    return rows ? es_apply_master_kernel<true, kG> : es_apply_master_kernel<false, kG>;
+    return rows ? es_apply_master_kernel<true> : es_apply_master_kernel<false>;
 }
 
 // Tile shapes instantiated: T lanes per workgroup x U groups per lane.
@@ -1785,11 +1780,17 @@ int launch_steps(const es_plan_t* p, const Segment& g, int groups, const uint64_
         });
 }
 
-// Groups per lane and step of the memory-bound passes in full tiles: four, or two where
-// four would leave wave slots empty (fewer than eight workgroups per CU, 16.8 M
-// elements).  A perturb pass in a graph, two and four groups: 1 M elements 2.8
-// and 3.4 us, 8.4 M 7.7 and 8.0, 16.8 M 12.2 and 12.0, 134 M 85.1 and 83.7, 537
-// M 346 and 332.
+// Groups per lane and step of perturb, swap and the stream pass in full tiles:
+// four, or two where four would leave wave slots empty (fewer than eight
+// workgroups per CU, 16.8 M elements).  Two and four groups, us:
+//   perturb: 1 M elements 2.8 and 3.4, 8.4 M 7.7 and 8.0, 21 M 14.3 and 14.5,
+//   50 M 33.0 and 32.7, 134 M 85.7 and 84.7, 537 M 338.4 and 337.5;
+//   same-key swap: 21 M 14.4 and 14.8, 134 M 85.3 and 84.0, 537 M 340 and 335;
+//   two-key swap: 17 M 19.6 and 19.8, 21 M 21.6 and 20.6, 134 M 123 and 119,
+//   4 G 3780 and 3640, 22.7 G 21 560 and 20 880 (eight waves per SIMD with two,
+//   five with four: these passes don't lack waves).
+// Over the largest sets two are better for a single key, perturb 4 G 2527 and
+// 2584, 22.7 G 14 250 and 15 000, the stream pass alike, and follow the same rule.
 bool four_groups(const es_plan_t* p, const Segment& g) {
     const uint64_t elems = g.n_full * p->tile_elems;
     return elems >= uint64_t(p->cus) * 8 * (kStepThreads * 4 * kGroupElems);
@@ -1797,7 +1798,7 @@ bool four_groups(const es_plan_t* p, const Segment& g) {
 
 // A checksum launch: tiles cut in halves down to single group slots while that
 // gives at most kSumItems workgroups, each with one atomic on the result, else
-// whole tiles over `grid` workgroups.  1 M parameters: 29 us whole, 14 in
+// whole tiles over `grid` workgroups.  1 M parameters: 29 us whole, 12 in
 // slots; 24 M in 200 odd-sized tensors 46 whole, 34 in halves (800 workgroups),
 // 54 in slots (3600); 60 M in 216 (1800 halves) stay whole, 51 us.
 struct SumLaunch {
@@ -2862,11 +2863,9 @@ int es_perturb_master(es_plan_t* plan, uint64_t seed, int32_t sign, float sigma,
         for (int k = 0; k < n_seg; ++k) {
             const Segment& g = seg[k];
             const bool strided = g.rows != nullptr;
-            const bool four = four_groups(plan, g);
-            const ApplyMasterKernel kernel = four ? apply_master_kernel<4>(strided)
-                                                  : apply_master_kernel<2>(strided);
+            const ApplyMasterKernel kernel = apply_master_kernel(strided);
             rc = launch_steps(
-                plan, g, four ? 4 : 2,
+                plan, g, 2,
                 plan->d_master + (strided ? plan->n_full + plan->n_tail : 0),
                 "es_perturb_master", ": es_apply_master_kernel", [&](const StepLaunch& l) {
                     hipLaunchKernelGGL(kernel, l.grid, dim3(kStepThreads), 0, s, l.tiles,
