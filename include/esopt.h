@@ -367,7 +367,7 @@ int es_plan_checksum(es_plan_t* plan, uint64_t* out_dev, es_stream_t stream);
  * value are left unchanged, -128 included. */
 typedef struct es_qtensor {
     void*        data;       /* device int8 codes, contiguous; any alignment
-                                (16-byte aligned data takes the vector path) */
+                                (16-byte aligned data streams fastest) */
     const float* scales;     /* device binary32 scales, ceil(numel / row)
                                 entries (1 when row == 0), 4-byte aligned */
     uint64_t     numel;      /* < 2^31 */

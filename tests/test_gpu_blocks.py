@@ -88,7 +88,7 @@ def test_column_shards_of_a_matrix():
 
 def test_row_and_column_blocks_with_ragged_edges():
     """A 3 x 4 grid of blocks of uneven sizes, the narrowest 8 columns wide,
-    including 2-byte-aligned copies (element-wise path)."""
+    including 2-byte-aligned copies (tail tiles throughout)."""
     rows, cols = 531, 2200
     bits = wl.random_bf16_bits(rows * cols, 62)
     _grid_blocks(bits, rows, cols, [0, 1, 260, rows], [0, 8, 1000, 2192, cols], [0, 3, 120, 1])
@@ -205,7 +205,7 @@ def test_block_matches_oracle_at_whole_tensor_indices_across_2_34(pad):
     from below to above whole-tensor element 2^34, which falls inside one of
     the block's rows (the counter's high word changes mid-row and mid-tile),
     checked element by element against the oracle after every pass; pad 1
-    puts it at a 2-byte-aligned address (element-wise accesses)."""
+    puts it at a 2-byte-aligned address (tail tiles throughout)."""
     row_len = (1 << 20) + 4096
     rows, cols = 64, 1024
     row0 = (1 << 34) // row_len - rows // 2

@@ -8,7 +8,7 @@ sides of the tile transitions the plan actually lays out for that tensor
 (taken from the library's own tiling, es_tile_layout, at the tensor's
 address): the head tail into the first full tile, the first and the last
 full-to-full transitions, and the last full tile into the trailing tail, so
-that the pipelined full-tile path and the bounds-checked tail path are both
+that the full-tile path and the bounds-checked tail path are both
 sampled where they meet."""
 import numpy as np
 import pytest

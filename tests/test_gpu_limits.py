@@ -129,6 +129,7 @@ def test_update_of_a_plan_beyond_one_launch():
     Elements around the start, the cut between them, a counter's high word and
     the end, each pass against the oracle."""
     n = (1 << 36) + 3 * 65536 + 4099
+    torch.cuda.empty_cache()
     if torch.cuda.mem_get_info()[0] < 2 * n + (8 << 30):
         pytest.skip("not enough free device memory")
     t = torch.zeros(n, dtype=torch.bfloat16, device="cuda")
@@ -167,4 +168,6 @@ def test_update_of_a_plan_beyond_one_launch():
                   "update beyond 2^36")
     # 256 elements in every 2^30 held zeros, which the passes left as noise
     far = torch.stack([t[k << 30:(k << 30) + 256] for k in range(1, 64)])
+    del t
+    torch.cuda.empty_cache()                            # the library allocates outside the cache
     assert int((far != 0).sum()) > 0.99 * far.numel()
